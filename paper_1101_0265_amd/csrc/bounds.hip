@@ -5,8 +5,8 @@
 //
 // Lanczos with full reorthogonalisation runs on the device: the symmetric matrix-vector
 // product reads only the upper triangle of the matrix in 64x64 tiles (row part and
-// transposed column part of each off-diagonal tile from one LDS copy; HBM-bound, one pass over
-// half the matrix per product), the Gram-Schmidt passes are fixed-order reductions, so every
+// transposed column part of each off-diagonal tile from one copy in registers; bound by one
+// pass over half the matrix per product), the Gram-Schmidt passes are fixed-order reductions, so every
 // run gives the same tridiagonal bit for bit.  The host diagonalises the small tridiagonal
 // (implicit QR) and forms the bounds.
 #include <hip/hip_runtime.h>
@@ -43,91 +43,170 @@ constexpr double kBreakdown = 1e-12;
 struct SymvArgs {
   const double* M;
   int64_t ld, n, np;
-  int nv;
-  int abs_mode;                 // 1: use |M| (Gershgorin row sums)
+  int nv, strip;                // vectors; tiles per strip
   const double* x[2];
   double* y[2];
   double a[2], b[2];
-  double* part;                 // [nt][nt][nv][2 kT]: row part, then column part
+  double* part;                 // [nt][nt][nv][kT] column parts, then [nt][nt][nv][kT] row parts
+  // x_v is not normalised yet: its squared norm in nt partial sums, the normalised vector's
+  // place, and the norm's (or null); null: x_v is used as it is
+  const double* nrm2[2];
+  double* vout[2];
+  double* beta[2];
+  // last product of a Lanczos step: h_k = V_k . y_v for k <= j, block partials [k][nt]
+  const double* V[2];
+  double* hp[2];
+  int j;
 };
 
-// One workgroup per upper tile (I, J), I <= J: the tile goes to LDS once; the row part
-// M_IJ x_J (for block I) and, off the diagonal, the column part M_IJ^T x_I (for block J).
-// A diagonal tile holds only its upper triangle in memory and is mirrored in LDS.
-__global__ __launch_bounds__(256) void symv_tile_kernel(SymvArgs g, int nt) {
-  const int J = blockIdx.x, I = blockIdx.y;
-  if (I > J) return;
-  __shared__ double tile[kT][kT + 1];
-  __shared__ double xs[2][2][kT];          // [vector][I or J][k]
-  constexpr int kPer = kT * kT / 256;      // values per thread
-  const int t = threadIdx.x;
-  const int64_t r0 = (int64_t)I * kT, c0 = (int64_t)J * kT;
-  double ld[kPer];                         // all loads in flight before the first LDS store
+__device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int idx = e * 256 + t, r = idx / kT, c = idx % kT;
-    ld[e] = (r0 + r < g.n && c0 + c < g.n && (I != J || c >= r))
-                ? g.M[(r0 + r) * g.ld + c0 + c] : 0.0;
-  }
-#pragma unroll
-  for (int e = 0; e < kPer; ++e) {
-    const int idx = e * 256 + t, r = idx / kT, c = idx % kT;
-    tile[r][c] = g.abs_mode ? fabs(ld[e]) : ld[e];
-  }
-  if (t < 2 * kT) {
-    const int which = t / kT, k = t % kT;
-    for (int v = 0; v < g.nv; ++v) xs[v][which][k] = g.x[v][(which ? c0 : r0) + k];
-  }
-  __syncthreads();
-  if (I == J) {
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-      const int idx = e * 256 + t, r = idx / kT, c = idx % kT;
-      if (r > c) tile[r][c] = tile[c][r];
-    }
-    __syncthreads();
-  }
-  const int v = t / (2 * kT), rem = t % (2 * kT);
-  if (v >= g.nv) return;
-  double* out = g.part + (((size_t)I * nt + J) * g.nv + v) * (2 * kT);
-  if (rem < kT) {                           // row part, row rem of block I
-    double s = 0.0;
-    for (int c = 0; c < kT; ++c) s += tile[rem][c] * xs[v][1][c];
-    out[rem] = s;
-  } else if (I != J) {                      // column part, column rem - kT of block J
-    const int c = rem - kT;
-    double s = 0.0;
-    for (int r = 0; r < kT; ++r) s += tile[r][c] * xs[v][0][r];
-    out[rem] = s;
-  }
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
-// y_v[i] = a_v (sum of the row parts of tiles (B, J >= B) and the column parts of tiles
-// (I < B, B)) + b_v x_v[i]; zero beyond n.  One workgroup per row block B and vector: 16
-// groups of 64 threads each take every 16th tile, then the 16 partial sums of a row are
-// added in group order (fixed order, no atomics).
+// The norm from its nt partial sums, by every wave for itself (fixed order).
+__device__ __forceinline__ double norm_of(const double* __restrict__ nrm2, int nt) {
+  double s = 0.0;
+  for (int i = threadIdx.x & 63; i < nt; i += 64) s += nrm2[i];
+  return sqrt(wave_sum(s));
+}
+
+// One workgroup per strip of up to g.strip upper tiles (I, J), (I, J + 1), ... of block row I:
+// the row part sum_J M_IJ x_J (for block I) and each tile's column part M_IJ^T x_I (for block J).
+// Every thread keeps 16 values of the tile in registers (4 rows x 4 columns, 16 apart) and uses
+// each for both parts, the next tile's 16 loads in flight meanwhile; sums run over the 16 lanes
+// of a row once per strip and over the 16 threads of a column once per tile.  19 us with one
+// vector and 24 us with two at n = 4096 (67 MB: 3.5 and 2.8 TB/s).  x through LDS instead, or
+// x_J loaded a tile ahead, cost the two-vector kernel registers (3 -> 2 waves per SIMD) or time
+// (24 -> 26 us).
+template <int NV, bool ABS>
+__global__ __launch_bounds__(256) void symv_tile_kernel(SymvArgs g, int nt) {
+  const int I = blockIdx.y, J0 = I + (int)blockIdx.x * g.strip;
+  if (J0 >= nt) return;
+  const int J1 = min(J0 + g.strip, nt);
+  __shared__ double cs[2][4][NV][kT];      // column sums of the four waves, by tile parity
+  const int t = threadIdx.x, tx = t & 15, ty = t >> 4, wid = t >> 6;
+  const int64_t r0 = (int64_t)I * kT;
+  double m[4][4];
+  auto load = [&](int J, double (&o)[4][4]) {
+    const int64_t c0 = (int64_t)J * kT;
+    const double* p = g.M + (r0 + ty) * g.ld + c0 + tx;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool in = r0 + ty + 16 * q < g.n && c0 + tx + 16 * c < g.n &&
+                        (J != I || tx + 16 * c >= ty + 16 * q);
+        const double e = in ? p[(int64_t)(16 * q) * g.ld + 16 * c] : 0.0;
+        o[q][c] = ABS ? fabs(e) : e;
+      }
+  };
+  load(J0, m);                             // (ahead of the norm, which waits for its own loads)
+  double inv[NV], xi[NV][4], row[NV][4];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    inv[v] = 1.0;
+    if (g.nrm2[v]) {
+      const double nrm = norm_of(g.nrm2[v], nt);
+      inv[v] = nrm > 0.0 ? 1.0 / nrm : 0.0;      // a zero norm leaves zeros: T is cut there
+      if (I == 0 && J0 == 0 && t == 0 && g.beta[v]) *g.beta[v] = nrm;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      row[v][q] = 0.0;
+      xi[v][q] = g.x[v][r0 + ty + 16 * q] * inv[v];
+    }
+    if (J0 == I && g.vout[v] && t < kT) g.vout[v][r0 + t] = g.x[v][r0 + t] * inv[v];
+  }
+  for (int J = J0; J < J1; ++J) {
+    const int par = (J - J0) & 1;
+    double nx[4][4];
+    if (J + 1 < J1) load(J + 1, nx);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      double xj[4], col[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        xj[c] = g.x[v][(int64_t)J * kT + tx + 16 * c] * inv[v];
+        col[c] = 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          row[v][q] += m[q][c] * xj[c];
+          // (a diagonal entry counts once)
+          const double e = (J == I && tx + 16 * c == ty + 16 * q) ? 0.0 : m[q][c];
+          col[c] += e * xi[v][q];
+        }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        col[c] += __shfl_xor(col[c], 16, 64);
+        col[c] += __shfl_xor(col[c], 32, 64);
+        if ((t & 63) < 16) cs[par][wid][v][tx + 16 * c] = col[c];
+      }
+    }
+    __syncthreads();                       // (the other parity's sums were read before this)
+    if (t < NV * kT) {
+      const int v = t / kT, c = t % kT;
+      g.part[(((size_t)I * nt + J) * NV + v) * kT + c] =
+          ((cs[par][0][v][c] + cs[par][1][v][c]) + cs[par][2][v][c]) + cs[par][3][v][c];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m[q][c] = nx[q][c];
+  }
+  double* rp = g.part + (size_t)nt * nt * NV * kT;
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double s = row[v][q];
+      s += __shfl_xor(s, 1, 64);
+      s += __shfl_xor(s, 2, 64);
+      s += __shfl_xor(s, 4, 64);
+      s += __shfl_xor(s, 8, 64);
+      if (tx == 0) rp[(((size_t)I * nt + blockIdx.x) * NV + v) * kT + ty + 16 * q] = s;
+    }
+}
+
+// y_v[i] = a_v (sum of the row parts of the strips of block row B and the column parts of tiles
+// (I <= B, B)) + b_v x_v[i]; zero beyond n.  One workgroup per row block B and vector: 16 waves
+// each take every 16th part, then the 16 partial sums of a row are added in wave order (fixed
+// order, no atomics).  The last product of a Lanczos step goes on to the block's share of the
+// first Gram-Schmidt pass's dot products, which saves a launch that would read y again.
 __global__ __launch_bounds__(1024) void symv_reduce_kernel(SymvArgs g, int nt) {
   __shared__ double acc[16][kT];
   const int B = blockIdx.x, v = blockIdx.y;
   const int grp = threadIdx.x / kT, r = threadIdx.x % kT;
+  const int ns = (nt - B + g.strip - 1) / g.strip;
+  const double* rp = g.part + (size_t)nt * nt * g.nv * kT;
   double s = 0.0;
-  // tiles of block row B in the order J = B..nt-1, then I = 0..B-1 (column parts)
-  for (int q = grp; q < nt; q += 16) {
-    if (q < nt - B) {
-      const int J = B + q;
-      s += g.part[(((size_t)B * nt + J) * g.nv + v) * (2 * kT) + r];
-    } else {
-      const int I = q - (nt - B);
-      s += g.part[(((size_t)I * nt + B) * g.nv + v) * (2 * kT) + kT + r];
-    }
+  for (int q = grp; q < ns + B + 1; q += 16) {
+    if (q < ns) s += rp[(((size_t)B * nt + q) * g.nv + v) * kT + r];
+    else s += g.part[(((size_t)(q - ns) * nt + B) * g.nv + v) * kT + r];
   }
   acc[grp][r] = s;
   __syncthreads();
-  if (grp != 0) return;
-  double tot = 0.0;
-  for (int k = 0; k < 16; ++k) tot += acc[k][r];
   const int64_t i = (int64_t)B * kT + r;
-  g.y[v][i] = i < g.n ? g.a[v] * tot + g.b[v] * g.x[v][i] : 0.0;
+  if (grp == 0) {
+    double tot = 0.0;
+    for (int k = 0; k < 16; ++k) tot += acc[k][r];
+    // (the normalised x_v, where this product was handed the raw one)
+    const double x = g.b[v] != 0.0 ? (g.vout[v] ? g.vout[v][i] : g.x[v][i]) : 0.0;
+    const double y = i < g.n ? g.a[v] * tot + g.b[v] * x : 0.0;
+    g.y[v][i] = y;
+    acc[0][r] = y;
+  }
+  if (!g.hp[v]) return;
+  __syncthreads();
+  const double y = acc[0][r];
+  for (int k = grp; k <= g.j; k += 16) {
+    const double d = wave_sum(g.V[v][(size_t)k * g.np + i] * y);
+    if (r == 0) g.hp[v][(size_t)k * nt + B] = d;
+  }
 }
 
 // d[i] = M[i][i] for i < n.
@@ -141,85 +220,70 @@ __global__ __launch_bounds__(256) void diag_kernel(const double* M, int64_t ld, 
 struct Chains {
   double* V;       // [chain][kMax + 1][np]
   double* w;       // [chain][np]
-  double* h;       // [chain][kMax + 1]
+  double* hp;      // [chain][2][(kMax + 1) nt] block partials of the dot products, by pass
+  double* nrm2;    // [chain][nt] block partials of ||w||^2
   double* alpha;   // [chain][kMax]
   double* beta;    // [chain][kMax]
   int64_t np;
   int kmax;
+  int nt;
 };
 
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) red[wid] = v;
+// One Gram-Schmidt pass on the 64 rows of block B: h_k = V_k . w from the block partials, w <- w
+// - sum_{k <= j} h_k V_k (the terms over 16 waves, added in wave order), then the block's
+// partials of what the next kernel needs: the second pass's dot products (PASS 0) or ||w||^2
+// (PASS 1).  Every block sums all partials of h itself, which costs less than a launch; h_j goes
+// into alpha_j (set on pass 0, added on 1).
+template <int PASS>
+__global__ __launch_bounds__(1024) void lz_update_kernel(Chains c, int j) {
+  __shared__ double h[kMaxSteps];
+  __shared__ double acc[16][kT];
+  const int B = blockIdx.x, ch = blockIdx.y, nt = c.nt;
+  const int grp = threadIdx.x / kT, r = threadIdx.x % kT;
+  const double* hp = c.hp + ((size_t)ch * 2 + PASS) * (c.kmax + 1) * nt;
+  const double* V = c.V + (size_t)ch * (c.kmax + 1) * c.np;
+  const int64_t i = (int64_t)B * kT + r;
+  for (int k = grp; k <= j; k += 16) {
+    double s = 0.0;
+    for (int b = r; b < nt; b += 64) s += hp[(size_t)k * nt + b];
+    s = wave_sum(s);
+    if (r == 0) h[k] = s;
+  }
   __syncthreads();
+  if (B == 0 && threadIdx.x == 0) {
+    double* al = c.alpha + (size_t)ch * c.kmax + j;
+    *al = PASS == 0 ? h[j] : *al + h[j];
+  }
   double s = 0.0;
-  if (threadIdx.x == 0)
-    for (int k = 0; k < kVecThreads / 64; ++k) s += red[k];
-  return s;                     // valid in thread 0
-}
-
-// h_k = V_k . w for k <= j; the pass's h_j goes into alpha_j (set on pass 0, added on 1).
-__global__ __launch_bounds__(kVecThreads) void lz_dots_kernel(Chains c, int j, int pass) {
-  __shared__ double red[kVecThreads / 64];
-  const int k = blockIdx.x, ch = blockIdx.y;
-  const double* Vk = c.V + ((size_t)ch * (c.kmax + 1) + k) * c.np;
-  const double* w = c.w + (size_t)ch * c.np;
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < c.np; i += kVecThreads) s += Vk[i] * w[i];
-  s = block_sum(s, red);
-  if (threadIdx.x == 0) {
-    c.h[(size_t)ch * (c.kmax + 1) + k] = s;
-    if (k == j) {
-      double* a = c.alpha + (size_t)ch * c.kmax + j;
-      *a = pass == 0 ? s : *a + s;
+  for (int k = grp; k <= j; k += 16) s += h[k] * V[(size_t)k * c.np + i];
+  acc[grp][r] = s;
+  __syncthreads();
+  if (grp == 0) {
+    double tot = 0.0;
+    for (int k = 0; k < 16; ++k) tot += acc[k][r];
+    const double w = c.w[(size_t)ch * c.np + i] - tot;
+    c.w[(size_t)ch * c.np + i] = w;
+    acc[0][r] = w;
+    if (PASS == 1) {
+      const double q = wave_sum(w * w);
+      if (r == 0) c.nrm2[(size_t)ch * nt + B] = q;
     }
   }
-}
-
-// w <- w - sum_{k <= j} h_k V_k, the sum in increasing k for every element.
-__global__ __launch_bounds__(kVecThreads) void lz_update_kernel(Chains c, int j) {
-  const int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  const int ch = blockIdx.y;
-  if (i >= c.np) return;
-  const double* V = c.V + (size_t)ch * (c.kmax + 1) * c.np;
-  const double* h = c.h + (size_t)ch * (c.kmax + 1);
-  double acc = 0.0;
-#pragma unroll 8
-  for (int k = 0; k <= j; ++k) acc += h[k] * V[(size_t)k * c.np + i];
-  c.w[(size_t)ch * c.np + i] -= acc;
-}
-
-// out[ch * ostride] = ||x_ch|| (one workgroup per chain, fixed order).
-__global__ __launch_bounds__(1024) void lz_norm_kernel(const double* x, int64_t xstride,
-                                                       double* out, int64_t ostride,
-                                                       int64_t np) {
-  __shared__ double red[16];
-  const int ch = blockIdx.y;
-  const double* v = x + (size_t)ch * xstride;
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < np; i += 1024) s += v[i] * v[i];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  if (PASS == 1) return;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double tsum = 0.0;
-    for (int k = 0; k < 16; ++k) tsum += red[k];
-    out[(size_t)ch * ostride] = sqrt(tsum);
+  const double w = acc[0][r];
+  double* hn = c.hp + ((size_t)ch * 2 + 1) * (c.kmax + 1) * nt;
+  for (int k = grp; k <= j; k += 16) {
+    const double d = wave_sum(V[(size_t)k * c.np + i] * w);
+    if (r == 0) hn[(size_t)k * nt + B] = d;
   }
 }
 
-// dst_ch = x_ch / nrm_ch (a zero norm leaves zeros: a breakdown, where T is cut).
-__global__ __launch_bounds__(kVecThreads) void lz_scale_kernel(const double* x, int64_t xstride,
-                                                               const double* nrm,
-                                                               int64_t nstride, double* dst,
-                                                               int64_t dstride, int64_t np) {
-  const int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  const int ch = blockIdx.y;
-  if (i >= np) return;
-  const double b = nrm[(size_t)ch * nstride];
-  const double inv = b > 0.0 ? 1.0 / b : 0.0;
-  dst[(size_t)ch * dstride + i] = x[(size_t)ch * xstride + i] * inv;
+// The last step's beta (the others are written where the vector is normalised).
+__global__ __launch_bounds__(64) void lz_beta_kernel(Chains c, int j) {
+  const int ch = blockIdx.x;
+  const double b = norm_of(c.nrm2 + (size_t)ch * c.nt, c.nt);
+  if (threadIdx.x == 0) c.beta[(size_t)ch * c.kmax + j] = b;
 }
 
 // x = 1 on [0, n), 0 beyond.
@@ -229,7 +293,7 @@ __global__ __launch_bounds__(kVecThreads) void fill_ones_kernel(double* x, int64
   if (i < np) x[i] = i < n ? 1.0 : 0.0;
 }
 
-// V_0 = s / ||s|| for every chain; s = start (n values, zero padded), or the fixed
+// w = s and its squared norm for every chain; s = start (n values, zero padded), or the fixed
 // pseudo-random vector u_i in [-1, 1) from SplitMix64 of i (Steele, Lea, Flood 2014).
 __device__ __forceinline__ double splitmix_uniform(uint64_t i) {
   uint64_t z = i + 0x9E3779B97F4A7C15ull * (i + 1);
@@ -239,14 +303,14 @@ __device__ __forceinline__ double splitmix_uniform(uint64_t i) {
   return (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
-__global__ __launch_bounds__(kVecThreads) void lz_start_kernel(Chains c, const double* start,
-                                                               int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+__global__ __launch_bounds__(kT) void lz_start_kernel(Chains c, const double* start, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   const int ch = blockIdx.y;
-  if (i >= c.np) return;
   double v = 0.0;
   if (i < n) v = start ? start[i] : splitmix_uniform((uint64_t)i);
   c.w[(size_t)ch * c.np + i] = v;
+  const double q = wave_sum(v * v);
+  if (threadIdx.x == 0) c.nrm2[(size_t)ch * c.nt + blockIdx.x] = q;
 }
 
 // ---- host side -------------------------------------------------------------------------
@@ -331,9 +395,8 @@ static void ritz_from(const double* al, const double* be, int steps, double* out
 struct BoundsWorkspace {
   int64_t np = 0;
   int kmax = 0, nv = 0;
-  double *V = nullptr, *w = nullptr, *h = nullptr, *alpha = nullptr, *beta = nullptr;
-  double *y = nullptr, *z = nullptr, *part = nullptr;
-  double* s0 = nullptr;         // [chain] norm of the start vector
+  double *V = nullptr, *w = nullptr, *hp = nullptr, *alpha = nullptr, *beta = nullptr;
+  double *y = nullptr, *z = nullptr, *part = nullptr, *nrm2 = nullptr;
   double* host = nullptr;       // pinned read-back
   size_t host_cap = 0;
   std::mutex mu;
@@ -351,8 +414,8 @@ static BoundsWorkspace* bounds_workspace() {
 }
 
 static void release(BoundsWorkspace* w) {
-  double** ptrs[] = {&w->V, &w->w, &w->h, &w->alpha, &w->beta, &w->y, &w->z, &w->part,
-                     &w->s0};
+  double** ptrs[] = {&w->V, &w->w, &w->hp, &w->alpha, &w->beta, &w->y, &w->z, &w->part,
+                     &w->nrm2};
   for (double** p : ptrs) {
     if (*p) (void)hipFree(*p);
     *p = nullptr;
@@ -367,11 +430,11 @@ static int ensure(BoundsWorkspace* w, int64_t np, int kmax, int nv) {
     release(w);
     const int nt = (int)(np / kT);
     const size_t sizes[] = {(size_t)nv * (kmax + 1) * np, (size_t)nv * np,
-                            (size_t)nv * (kmax + 1), (size_t)nv * kmax, (size_t)nv * kmax,
-                            (size_t)nv * np, (size_t)nv * np,
-                            (size_t)nt * nt * nv * 2 * kT, (size_t)nv};
-    double** ptrs[] = {&w->V, &w->w, &w->h, &w->alpha, &w->beta, &w->y, &w->z, &w->part,
-                       &w->s0};
+                            (size_t)nv * 2 * (kmax + 1) * nt, (size_t)nv * kmax,
+                            (size_t)nv * kmax, (size_t)nv * np, (size_t)nv * np,
+                            (size_t)nt * nt * nv * 2 * kT, (size_t)nv * nt};
+    double** ptrs[] = {&w->V, &w->w, &w->hp, &w->alpha, &w->beta, &w->y, &w->z, &w->part,
+                       &w->nrm2};
     for (int i = 0; i < 9; ++i)
       if (hipMalloc(ptrs[i], sizes[i] * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
@@ -393,9 +456,17 @@ static int ensure(BoundsWorkspace* w, int64_t np, int kmax, int nv) {
   return SNF_OK;
 }
 
-static void launch_symv(const SymvArgs& g, hipStream_t s) {
+// Tiles per strip: as many as leave each compute unit two strips (n = 4096: 544 strips of 4).
+// 40-step gap_bounds at n = 1000 / 2000 / 4096 / 6000: 1.59 / 2.28 / 4.02 / 6.36 ms with one
+// tile a strip, 1.74 / 1.98 / 4.00 / 5.34 with two, 1.58 / 1.98 / 3.80 / 5.48 by this rule (one,
+// two, four, four), 2.88 / 2.95 / 3.53 / 5.24 with eight at every order.
+static void launch_symv(SymvArgs& g, hipStream_t s, bool abs_mode = false) {
   const int nt = (int)(g.np / kT);
-  hipLaunchKernelGGL(symv_tile_kernel, dim3(nt, nt), dim3(256), 0, s, g, nt);
+  g.strip = nt >= 48 ? 4 : nt >= 32 ? 2 : 1;
+  const dim3 grid((nt + g.strip - 1) / g.strip, nt);
+  if (abs_mode) hipLaunchKernelGGL((symv_tile_kernel<1, true>), grid, dim3(256), 0, s, g, nt);
+  else if (g.nv == 1) hipLaunchKernelGGL((symv_tile_kernel<1, false>), grid, dim3(256), 0, s, g, nt);
+  else hipLaunchKernelGGL((symv_tile_kernel<2, false>), grid, dim3(256), 0, s, g, nt);
   hipLaunchKernelGGL(symv_reduce_kernel, dim3(nt, g.nv), dim3(1024), 0, s, g, nt);
 }
 
@@ -412,31 +483,42 @@ static SymvArgs symv_args(const double* M, int64_t ld, int64_t n, int64_t np, in
   return g;
 }
 
-// Lanczos on nv chains; apply(j) must leave A v_j of every chain in c.w.
+// Lanczos on nv chains.  apply(j, first, last) must leave A v_j of every chain in c.w: its first
+// product takes the unnormalised vector in c.w and leaves v_j in V (first), its last one
+// computes the first pass's dot products (last).  Four launches a step besides the products
+// between them.
 template <typename Apply>
 static int run_lanczos(BoundsWorkspace* w, int64_t n, int64_t np, int nv, int steps,
                        const double* start, Apply apply, hipStream_t s) {
-  Chains c{w->V, w->w, w->h, w->alpha, w->beta, np, w->kmax};
-  const int64_t vstride = (int64_t)(c.kmax + 1) * np;
-  const dim3 gv((unsigned)((np + kVecThreads - 1) / kVecThreads), nv);
-  hipLaunchKernelGGL(lz_start_kernel, gv, dim3(kVecThreads), 0, s, c, start, n);
-  hipLaunchKernelGGL(lz_norm_kernel, dim3(1, nv), dim3(1024), 0, s, c.w, np, w->s0,
-                     (int64_t)1, np);
-  hipLaunchKernelGGL(lz_scale_kernel, gv, dim3(kVecThreads), 0, s, c.w, np, w->s0, (int64_t)1,
-                     c.V, vstride, np);
+  const int nt = (int)(np / kT);
+  Chains c{w->V, w->w, w->hp, w->nrm2, w->alpha, w->beta, np, w->kmax, nt};
+  const dim3 gb(nt, nv);
+  hipLaunchKernelGGL(lz_start_kernel, gb, dim3(kT), 0, s, c, start, n);
   BD_HIP(hipGetLastError());
   for (int j = 0; j < steps; ++j) {
-    apply(j);
-    for (int pass = 0; pass < 2; ++pass) {
-      hipLaunchKernelGGL(lz_dots_kernel, dim3(j + 1, nv), dim3(kVecThreads), 0, s, c, j, pass);
-      hipLaunchKernelGGL(lz_update_kernel, gv, dim3(kVecThreads), 0, s, c, j);
-    }
-    hipLaunchKernelGGL(lz_norm_kernel, dim3(1, nv), dim3(1024), 0, s, c.w, np, c.beta + j,
-                       (int64_t)c.kmax, np);
-    hipLaunchKernelGGL(lz_scale_kernel, gv, dim3(kVecThreads), 0, s, c.w, np, c.beta + j,
-                       (int64_t)c.kmax, c.V + (size_t)(j + 1) * np, vstride, np);
+    auto first = [&](SymvArgs& g) {
+      for (int v = 0; v < nv; ++v) {
+        g.x[v] = c.w + (size_t)v * np;
+        g.nrm2[v] = c.nrm2 + (size_t)v * nt;
+        g.vout[v] = c.V + ((size_t)v * (c.kmax + 1) + j) * np;
+        g.beta[v] = j > 0 ? c.beta + (size_t)v * c.kmax + j - 1 : nullptr;
+      }
+    };
+    auto last = [&](SymvArgs& g) {
+      for (int v = 0; v < nv; ++v) {
+        g.y[v] = c.w + (size_t)v * np;
+        g.V[v] = c.V + (size_t)v * (c.kmax + 1) * np;
+        g.hp[v] = c.hp + (size_t)v * 2 * (c.kmax + 1) * nt;
+      }
+      g.j = j;
+    };
+    apply(first, last);
+    hipLaunchKernelGGL(lz_update_kernel<0>, gb, dim3(1024), 0, s, c, j);
+    hipLaunchKernelGGL(lz_update_kernel<1>, gb, dim3(1024), 0, s, c, j);
     BD_HIP(hipGetLastError());
   }
+  hipLaunchKernelGGL(lz_beta_kernel, dim3(nv), dim3(64), 0, s, c, steps - 1);
+  BD_HIP(hipGetLastError());
   return SNF_OK;
 }
 
@@ -479,10 +561,10 @@ int snf_spectral_bounds(const double* F_dev, int64_t n, int64_t ld, int32_t step
   int rc = ensure(w, np, std::max(steps, w->kmax), std::max(1, w->nv));
   if (rc) return rc;
   const int kmax = w->kmax;
-  auto apply = [&](int j) {
+  auto apply = [&](auto first, auto last) {
     SymvArgs g = symv_args(F_dev, ld, n, np, 1, w->part);
-    g.x[0] = w->V + (size_t)j * np;
-    g.y[0] = w->w;
+    first(g);
+    last(g);
     g.a[0] = 1.0;
     g.b[0] = 0.0;
     launch_symv(g, s);
@@ -494,12 +576,11 @@ int snf_spectral_bounds(const double* F_dev, int64_t n, int64_t ld, int32_t step
     hipLaunchKernelGGL(fill_ones_kernel, dim3((unsigned)((np + kVecThreads - 1) / kVecThreads)),
                        dim3(kVecThreads), 0, s, w->z, n, np);
     SymvArgs g = symv_args(F_dev, ld, n, np, 1, w->part);
-    g.abs_mode = 1;
     g.x[0] = w->z;
     g.y[0] = w->y;
     g.a[0] = 1.0;
     g.b[0] = 0.0;
-    launch_symv(g, s);
+    launch_symv(g, s, true);
     BD_HIP(hipGetLastError());
   }
   double* hab = w->host;
@@ -544,10 +625,9 @@ int snf_gap_bounds(const double* F_dev, const double* D_dev, int64_t n, int64_t 
   if (rc) return rc;
   const int kmax = w->kmax;
   // chain 0: D (F - lambda_min I) D;  chain 1: (I - D)(lambda_max I - F)(I - D)
-  auto apply = [&](int j) {
+  auto apply = [&](auto first, auto last) {
     SymvArgs g = symv_args(D_dev, ld, n, np, 2, w->part);
-    g.x[0] = w->V + (size_t)j * np;
-    g.x[1] = w->V + ((size_t)(kmax + 1) + j) * np;
+    first(g);
     g.y[0] = w->y;
     g.y[1] = w->y + np;
     g.a[0] = 1.0;  g.b[0] = 0.0;
@@ -564,8 +644,7 @@ int snf_gap_bounds(const double* F_dev, const double* D_dev, int64_t n, int64_t 
     SymvArgs d = symv_args(D_dev, ld, n, np, 2, w->part);
     d.x[0] = w->z;
     d.x[1] = w->z + np;
-    d.y[0] = w->w;
-    d.y[1] = w->w + np;
+    last(d);
     d.a[0] = 1.0;  d.b[0] = 0.0;
     d.a[1] = -1.0; d.b[1] = 1.0;
     launch_symv(d, s);
