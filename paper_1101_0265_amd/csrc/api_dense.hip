@@ -14,6 +14,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <memory>
 #include <mutex>
 #include <vector>
@@ -53,6 +54,8 @@ struct Workspace {
   SnfState* state = nullptr;
   Buffers* bufs_dev = nullptr;
   SnfState* state_host = nullptr;    // pinned
+  SnfHeader* hdr = nullptr;          // [2] state headers of a direct solve, by step parity
+  double* direct_partials = nullptr; // [2][kDirectSlots][4]
   int32_t* flags_host = nullptr;     // pinned, [2] stop flags of in-flight chunks
   double* sums_dev = nullptr;
   double* sums_host = nullptr;       // pinned
@@ -124,6 +127,10 @@ static void release_all(Workspace* w) {
   w->split_buf = nullptr;
   if (w->state) (void)hipFree(w->state);
   w->state = nullptr;
+  if (w->hdr) (void)hipFree(w->hdr);
+  w->hdr = nullptr;
+  if (w->direct_partials) (void)hipFree(w->direct_partials);
+  w->direct_partials = nullptr;
   if (w->bufs_dev) (void)hipFree(w->bufs_dev);
   w->bufs_dev = nullptr;
   if (w->sums_dev) (void)hipFree(w->sums_dev);
@@ -167,6 +174,8 @@ static int ensure_workspace(Workspace* w, int64_t np, int lp_bytes, int partial_
   if (!w->state) {
     SNF_HIP(hipMalloc(&w->state, sizeof(SnfState)));
     SNF_HIP(hipMalloc(&w->bufs_dev, sizeof(Buffers)));
+    SNF_HIP(hipMalloc(&w->hdr, 2 * sizeof(SnfHeader)));
+    SNF_HIP(hipMalloc(&w->direct_partials, 2 * kDirectSlots * 4 * sizeof(double)));
     SNF_HIP(hipHostMalloc(&w->state_host, sizeof(SnfState), hipHostMallocDefault));
     SNF_HIP(hipHostMalloc(&w->flags_host, 8 * sizeof(int32_t), hipHostMallocDefault));
     SNF_HIP(hipMalloc(&w->sums_dev, 4 * sizeof(double)));
@@ -631,6 +640,70 @@ static int newton_correct(Workspace* w, const double* F_dev, int64_t n, int64_t 
   return SNF_OK;
 }
 
+static int device_cus(Workspace* w) {
+  if (!w->num_cus) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&w->num_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return 0;
+  }
+  return w->num_cus;
+}
+
+// Result of a solve that left its final state in w->state_host (the stream is idle).  per_step:
+// the step launches were timed one by one; else the one launch is the solve.
+static int finish_direct(Workspace* w, snf_result* out, snf_log_rec* log, int32_t log_cap,
+                         bool time_products, int per_step) {
+  const SnfState* st = w->state_host;
+  fill_result(st, out, log, log_cap);
+  const int status = st->stop ? st->status : SNF_ENOCONV;
+  out->status = status;
+  float ms = 0.f;
+  SNF_HIP(hipEventElapsedTime(&ms, w->ev[0], w->ev[1]));
+  out->device_ms = ms;
+  if (time_products && !per_step) out->product_ms = ms;
+  for (int k = 0; time_products && per_step && k < st->products; ++k) {
+    SNF_HIP(hipEventElapsedTime(&ms, w->prod_ev[2 * k], w->prod_ev[2 * k + 1]));
+    out->product_ms += ms;
+  }
+  return status;
+}
+
+// ---- direct solves (FP64, small and middle order) ------------------------------------------
+// The step loop of a direct solve: one launch per step, kept kDirectLead steps ahead of the
+// step the device reports to have begun (a word in host-visible memory that the step kernels
+// write), so the GPU never waits for the host and few empty launches follow the stop.
+constexpr int kDirectLead = 4;
+
+static int direct_steps(const DirectArgs& a, int tile, StepOperands ops, int max_steps,
+                        volatile int32_t* progress, const std::vector<hipEvent_t>* ev, int* slot,
+                        hipStream_t s) {
+  int enq = 0;
+  *progress = 0;
+  // (the step after the last product only advances the state)
+  while (enq <= max_steps) {
+    int seen = *progress;
+    for (int spins = 1; seen >= 0 && enq - seen >= kDirectLead; ++spins) {
+      if (spins % 4096 == 0) {                 // a device error would leave the word as it is
+        const hipError_t q = hipStreamQuery(s);
+        if (q != hipErrorNotReady && q != hipSuccess) return dev_error(q, "a direct step");
+        if (q == hipSuccess && *progress == seen) return dev_error(hipErrorUnknown, "a direct step");
+      }
+      seen = *progress;
+    }
+    if (seen < 0) break;
+    int pa = 0, pb = 0;
+    ops.next(&pa, &pb);
+    if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq], s));
+    launch_direct_step(tile, a, enq, pa, pb, s);
+    if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq + 1], s));
+    ++enq;
+  }
+  SNF_HIP(hipGetLastError());
+  *slot = enq & 1;
+  return SNF_OK;
+}
+
 static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
                              const snf_params* params, snf_scheme scheme,
                              snf_precision precision, double* D_dev, snf_result* out,
@@ -656,7 +729,17 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
   // (the subspace correction's full-grid products need a partial slot per tile of the grid)
   const int slot_tiles = (params->flags & SNF_FLAG_SUBSPACE_NEWTON) ? num_product_tiles(np, 0)
                                                                      : tiles;
-  rc = ensure_workspace(w, np, lowp_bytes_for(precision), slot_tiles + 16 * kSplitCap,
+  // FP64 solves up to the order that one tile per compute unit covers take the direct kernels;
+  // those that fit run in one workgroup (the subspace correction goes on from the iterate
+  // buffers, so its solves only take the tiles of 32, with the padded row stride)
+  const bool newton = (params->flags & SNF_FLAG_SUBSPACE_NEWTON) != 0;
+  const bool fp64 = precision == SNF_P_FP64;
+  const bool in_wg = fp64 && !newton && solve_wg_bytes(n, scheme) > 0;
+  int tile = 0;
+  if (fp64 && !in_wg) tile = direct_tile(newton ? np : n, device_cus(w));
+  if (newton && tile != 32) tile = 0;
+  const int64_t dld = newton ? np : direct_stride(n, tile ? tile : kTile);
+  rc = ensure_workspace(w, in_wg ? 0 : tile ? std::max(np, dld) : np, lowp_bytes_for(precision), slot_tiles + 16 * kSplitCap,
                         (scheme_pmm_m(scheme) || scheme_is_pij(scheme)) ? 4 : 3);
   if (rc != SNF_OK) {
     out->status = rc;
@@ -670,82 +753,101 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
   const bool time_products = (params->flags & SNF_FLAG_TIME_PRODUCTS) != 0;
   const int per_it = products_per_iteration(scheme, params->poly_i, params->poly_j);
   const int max_steps = (params->max_iter + 1) * per_it + 1;
-  if (time_products && (int)w->prod_ev.size() < 2 * max_steps) {
+  if (time_products && (int)w->prod_ev.size() < 2 * (max_steps + 1)) {
     const size_t old = w->prod_ev.size();
-    w->prod_ev.resize(2 * max_steps);
+    w->prod_ev.resize(2 * (max_steps + 1));
     for (size_t i = old; i < w->prod_ev.size(); ++i) SNF_HIP(hipEventCreate(&w->prod_ev[i]));
   }
 
-  rc = upload_buffers(w, s);
-  if (rc != SNF_OK) return out->status = rc;
-  SNF_HIP(hipMemcpyAsync(w->state, w->state_host, sizeof(SnfState), hipMemcpyHostToDevice, s));
-  SNF_HIP(hipEventRecord(w->ev[0], s));
-  launch_f0(F_dev, n, ld, np, w->state, w->bufs_dev, lowp_kind_for(precision), w->partials, s);
-  launch_schedule(w->state, w->partials, kF0Blocks, 1, s);
-  SNF_HIP(hipGetLastError());
-
-  // Launch-ahead loop: chunks of `chunk` steps, two chunks in flight.
+  if (in_wg) {
+    SNF_HIP(hipEventRecord(w->ev[0], s));
+    if (launch_solve_wg(*w->state_host, F_dev, ld, D_dev, ld, w->state_host, max_steps, s) != 0)
+      return dev_error(hipGetLastError(), "the one-workgroup solve");
+    SNF_HIP(hipEventRecord(w->ev[1], s));
+    SNF_HIP(hipStreamSynchronize(s));
+    return finish_direct(w, out, log, log_cap, time_products, 0);
+  }
+  // chunk: steps enqueued between two looks at the stop flag
   const int chunk = np >= 2048 ? 2 : (np >= 1024 ? 4 : 8);
-  const bool lowp = precision != SNF_P_FP64;
-  const bool pij = scheme_is_pij(scheme);
-  // small orders in FP64: 32x32 tiles with the k range split inside the workgroup
-  const bool small = !lowp && !pij && np <= kSmallMaxNp;
-  const SmallGrid sgrid = make_small_grid(np, n, w->partials);
-  int enq = 0, chunks = 0, checked = 0;
-  int ev_used = 0;
-  bool stopped = false;
   volatile int32_t* flags = w->flags_host;
-  auto enqueue_chunk = [&]() -> int {
-    for (int k = 0; k < chunk && enq < max_steps; ++k, ++enq) {
-      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used], s));
-      if (small) {
-        launch_product_small(w->state, w->bufs_dev, sgrid, s);
-      } else {
+  int ev_used = 0;
+  if (tile) {
+    DirectArgs a;
+    for (int i = 0; i < 4; ++i) {
+      a.bufs.x[i] = w->x[i];
+      a.bufs.lp[i] = nullptr;
+    }
+    a.hdr = w->hdr;
+    a.log = w->state->log;
+    a.partials = w->direct_partials;
+    a.progress = w->flags_host + 4;
+    a.n = n;
+    a.ld = dld;
+    a.nt = (int)((newton ? np : n) + tile - 1) / tile;
+    SNF_HIP(hipEventRecord(w->ev[0], s));
+    launch_direct_f0(a, *w->state_host, F_dev, ld, s);
+    int slot = 0;
+    rc = direct_steps(a, tile, StepOperands(scheme, per_it), max_steps, w->flags_host + 4,
+                      time_products ? &w->prod_ev : nullptr, &slot, s);
+    if (rc != SNF_OK) return rc;
+    launch_direct_out(a, slot, D_dev, ld, w->state_host, s);
+    SNF_HIP(hipGetLastError());
+    SNF_HIP(hipEventRecord(w->ev[1], s));
+    SNF_HIP(hipStreamSynchronize(s));
+    if (!newton) return finish_direct(w, out, log, log_cap, time_products, 1);
+    // the correction's code finds the solve's state and buffer table where a launch per kernel
+    // would have left them
+    if (time_products) ev_used = 2 * (max_steps + 1);
+    rc = upload_buffers(w, s);
+    if (rc != SNF_OK) return rc;
+    SNF_HIP(hipMemcpyAsync(w->state, w->state_host, sizeof(SnfState), hipMemcpyHostToDevice, s));
+  } else {
+    rc = upload_buffers(w, s);
+    if (rc != SNF_OK) return out->status = rc;
+    SNF_HIP(hipMemcpyAsync(w->state, w->state_host, sizeof(SnfState), hipMemcpyHostToDevice, s));
+    SNF_HIP(hipEventRecord(w->ev[0], s));
+    launch_f0(F_dev, n, ld, np, w->state, w->bufs_dev, lowp_kind_for(precision), w->partials, s);
+    launch_schedule(w->state, w->partials, kF0Blocks, 1, s);
+    SNF_HIP(hipGetLastError());
+
+    // Launch-ahead loop: chunks of `chunk` steps, two chunks in flight.
+    const bool lowp = precision != SNF_P_FP64;
+    const bool pij = scheme_is_pij(scheme);
+    int enq = 0, chunks = 0, checked = 0;
+    bool stopped = false;
+    auto enqueue_chunk = [&]() -> int {
+      for (int k = 0; k < chunk && enq < max_steps; ++k, ++enq) {
+        if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used], s));
         launch_product(kPrecF64, w->state, w->bufs_dev, grid, s);
         if (pij) launch_product_dual(w->state, w->bufs_dev, grid, s);
         if (lowp) launch_product(lowp_kind_for(precision), w->state, w->bufs_dev, grid, s);
         launch_split_fixup(w->state, w->bufs_dev, grid, s);
+        if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used + 1], s));
+        if (time_products) ev_used += 2;
+        launch_schedule(w->state, w->partials, grid.partial_count, 0, s);
       }
-      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used + 1], s));
-      if (time_products) ev_used += 2;
-      launch_schedule(w->state, w->partials, small ? sgrid.tiles : grid.partial_count, 0, s);
-    }
-    SNF_HIP(hipGetLastError());
-    SNF_HIP(hipMemcpyAsync((void*)(flags + (chunks & 1)), &w->state->stop, sizeof(int32_t),
-                           hipMemcpyDeviceToHost, s));
-    SNF_HIP(hipEventRecord(w->ev[2 + (chunks & 1)], s));
-    ++chunks;
-    return SNF_OK;
-  };
-  // the smallest orders run the whole step loop in one cooperative launch (not the P_{m,m}
-  // schemes: measured no faster inside that launch, P_{5,5} with alpha = 1 slower)
-  bool persistent = false;
-  if (small && np <= kPersistMaxNp && !scheme_pmm_m(scheme)) {
-    if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[0], s));
-    persistent = launch_solve_small(w->state, w->bufs_dev, sgrid, w->partials, max_steps, s) == 0;
-    if (!persistent) (void)hipGetLastError();   // not co-resident: the launch-per-step path
-    else if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[1], s));
-    if (persistent) {
-      ev_used = 2;
-      stopped = true;
-    }
-  }
-  if (!persistent) {
+      SNF_HIP(hipGetLastError());
+      SNF_HIP(hipMemcpyAsync((void*)(flags + (chunks & 1)), &w->state->stop, sizeof(int32_t),
+                             hipMemcpyDeviceToHost, s));
+      SNF_HIP(hipEventRecord(w->ev[2 + (chunks & 1)], s));
+      ++chunks;
+      return SNF_OK;
+    };
     rc = enqueue_chunk();
     if (rc != SNF_OK) return out->status = rc;
-  }
-  while (!stopped && enq < max_steps) {
-    rc = enqueue_chunk();
-    if (rc != SNF_OK) return out->status = rc;
-    // wait for the older in-flight chunk and look at its stop flag
-    SNF_HIP(hipEventSynchronize(w->ev[2 + (checked & 1)]));
-    stopped = flags[checked & 1] != 0;
-    ++checked;
+    while (!stopped && enq < max_steps) {
+      rc = enqueue_chunk();
+      if (rc != SNF_OK) return out->status = rc;
+      // wait for the older in-flight chunk and look at its stop flag
+      SNF_HIP(hipEventSynchronize(w->ev[2 + (checked & 1)]));
+      stopped = flags[checked & 1] != 0;
+      ++checked;
+    }
   }
   // subspace correction of the solve's result, then its FP64 refinement
   std::unique_ptr<SnfState> main_st;
   NewtonStats ns;
-  if (params->flags & SNF_FLAG_SUBSPACE_NEWTON) {
+  if (newton) {
     SNF_HIP(hipMemcpyAsync(w->state_host, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));
     SNF_HIP(hipStreamSynchronize(s));
     const int st0 = w->state_host->stop ? w->state_host->status : SNF_ENOCONV;
@@ -799,12 +901,7 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
   float ms = 0.f;
   SNF_HIP(hipEventElapsedTime(&ms, w->ev[0], w->ev[1]));
   out->device_ms = ms;
-  if (time_products && persistent) {
-    // one launch ran every product and every schedule step
-    float m = 0.f;
-    SNF_HIP(hipEventElapsedTime(&m, w->prod_ev[0], w->prod_ev[1]));
-    out->product_ms = m;
-  } else if (time_products) {
+  if (time_products) {
     // step k of the loop ran the k-th product; steps after the stop were empty launches
     double tot = 0.0;
     const int real = st->products;

@@ -3,14 +3,14 @@
 //
 // Every byte of device memory beyond the caller's F and D comes from `scratch`, a file-scope
 // device array of fixed size: the FP64 iterate buffers, the per-tile partial sums, the scalar
-// state and the buffer table.  Its device address is taken once per device with
+// state.  Its device address is taken once per device with
 // hipGetSymbolAddress (the array's name in host code is a host-side stand-in, not a device
 // address) and kept; every kernel argument and copy uses that address.  Host staging (the
 // scalar state, the stop flag) lives in static host arrays, and the step loop reads the stop
 // flag with a synchronous copy instead of pinned memory and events, so the call makes no
-// allocation of any kind.  The kernels are those of snf_purify_dense (the small-order FP64
-// product, its cooperative whole-solve variant, f_0, the schedule and the copy-out), launched
-// in the same order on the same decomposition, so the results are the same bit for bit.
+// allocation of any kind.  The kernels are those of snf_purify_dense (the direct steps and the
+// one-workgroup solve), launched in the same order on the same decomposition, so the results
+// are the same bit for bit.
 #include <hip/hip_runtime.h>
 
 #include <stdio.h>
@@ -24,21 +24,21 @@
 namespace snf {
 namespace na {
 
-constexpr int64_t kNaMaxNp = kSmallMaxNp;               // 896: the small-order FP64 path
-constexpr int kNaPartialSlots = kF0Blocks;              // >= f_0's blocks and 2 x 406 tiles
-constexpr size_t kNaMatrix = (size_t)kNaMaxNp * kNaMaxNp;
+constexpr int64_t kNaMaxNp = SNF_NOALLOC_MAX_N;         // largest padded order taken
+constexpr int64_t kNaMaxLd = 912;                       // largest row stride: 19 tiles of 48
+constexpr int kNaPartialSlots = 2 * kDirectSlots;
+constexpr size_t kNaMatrix = (size_t)kNaMaxLd * kNaMaxLd;
 
 // Layout of the scratch array (offsets in doubles, each a multiple of 32, i.e. 256 bytes).
 constexpr size_t align32(size_t v) { return (v + 31) / 32 * 32; }
 constexpr size_t kOffState = 0;
-constexpr size_t kOffBufs = align32(kOffState + (sizeof(SnfState) + 7) / 8);
-constexpr size_t kOffClock = align32(kOffBufs + (sizeof(Buffers) + 7) / 8);
+constexpr size_t kOffHdr = align32(kOffState + (sizeof(SnfState) + 7) / 8);
+constexpr size_t kOffClock = align32(kOffHdr + (2 * sizeof(SnfHeader) + 7) / 8);
 constexpr size_t kOffPartials = align32(kOffClock + 2);
 constexpr size_t kOffX = align32(kOffPartials + (size_t)kNaPartialSlots * 4);
 constexpr size_t kScratchDoubles = SNF_NOALLOC_SCRATCH_BYTES / 8;
 static_assert(kOffX + 4 * kNaMatrix <= kScratchDoubles,
               "the layout must fit in SNF_NOALLOC_SCRATCH_BYTES");
-static_assert(kNaMaxNp == SNF_NOALLOC_MAX_N, "SNF_NOALLOC_MAX_N is the padded-order limit");
 
 }  // namespace na
 }  // namespace snf
@@ -78,53 +78,56 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
     base = (double*)p;
     g_na_ptr[dev] = base;
   }
-  const int64_t np = (n + kTile - 1) / kTile * kTile;
   SnfState* st = (SnfState*)(base + kOffState);
-  Buffers* bufs_dev = (Buffers*)(base + kOffBufs);
   unsigned long long* clk = (unsigned long long*)(base + kOffClock);
-  double* partials = base + kOffPartials;
-  // The iterate buffers hold kNaMaxNp^2 values each; the kernels index rows with this call's
-  // np, and every entry of an np x np buffer is written before it is read (f_0 writes all of
-  // X_0 including its zero padding, every product's epilogue all of its output), so nothing
-  // left by an earlier call needs clearing.
-  Buffers b;
-  for (int i = 0; i < 4; ++i) {
-    b.x[i] = base + kOffX + (size_t)i * kNaMatrix;
-    b.lp[i] = nullptr;
-  }
   SnfState* sh = &g_na_state[dev];
   init_state(sh, n, params, scheme, SNF_P_FP64);
-  NA_HIP(hipMemcpyAsync(bufs_dev, &b, sizeof(b), hipMemcpyHostToDevice, s));
-  NA_HIP(hipMemcpyAsync(st, sh, sizeof(SnfState), hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(na_clock_kernel, dim3(1), dim3(64), 0, s, clk);
-  launch_f0(F_dev, n, ld, np, st, bufs_dev, -1, partials, s);
-  launch_schedule(st, partials, kF0Blocks, 1, s);
-  NA_HIP(hipGetLastError());
-
   const int per_it = products_per_iteration(scheme, params->poly_i, params->poly_j);
   const int max_steps = (params->max_iter + 1) * per_it + 1;
-  const SmallGrid sgrid = make_small_grid(np, n, partials);
-  bool stopped = false;
-  if (np <= kPersistMaxNp && !scheme_pmm_m(scheme)) {
-    // the whole step loop in one cooperative launch, as snf_purify_dense does
-    stopped = launch_solve_small(st, bufs_dev, sgrid, partials, max_steps, s) == 0;
-    if (!stopped) (void)hipGetLastError();   // not co-resident: a launch per step below
-  }
-  const int chunk = np >= 1024 ? 4 : 8;
-  int enq = 0;
-  while (!stopped && enq < max_steps) {
-    for (int k = 0; k < chunk && enq < max_steps; ++k, ++enq) {
-      launch_product_small(st, bufs_dev, sgrid, s);
-      launch_schedule(st, partials, sgrid.tiles, 0, s);
+  hipLaunchKernelGGL(na_clock_kernel, dim3(1), dim3(64), 0, s, clk);
+  if (solve_wg_bytes(n, scheme) > 0) {
+    if (launch_solve_wg(*sh, F_dev, ld, D_dev, ld, st, max_steps, s) != 0)
+      return record_hip_error(hipGetLastError(), "the one-workgroup solve");
+  } else {
+    // The iterate buffers hold kNaMatrix values each; the kernels index rows with this call's
+    // stride, and every entry they read is written before (f_0 writes all of X_0 including its
+    // zero padding, every step all of its output), so nothing left by an earlier call needs
+    // clearing.
+    int cus = 0;
+    NA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int tile = direct_tile(n, cus);
+    if (!tile || direct_stride(n, tile) > kNaMaxLd) return SNF_EDEVICE;
+    DirectArgs a;
+    for (int i = 0; i < 4; ++i) {
+      a.bufs.x[i] = base + kOffX + (size_t)i * kNaMatrix;
+      a.bufs.lp[i] = nullptr;
     }
-    NA_HIP(hipGetLastError());
-    // a synchronous read of the stop flag (no pinned staging, no events)
-    NA_HIP(hipMemcpyAsync(&g_na_flag[dev], &st->stop, sizeof(int32_t), hipMemcpyDeviceToHost,
-                          s));
-    NA_HIP(hipStreamSynchronize(s));
-    stopped = g_na_flag[dev] != 0;
+    a.hdr = (SnfHeader*)(base + kOffHdr);
+    a.log = st->log;
+    a.partials = base + kOffPartials;
+    a.progress = nullptr;
+    a.n = n;
+    a.ld = direct_stride(n, tile);
+    a.nt = (int)((n + tile - 1) / tile);
+    launch_direct_f0(a, *sh, F_dev, ld, s);
+    StepOperands ops(scheme, per_it);
+    int enq = 0;
+    bool stopped = false;
+    while (!stopped && enq <= max_steps) {
+      for (int k = 0; k < 8 && enq <= max_steps; ++k, ++enq) {
+        int pa = 0, pb = 0;
+        ops.next(&pa, &pb);
+        launch_direct_step(tile, a, enq, pa, pb, s);
+      }
+      NA_HIP(hipGetLastError());
+      // a synchronous read of the stop flag (no pinned staging, no events)
+      NA_HIP(hipMemcpyAsync(&g_na_flag[dev], &a.hdr[enq & 1].stop, sizeof(int32_t),
+                            hipMemcpyDeviceToHost, s));
+      NA_HIP(hipStreamSynchronize(s));
+      stopped = g_na_flag[dev] != 0;
+    }
+    launch_direct_out(a, enq & 1, D_dev, ld, st, s);
   }
-  launch_copy_out(st, bufs_dev, n, np, D_dev, ld, s);
   hipLaunchKernelGGL(na_clock_kernel, dim3(1), dim3(64), 0, s, clk + 1);
   NA_HIP(hipGetLastError());
   NA_HIP(hipMemcpyAsync(sh, st, sizeof(SnfState), hipMemcpyDeviceToHost, s));

@@ -12,16 +12,17 @@
 //                        tr Y, ||Y||_F^2 per tile.
 //                        The FP64 variant with a second epilogue output serves the first
 //                        product of a P_{i,j} iteration.
-//  * small orders     -- 32x32 output tiles with the k range split over the four waves of a
-//                        workgroup (no split fix-up), and, at the smallest orders, the whole
-//                        step loop of a solve in one cooperative launch.
+//  * direct kernels   -- FP64 solves up to the order where a tile of at most 96x96 per compute
+//                        unit covers the upper triangle: operands straight from L2 to
+//                        registers, k split over the four waves of a workgroup, the schedule at
+//                        the head of the next step's kernel; at the smallest orders the whole
+//                        solve in one workgroup, iterates in LDS.
 //  * schedule_kernel  -- one workgroup: fixed-order reduction of the per-tile partials and the
 //                        scalar state machine (branch, alpha, beta, beta-bar, stopping).
 //  * copy kernels     -- padded <-> caller layout.
 //  * grouped kernels  -- the serving loop's step over many requests in one launch.
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
-#include <hip/hip_cooperative_groups.h>
 
 #include "schedule_math.h"
 #include "snf_internal.h"
@@ -260,7 +261,7 @@ struct EpiArgs {
   double d2, d1, d0;
 };
 
-__device__ __forceinline__ EpiArgs epi_args(const SnfState* st, const Buffers* bufs) {
+__device__ __forceinline__ EpiArgs epi_args(const SnfHeader* st, const Buffers* bufs) {
   EpiArgs e;
   e.Xt = bufs->x[st->ix];
   e.Y = bufs->x[st->io];
@@ -659,141 +660,6 @@ __device__ __forceinline__ void product_body(const SnfState* __restrict__ st,
 }
 
 // ---------------------------------------------------------------------------------------
-// Small orders: FP64 product in 32x32 output tiles with the k range split over the four
-// waves of a workgroup and summed in LDS, so a step needs no split fix-up launch (at
-// n = 256 the 128x128 engine has 3 tiles, which it splits 16 ways and then fixes up).
-// Wave w sums k in [w np/4, (w + 1) np/4) in chunks of 32; in MFMA step s of a chunk the lane
-// group g = l / 16 takes k = chunk + 8 g + s, so each lane reads 8 consecutive values of a
-// row (operands are symmetric: row j of B is column j).  The four partial tiles are added
-// in wave order, then the shared epilogue runs on 4 entries per thread.
-// ---------------------------------------------------------------------------------------
-constexpr int kSmallTile = 32;
-constexpr int kSmallThreads = 256;
-
-// One 32x32 tile of the pending product (st: the scalar state, in device memory or an LDS
-// copy of it); its FP64 sums go to partials[tile].
-__device__ __forceinline__ void small_tile_product(const SnfState* __restrict__ st,
-                                                   const Buffers* __restrict__ bufs,
-                                                   const SmallGrid& g, int tile,
-                                                   double* __restrict__ partials,
-                                                   double (*part)[kSmallTile][kSmallTile + 1]) {
-  const int64_t np = g.np;
-  const double* A = bufs->x[st->ia];
-  const double* B = bufs->x[st->ib];
-  int bi, bj;
-  tile_coords(tile, (int)(np / kSmallTile), 1, bi, bj);
-  const int64_t i0 = (int64_t)bi * kSmallTile, j0 = (int64_t)bj * kSmallTile;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int fr = lane & 15, fg = lane >> 4;
-  const int64_t kw0 = (int64_t)wid * (np / 4), kw1 = kw0 + np / 4;
-
-  dbl4 acc[2][2];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
-
-  // chunk registers: rows m (A) and q (B), 8 consecutive k values each (4 x 16 bytes); two
-  // sets, so the next chunk's loads are in flight while this one's MFMAs run
-  u32x4 ra0[2][4], rb0[2][4], ra1[2][4], rb1[2][4];
-  auto gload = [&](int64_t kc, u32x4 (&ra)[2][4], u32x4 (&rb)[2][4]) {
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const double* pa = A + (i0 + m * 16 + fr) * np + kc + fg * 8;
-      const double* pb = B + (j0 + m * 16 + fr) * np + kc + fg * 8;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        ra[m][v] = gload16(pa + 2 * v);
-        rb[m][v] = gload16(pb + 2 * v);
-      }
-    }
-  };
-  auto compute = [&](const u32x4 (&ra)[2][4], const u32x4 (&rb)[2][4]) {
-    double a[2][8], b[2][8];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double2 da = __builtin_bit_cast(double2, ra[m][v]);
-        const double2 db = __builtin_bit_cast(double2, rb[m][v]);
-        a[m][2 * v] = da.x;
-        a[m][2 * v + 1] = da.y;
-        b[m][2 * v] = db.x;
-        b[m][2 * v + 1] = db.y;
-      }
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          acc[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m][s], b[q][s], acc[m][q], 0, 0, 0);
-  };
-  // the wave's range is a multiple of 32 (np is a multiple of 128).  The next chunk is
-  // loaded on every path (past the end the last chunk again, never used) and ahead of this
-  // chunk's MFMAs (scheduling barrier): with a conditional load the compiler's wait before
-  // the MFMAs would also cover the next chunk's loads, and they would not overlap.
-  gload(kw0, ra0, rb0);
-  for (int64_t kc = kw0; kc < kw1; kc += 64) {
-    gload(min(kc + 32, kw1 - 32), ra1, rb1);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(ra0, rb0);
-    gload(min(kc + 64, kw1 - 32), ra0, rb0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (kc + 32 < kw1) compute(ra1, rb1);
-  }
-  // accumulator of lane l, register v: row (l / 16) + 4 v, column l % 16 of block (m, q)
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        part[wid][m * 16 + fg + 4 * v][q * 16 + fr] = acc[m][q][v];
-  __syncthreads();
-  const EpiArgs ea = epi_args(st, bufs);
-  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
-  double xs[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int idx = e * kSmallThreads + tid;
-    xs[e] = ea.Xt[(i0 + idx / kSmallTile) * np + j0 + idx % kSmallTile];
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int idx = e * kSmallThreads + tid;
-    const int r = idx / kSmallTile, c = idx % kSmallTile;
-    const double p = ((part[0][r][c] + part[1][r][c]) + part[2][r][c]) + part[3][r][c];
-    epi_elem(p, xs[e], i0 + r, j0 + c, 1, bi == bj, g.n, np, ea, e2, t1, t2);
-  }
-  write_partials(e2, t1, t2, partials, tile);
-}
-
-__global__ __launch_bounds__(kSmallThreads) void product_f64_small_kernel(
-    const SnfState* __restrict__ st, const Buffers* __restrict__ bufs, SmallGrid g) {
-  if (st->stop || st->prec != kPrecF64 || st->dual) return;
-  __shared__ double part[4][kSmallTile][kSmallTile + 1];
-  small_tile_product(st, bufs, g, blockIdx.x, g.partials, part);
-}
-
-
-SmallGrid make_small_grid(int64_t np, int64_t n, double* partials) {
-  SmallGrid g;
-  g.np = np;
-  g.n = n;
-  g.partials = partials;
-  const int nt = (int)(np / kSmallTile);
-  g.tiles = nt * (nt + 1) / 2;
-  return g;
-}
-
-void launch_product_small(SnfState* st, const Buffers* bufs_dev, const SmallGrid& g,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(product_f64_small_kernel, dim3(g.tiles), dim3(kSmallThreads), 0, s, st,
-                     bufs_dev, g);
-}
-
-// ---------------------------------------------------------------------------------------
 // Product kernel, bf16 MFMA 16x16x32 with f32 accumulation.
 //   Here the LDS tiles are 'row panels' with k contiguous: sA[i][k] = A[i0+i][k0+k] and
 //   sB[j][k] = B[j0+j][k0+k] (B[k][j] = B[j][k] by symmetry), because a lane's MFMA operand
@@ -1061,14 +927,14 @@ void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid
 // Schedule: reduce the partials in a fixed order, then advance the scalar state.
 // ---------------------------------------------------------------------------------------
 // alpha of a scaled P_{i,j} step: the smaller of the two sides' roots (tables from the state)
-__device__ double pij_alpha_state(const SnfState* s) {
+__device__ double pij_alpha_state(const SnfHeader* s) {
   const double lo = sched::pij_alpha_side_tab(s->pij_i, s->pij_j, s->pbin[0], s->xstar, s->beta);
   const double hi =
       sched::pij_alpha_side_tab(s->pij_j, s->pij_i, s->pbin[1], 1.0 - s->xstar, s->abar);
   return lo < hi ? lo : hi;
 }
 
-__device__ void decide(SnfState* s) {
+__device__ void decide(SnfHeader* s) {
 #pragma clang fp contract(off)
   // precision phase (only for the mixed-precision modes)
   if (s->mode != SNF_P_FP64) {
@@ -1162,7 +1028,7 @@ __device__ void decide(SnfState* s) {
   }
 }
 
-__device__ void advance_beta(SnfState* s, int br, double a) {
+__device__ void advance_beta(SnfHeader* s, int br, double a) {
 #pragma clang fp contract(off)
   if (br == SNF_BRANCH_SQUARE) {
     s->beta = sched::alg2_square_map(s->beta, a);
@@ -1190,7 +1056,7 @@ __device__ void advance_beta(SnfState* s, int br, double a) {
 // Set up the next product of a P_{m,m} iteration once the previous one finished:
 // P(1/2 + v) = 1/2 + v r(v^2), v = a (X - I/2), W = v^2.  After W: T = r_m W^2 + r_{m-1} W
 // + r_{m-2} I from W.W; then T <- W.T + r_k I down to k = 0; then X_new = 1/2 I + v T.
-__device__ void pmm_next(SnfState* s) {
+__device__ void pmm_next(SnfHeader* s) {
 #pragma clang fp contract(off)
   const int m = s->pmm_m;
   double r[sched::kPmmMaxM + 1];
@@ -1230,7 +1096,7 @@ __device__ void pmm_next(SnfState* s) {
 // Set up the next product of a P_{i,j} iteration: P(x* + v) = x* + v Q(v), v = a (X - x* I),
 // W = v^2, Q(v) = sum_k (q_2k + q_(2k+1) v) W^k.  The first product gave W and the top level
 // T; then T <- T.W + q_(2k+1) V + q_2k I for k = h - 2 .. 0; then X_new = x* I + V T.
-__device__ void pij_next(SnfState* s) {
+__device__ void pij_next(SnfHeader* s) {
 #pragma clang fp contract(off)
   const double a = s->alpha, xs = s->xstar;
   const int ta = (s->cur + 2) & 3, tb = (s->cur + 3) & 3;
@@ -1259,7 +1125,7 @@ __device__ void pij_next(SnfState* s) {
   s->c0 = xs;
 }
 
-__device__ void finish(SnfState* s, int status) {
+__device__ void finish(SnfHeader* s, int status) {
   if ((status == SNF_OK || status == SNF_OK_FLOOR) && s->has_nocc) {
     const double err = s->t1 - (double)s->n_occ;
     if (fabs(err) >= 0.5) status = SNF_EMIXED;
@@ -1269,9 +1135,8 @@ __device__ void finish(SnfState* s, int status) {
 }
 
 // The scalar state machine, run by one thread on a copy of the state's header in LDS (s);
-// the per-iteration log record goes straight to the state in device memory (sg; not written
-// when sg is null).
-__device__ void schedule_step(SnfState* __restrict__ s, SnfState* __restrict__ sg, double e2,
+// the per-iteration log record goes straight to memory (log; not written when null).
+__device__ void schedule_step(SnfHeader* __restrict__ s, snf_log_rec* __restrict__ log, double e2,
                               double t1, double t2, int init) {
   if (init) {
     s->t1 = t1;
@@ -1286,7 +1151,7 @@ __device__ void schedule_step(SnfState* __restrict__ s, SnfState* __restrict__ s
     s->e_last = e;
     const int it = s->iter;
     snf_log_rec dummy;
-    snf_log_rec* rec = sg ? &sg->log[it < SNF_LOG_MAX ? it : SNF_LOG_MAX - 1] : &dummy;
+    snf_log_rec* rec = log ? &log[it < SNF_LOG_MAX ? it : SNF_LOG_MAX - 1] : &dummy;
     rec->i = it;
     rec->branch = s->branch;
     rec->precision = s->prec;
@@ -1359,12 +1224,12 @@ __device__ void schedule_step(SnfState* __restrict__ s, SnfState* __restrict__ s
 // header (everything before the log) is staged in LDS by all threads, advanced there by
 // thread 0 and written back by all threads: one pass of coalesced accesses instead of a
 // chain of dependent single-thread loads and stores to device memory.
-constexpr int kStateHeaderBytes = (int)offsetof(SnfState, log);
+constexpr int kStateHeaderBytes = (int)sizeof(SnfHeader);
 
 __device__ void schedule_body(SnfState* __restrict__ sg, const double* __restrict__ partials,
                               int count, int init) {
   __shared__ double red[24];
-  __shared__ __attribute__((aligned(16))) SnfState hs;   // only the header is used
+  __shared__ __attribute__((aligned(16))) SnfHeader hs;
   unsigned char* hb = (unsigned char*)&hs;
   const unsigned char* gb = (const unsigned char*)sg;
   for (int i = threadIdx.x; i < kStateHeaderBytes; i += kReduceThreads) hb[i] = gb[i];
@@ -1375,64 +1240,580 @@ __device__ void schedule_body(SnfState* __restrict__ sg, const double* __restric
     t2 += partials[i * 4 + 2];
   }
   block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
-  if (threadIdx.x == 0) schedule_step(&hs, sg, e2, t1, t2, init);
+  if (threadIdx.x == 0) schedule_step(&hs, sg->log, e2, t1, t2, init);
   __syncthreads();
   unsigned char* gw = (unsigned char*)sg;
   for (int i = threadIdx.x; i < kStateHeaderBytes; i += kReduceThreads) gw[i] = hb[i];
 }
 
 // ---------------------------------------------------------------------------------------
-// Small orders, whole solve in one cooperative launch: every workgroup owns one 32x32 tile
-// and a private LDS copy of the scalar state.  A step is the tile product, one grid barrier,
-// then every workgroup reduces all tiles' partial sums in the same fixed order and advances
-// its own copy of the state: identical inputs and code give identical states, so all
-// workgroups agree on the next product and on when to stop without a second barrier
-// (workgroup 0 also writes the log and, at the end, the state).  Partial sums alternate
-// between two buffers by step parity, so a step's sums are not overwritten before every
-// workgroup has read them.
+// Direct step: FP64 solves whose upper triangle is covered by at most one TxT tile per compute
+// unit (T = 32 .. 96).  A 128x128 engine has too few tiles there: it cut them into k-slices,
+// added the slices in a second kernel and advanced the state in a third, and at n = 1000 the
+// three took 27 + 13 + 5 us a product of 17 us of matrix-core work.  Here
+//  * the k range is split over the four waves of a workgroup, each with the whole tile in its
+//    accumulators, so nothing is shared until the end: no LDS staging and no barrier in the main
+//    loop, operands go from L2 straight to registers, PD k-steps ahead;
+//  * the four partial tiles are added in LDS in wave order, a band of 32 rows at a time;
+//  * the schedule of step s runs at the head of step s + 1, in every workgroup for itself, while
+//    the first operands are on their way.
+// The bound is the matrix cores (FP64: 64 cycles an instruction and SIMD) plus, per step, about
+// 8 us of launch boundary, cold operand loads and schedule.
+// A scale-and-fold solve of 19 products (wall time), this against the engine's three kernels (n
+// > 896), 32x32 tiles and a schedule kernel (256 < n <= 896), those in one cooperative launch
+// with grid barriers (n <= 256): n = 256 0.36 / 0.44 ms, 512 0.44 / 0.59, 704 0.50 / 0.89, 1000
+// 0.82 / 1.12, 1400 1.38 / 1.97, 2000 3.2 / 4.2, 2112 3.3 / 4.5.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSmallThreads) void solve_small_kernel(SnfState* __restrict__ sg,
-                                                                    const Buffers* __restrict__ bufs,
-                                                                    SmallGrid g,
-                                                                    double* __restrict__ partials2,
-                                                                    int max_steps) {
-  cooperative_groups::grid_group grid = cooperative_groups::this_grid();
-  __shared__ double part[4][kSmallTile][kSmallTile + 1];
-  __shared__ double red[24];
-  __shared__ __attribute__((aligned(16))) SnfState hs;   // only the header is used
-  unsigned char* hb = (unsigned char*)&hs;
-  const unsigned char* gb = (const unsigned char*)sg;
-  for (int i = threadIdx.x; i < kStateHeaderBytes; i += kSmallThreads) hb[i] = gb[i];
-  __syncthreads();
-  SnfState* log_to = blockIdx.x == 0 ? sg : nullptr;
-  for (int step = 0; step < max_steps; ++step) {
-    if (hs.stop) break;                     // the same decision in every workgroup
-    double* pbuf = partials2 + (size_t)(step & 1) * g.tiles * 4;
-    small_tile_product(&hs, bufs, g, blockIdx.x, pbuf, part);
-    grid.sync();
-    double e2 = 0.0, t1 = 0.0, t2 = 0.0;
-    for (int i = threadIdx.x; i < g.tiles; i += kSmallThreads) {
-      e2 += pbuf[i * 4 + 0];
-      t1 += pbuf[i * 4 + 1];
-      t2 += pbuf[i * 4 + 2];
-    }
-    block_sum3(e2, t1, t2, red);
-    if (threadIdx.x == 0) schedule_step(&hs, log_to, e2, t1, t2, 0);
-    __syncthreads();
+constexpr int kDirectThreads = 256;
+
+int direct_tile(int64_t n, int num_cus) {
+  if (num_cus > kDirectThreads) num_cus = kDirectThreads;   // (a step sums a slot per thread)
+  for (int t = 32; t <= 96; t += 16) {
+    const int64_t nt = (n + t - 1) / t;
+    if (nt * (nt + 1) / 2 <= num_cus) return t;
   }
+  return 0;
+}
+
+int64_t direct_stride(int64_t n, int tile) {
+  const int64_t w = (n + tile - 1) / tile * tile;
+  // rows a multiple of 2 KB apart would put the rows of one load on the same channels
+  return w % 256 ? w : w + 16;
+}
+
+__device__ __forceinline__ double* pick_buf(const Buffers& b, int i) {
+  double* p = b.x[0];
+  if (i == 1) p = b.x[1];
+  if (i == 2) p = b.x[2];
+  if (i == 3) p = b.x[3];
+  return p;
+}
+
+// Operand registers of PD k-steps for a tile side of TB 16-blocks.  Lane (fr, fk) = (l % 16,
+// l / 16) loads row k + fk of the operand (A[i][k] = A[k][i] by symmetry): columns 2 fr, 2 fr + 1
+// of each 32 (16-byte loads; block 2 p holds the even columns of pair p, block 2 p + 1 the odd
+// ones) and, for odd TB, column fr of the last 16.
+template <int TB, int PD>
+struct DirectOperand {
+  static constexpr int P = TB / 2, O = TB & 1;
+  u32x4 pair[PD][P > 0 ? P : 1];
+  double last[PD];
+  __device__ __forceinline__ void load(const double* rowptr, int slot) {
+    const int fr = threadIdx.x & 15;
+#pragma unroll
+    for (int p = 0; p < P; ++p) pair[slot][p] = gload16(rowptr + 32 * p + 2 * fr);
+    if constexpr (O)
+      last[slot] = *(const __attribute__((address_space(1))) double*)(rowptr + 32 * P + fr);
+  }
+  __device__ __forceinline__ double get(int slot, int m) const {
+    if (O && m == TB - 1) return last[slot];
+    const u32x4 v = pair[slot][m >> 1];
+    const unsigned lo = (m & 1) ? v[2] : v[0], hi = (m & 1) ? v[3] : v[1];
+    return __hiloint2double((int)hi, (int)lo);
+  }
+};
+
+// NC: column groups of the tile; four waves (the k quarters) for each, so that a wave holds
+// TB x TB / NC blocks.
+template <int TB, int NC, int PD>
+__global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectArgs g, int step,
+                                                                         int pa, int pb) {
+  constexpr int T = 16 * TB, QB = TB / NC, NT = kDirectThreads * NC;
+  static_assert(QB * NC == TB, "equal column groups");
+  constexpr int P = TB / 2, O = TB & 1, QP = QB / 2, QO = QB & 1, LW = T + 2;
+  __shared__ __attribute__((aligned(16))) SnfHeader hs;
+  __shared__ double red[24];
+  __shared__ __attribute__((aligned(16))) double part[4][32][LW];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int fr = lane & 15, fk = lane >> 4;
+  const int kq = wid & 3, cg = wid >> 2;                // k quarter, column group
+  const int64_t ld = g.ld;
+  const int tiles = g.nt * (g.nt + 1) / 2;
+  const int tile = xcd_remap(blockIdx.x, tiles);
+  int bi, bj;
+  tile_coords(tile, g.nt, 1, bi, bj);
+  const int64_t i0 = (int64_t)bi * T, j0 = (int64_t)bj * T;
+
+  // header and sums first: loads return in order, and these are waited for first
+  constexpr int HW = (int)(sizeof(SnfHeader) / 4);
+  static_assert(sizeof(SnfHeader) % 4 == 0 && HW <= 2 * NT, "two words a thread");
+  const unsigned* gh = (const unsigned*)(g.hdr + (step & 1));
+  const unsigned h0 = tid < HW ? gh[tid] : 0u;
+  const unsigned h1 = tid + NT < HW ? gh[tid + NT] : 0u;
+  const int count = step ? tiles : kDirectF0Blocks;
+  const double* ps = g.partials + (size_t)((step + 1) & 1) * kDirectSlots * 4;
+  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
+  if (tid < count) {
+    e2 = ps[tid * 4 + 0];
+    t1 = ps[tid * 4 + 1];
+    t2 = ps[tid * 4 + 2];
+  }
+
+  // the wave's k-steps (4 values of k each); rows n .. ld - 1 of the buffers are zero
+  const int KT = (int)((g.n + 3) / 4);
+  const int kb = kq * KT / 4, ke = (kq + 1) * KT / 4;
+  DirectOperand<TB, PD> A;
+  DirectOperand<QB, PD> B;
+  const double *Ap, *Bp;
+  auto load = [&](int ks, int slot) {
+    const int64_t off = (int64_t)(4 * min(ks, max(ke - 1, kb)) + fk) * ld;
+    A.load(Ap + off + i0, slot);
+    B.load(Bp + off + j0 + cg * 16 * QB, slot);
+  };
+  auto load_first = [&](int ia, int ib) {
+    Ap = pick_buf(g.bufs, ia);
+    Bp = pick_buf(g.bufs, ib);
+#pragma unroll
+    for (int u = 0; u < PD; ++u) load(kb + u, u);
+  };
+  load_first(pa, pb);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // the schedule of the step before (step 0: the first decision)
+  if (tid < HW) ((unsigned*)&hs)[tid] = h0;
+  if (tid + NT < HW) ((unsigned*)&hs)[tid + NT] = h1;
+  block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
+  if (tid == 0 && !hs.stop)
+    schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0);
+  __syncthreads();
   if (blockIdx.x == 0) {
-    unsigned char* gw = (unsigned char*)sg;
-    for (int i = threadIdx.x; i < kStateHeaderBytes; i += kSmallThreads) gw[i] = hb[i];
+    unsigned* gn = (unsigned*)(g.hdr + ((step + 1) & 1));
+    if (tid < HW) gn[tid] = ((const unsigned*)&hs)[tid];
+    if (tid + NT < HW) gn[tid + NT] = ((const unsigned*)&hs)[tid + NT];
+    if (tid == 0 && g.progress)
+      __hip_atomic_store(g.progress, hs.stop ? -1 : step + 1, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if (hs.stop) return;
+  const int ia = __builtin_amdgcn_readfirstlane(hs.ia), ib = __builtin_amdgcn_readfirstlane(hs.ib);
+  if (ia != pa || ib != pb) load_first(ia, ib);
+
+  dbl4 acc[TB][QB];
+#pragma unroll
+  for (int m = 0; m < TB; ++m)
+#pragma unroll
+    for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  auto compute = [&](int slot) {
+#pragma unroll
+    for (int m = 0; m < TB; ++m)
+#pragma unroll
+      for (int q = 0; q < QB; ++q)
+        acc[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.get(slot, m), B.get(slot, q), acc[m][q],
+                                                         0, 0, 0);
+  };
+  int ks = kb;
+  for (; ks + PD <= ke; ks += PD) {
+    // (past the end the last k-step again, never used: the number of loads in flight is the
+    // same on every path, so a wait leaves the newer ones in flight)
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+      compute(u);
+      load(ks + u + PD, u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < PD; ++u)
+    if (ks + u < ke) compute(u);
+
+  // Bands of 32 rows (one pair of block rows; the last 16 rows for odd TB): add the four
+  // partial tiles in wave order, combine, store the rows, then the mirror from LDS so that its
+  // stores are contiguous too.
+  const int n = (int)g.n;
+  const double* X = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.ix));
+  double* Y = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io));
+  const int dual = __builtin_amdgcn_readfirstlane(hs.dual);
+  double* Y2 = dual ? pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io2)) : nullptr;
+  const double c2 = hs.c2, c1 = hs.c1, c0 = hs.c0, d2 = hs.d2, d1 = hs.d1, d0 = hs.d0;
+  const bool diag = bi == bj;
+  e2 = t1 = t2 = 0.0;
+#pragma unroll
+  for (int p = 0; p < P + O; ++p) {
+    constexpr int W2 = T / 2;
+    const int rows = p < P ? 32 : 16;
+    constexpr int NE = 32 * W2 / NT;        // column pairs per thread, full band
+    double2 xs[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
+      if (r < rows) xs[e] = *(const double2*)(X + (i0 + 32 * p + r) * ld + j0 + c);
+    }
+#pragma unroll
+    for (int mm = 0; mm < (p < P ? 2 : 1); ++mm) {
+      const int m = 2 * p + mm;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int t = fk + 4 * v, r = p < P ? 2 * t + mm : t;
+#pragma unroll
+        for (int q = 0; q < QP; ++q)
+          *(double2*)(&part[kq][r][cg * 16 * QB + 32 * q + 2 * fr]) =
+              double2{acc[m][2 * q][v], acc[m][2 * q + 1][v]};
+        if (QO) part[kq][r][cg * 16 * QB + 32 * QP + fr] = acc[m][QB - 1][v];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
+      if (r >= rows) continue;
+      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
+      double y[2], y2[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double pr = ((part[0][r][c + h] + part[1][r][c + h]) + part[2][r][c + h]) +
+                          part[3][r][c + h];
+        const double x = h ? xs[e].y : xs[e].x;
+        const bool on = gr == gc + h, in = gr < n && gc + h < n;
+        y[h] = in ? c2 * pr + c1 * x + (on ? c0 : 0.0) : 0.0;
+        y2[h] = in ? d2 * pr + d1 * x + (on ? d0 : 0.0) : 0.0;
+        if (!diag || gr <= gc + h) {       // (a diagonal tile keeps its upper half)
+          const double w = on ? 1.0 : 2.0, d = pr - x;
+          e2 += w * (d * d);
+          t2 += w * (y[h] * y[h]);
+          if (on) t1 += y[h];
+          if (diag) {
+            Y[(int64_t)gr * ld + gc + h] = y[h];
+            if (Y2) Y2[(int64_t)gr * ld + gc + h] = y2[h];
+          }
+        }
+      }
+      if (!diag) {
+        *(double2*)(Y + (int64_t)gr * ld + gc) = double2{y[0], y[1]};
+        if (Y2) *(double2*)(Y2 + (int64_t)gr * ld + gc) = double2{y2[0], y2[1]};
+      }
+      *(double2*)(&part[0][r][c]) = double2{y[0], y[1]};   // (this thread's own entries)
+      if (Y2) *(double2*)(&part[1][r][c]) = double2{y2[0], y2[1]};
+    }
+    __syncthreads();
+    for (int idx = tid; idx < rows * T; idx += NT) {
+      const int r = idx % rows, c = idx / rows;
+      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
+      if (diag && gr >= gc) continue;
+      Y[(int64_t)gc * ld + gr] = part[0][r][c];
+      if (Y2) Y2[(int64_t)gc * ld + gr] = part[1][r][c];
+    }
+    if (p + 1 < P + O) __syncthreads();
+  }
+  __syncthreads();
+  block_sum3(e2, t1, t2, red);
+  if (tid == 0) {
+    double* po = g.partials + ((size_t)(step & 1) * kDirectSlots + tile) * 4;
+    po[0] = e2;
+    po[1] = t1;
+    po[2] = t2;
   }
 }
 
-int launch_solve_small(SnfState* st, const Buffers* bufs_dev, const SmallGrid& g,
-                       double* partials2, int max_steps, hipStream_t s) {
-  void* args[] = {(void*)&st, (void*)&bufs_dev, (void*)&g, (void*)&partials2, (void*)&max_steps};
-  return hipLaunchCooperativeKernel((const void*)solve_small_kernel, dim3(g.tiles),
-                                    dim3(kSmallThreads), args, 0, s) == hipSuccess
-             ? 0
-             : -1;
+// X_0 = f_0(F) on the whole ld x ld buffer (zero beyond n), upper triangle of F read, as
+// f0_kernel; block partials into parity 1, where step 0 looks for them.
+__global__ __launch_bounds__(256) void direct_f0_kernel(DirectArgs g, SnfHeader h,
+                                                        const double* __restrict__ F, int64_t ldf) {
+  __shared__ double tile[32][33];
+  __shared__ double red[24];
+  if (blockIdx.x == 0 && threadIdx.x == 0) g.hdr[0] = h;
+  const int alg1 = h.scheme == SNF_MCWEENY || h.scheme == SNF_SNF_FIXMU || h.pmm_m || h.pij_i;
+  const double lmin = h.lambda_min, lmax = h.lambda_max, mu = h.mu, gamma = h.gamma, xs = h.xstar;
+  double* X = g.bufs.x[0];
+  const int n = (int)g.n, ld = (int)g.ld, nt = (ld + 31) / 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  double t1 = 0.0, t2 = 0.0;
+  for (int t = blockIdx.x; t < nt * nt; t += gridDim.x) {
+    const int bi = t / nt, bj = t % nt, si = min(bi, bj), sj = max(bi, bj);
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+      const int gr = si * 32 + r, gc = sj * 32 + tx;
+      tile[r][tx] = (gr < n && gc < n) ? F[(int64_t)gr * ldf + gc] : 0.0;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+      const int gr = bi * 32 + r, gc = bj * 32 + tx;
+      if (gr >= ld || gc >= ld) continue;
+      const double v = (gr <= gc) ? tile[r][tx] : tile[tx][r];
+      double x = 0.0;
+      if (gr < n && gc < n) {
+        const bool d = gr == gc;
+        x = alg1 ? ((d ? mu : 0.0) - v) / gamma + (d ? xs : 0.0)
+                 : ((d ? lmax : 0.0) - v) / (lmax - lmin);
+        if (d) t1 += x;
+        t2 += x * x;
+      }
+      X[(int64_t)gr * ld + gc] = x;
+    }
+  }
+  double e0 = 0.0;
+  block_sum3(e0, t1, t2, red);
+  if (threadIdx.x == 0) {
+    double* po = g.partials + ((size_t)kDirectSlots + blockIdx.x) * 4;
+    po[0] = 0.0;
+    po[1] = t1;
+    po[2] = t2;
+  }
+}
+
+// D = X_cur and the final state out (host-visible memory: no copy engine and no extra launch).
+__global__ __launch_bounds__(256) void direct_out_kernel(DirectArgs g, int slot,
+                                                         double* __restrict__ D, int64_t ldd,
+                                                         SnfState* __restrict__ out) {
+  const SnfHeader* h = g.hdr + slot;
+  const double* X = pick_buf(g.bufs, h->cur);
+  const int n = (int)g.n;
+  for (int r = blockIdx.x; r < n; r += gridDim.x)
+    for (int c = threadIdx.x; c < n; c += 256) D[r * ldd + c] = X[(int64_t)r * g.ld + c];
+  if (blockIdx.x == 0) {
+    unsigned* o = (unsigned*)(SnfHeader*)out;
+    for (int i = threadIdx.x; i < (int)(sizeof(SnfHeader) / 4); i += 256) o[i] = ((const unsigned*)h)[i];
+    const int words = min(h->nlog, SNF_LOG_MAX) * (int)(sizeof(snf_log_rec) / 4);
+    unsigned* ol = (unsigned*)out->log;
+    for (int i = threadIdx.x; i < words; i += 256) ol[i] = ((const unsigned*)g.log)[i];
+  }
+}
+
+void launch_direct_f0(const DirectArgs& a, const SnfHeader& h, const double* F, int64_t ldf,
+                      hipStream_t s) {
+  hipLaunchKernelGGL(direct_f0_kernel, dim3(kDirectF0Blocks), dim3(256), 0, s, a, h, F, ldf);
+}
+
+void launch_direct_step(int tile, const DirectArgs& a, int step, int pa, int pb, hipStream_t s) {
+  const dim3 grid(a.nt * (a.nt + 1) / 2);
+#define SNF_DIRECT(TB, NC, PD)                                                                \
+  hipLaunchKernelGGL((direct_step_kernel<TB, NC, PD>), grid, dim3(kDirectThreads * NC), 0, s, \
+                     a, step, pa, pb)
+  switch (tile) {
+    case 32: SNF_DIRECT(2, 1, 16); break;
+    case 48: SNF_DIRECT(3, 1, 12); break;
+    case 64: SNF_DIRECT(4, 2, 8); break;
+    case 80: SNF_DIRECT(5, 1, 5); break;
+    default: SNF_DIRECT(6, 2, 4); break;
+  }
+#undef SNF_DIRECT
+}
+
+void launch_direct_out(const DirectArgs& a, int slot, double* D, int64_t ldd, SnfState* out,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(direct_out_kernel, dim3((unsigned)(a.n < 1024 ? a.n : 1024)), dim3(256), 0, s,
+                     a, slot, D, ldd, out);
+}
+
+// The buffer sequence of decide(), pmm_next() and pij_next().
+void StepOperands::next(int* pa, int* pb) {
+  const bool chain = scheme_pmm_m(scheme) || scheme_is_pij(scheme);
+  const int bw = (cur + 1) & 3, ta = (cur + 2) & 3, tb = (cur + 3) & 3;
+  if (k == 0) {
+    *pa = *pb = cur;
+    bt = ta;
+  } else if (!chain) {                     // S2.X
+    *pa = 2;
+    *pb = cur;
+  } else if (k == per_it - 1) {            // X.T
+    *pa = cur;
+    *pb = bt;
+  } else if (scheme_is_pij(scheme)) {      // T <- T.W
+    *pa = bt;
+    *pb = bw;
+    bt = bt == ta ? tb : ta;
+  } else if (k == 1) {                     // T from W.W
+    *pa = *pb = bw;
+  } else {                                 // T <- W.T
+    *pa = bw;
+    *pb = bt;
+    bt = bt == ta ? tb : ta;
+  }
+  if (++k == per_it) {
+    k = 0;
+    cur = chain ? bw : 1 - cur;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The smallest orders: the whole solve in one workgroup, the iterates in LDS (160 KB: two
+// buffers up to order 96, four up to 64).  A step of such a solve is bound by
+// latency, so nothing leaves the compute unit between steps: no launch, no grid barrier, no
+// memory.  Eight waves share the 16x16 blocks of the upper triangle; a step's results stay in
+// registers until the sums are known, so X needs no second buffer and is still whole when the
+// stop test passes.  The same 19 products at n = 17 / 64 / 96: 0.13 / 0.19 / 0.30 ms, against
+// 0.38 ms in a cooperative launch of 32x32 tiles.  Beyond order 96 one unit's matrix cores are
+// too few (n = 128: 0.47 ms, the direct steps 0.33).
+// ---------------------------------------------------------------------------------------
+constexpr int kWgThreads = 512, kWgWaves = kWgThreads / 64;
+
+static int wg_buffers(int scheme) {
+  if (scheme_pmm_m(scheme) || scheme_is_pij(scheme)) return 4;
+  return (scheme == SNF_MCWEENY || scheme == SNF_SNF_FIXMU) ? 2 : 1;
+}
+
+size_t solve_wg_bytes(int64_t n, int scheme) {
+  if (n > 96) return 0;
+  const int64_t np = (n + 15) / 16 * 16;
+  const size_t bytes = (size_t)wg_buffers(scheme) * np * np * sizeof(double);
+  return bytes <= (size_t)144 << 10 ? bytes : 0;
+}
+
+// NB buffers: 1: X in place; 2: X, S2 (index 2); 4: by index.
+template <int NB>
+__global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
+                                                              const double* __restrict__ F,
+                                                              int64_t ldf, double* __restrict__ D,
+                                                              int64_t ldd, SnfState* __restrict__ out,
+                                                              int max_steps) {
+  constexpr int MB = NB == 4 ? 2 : 3;      // blocks per wave at the largest order
+  extern __shared__ __attribute__((aligned(16))) double xbuf[];
+  __shared__ __attribute__((aligned(16))) SnfHeader hs;
+  __shared__ double red[3 * kWgWaves];
+  const int n = (int)h.n, np = (n + 15) / 16 * 16;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int fr = lane & 15, fk = lane >> 4;
+  // columns of odd rows are swapped 16 by 16 where rows are a multiple of 256 B apart: two rows
+  // of 16 values then cover the banks once
+  const int sw = np % 32 ? 0 : 16;
+  auto at = [&](int r, int c) { return r * np + (c ^ ((r & 1) ? sw : 0)); };
+  auto buf = [&](int i) {
+    return xbuf + (size_t)(NB == 1 ? 0 : NB == 2 ? (i == 2 ? 1 : 0) : i) * np * np;
+  };
+  auto sum3 = [&](double& a, double& b, double& c) {     // valid in thread 0
+    a = wave_sum(a);
+    b = wave_sum(b);
+    c = wave_sum(c);
+    if (lane == 0) {
+      red[wid * 3 + 0] = a;
+      red[wid * 3 + 1] = b;
+      red[wid * 3 + 2] = c;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      a = b = c = 0.0;
+      for (int w = 0; w < kWgWaves; ++w) {
+        a += red[w * 3 + 0];
+        b += red[w * 3 + 1];
+        c += red[w * 3 + 2];
+      }
+    }
+  };
+  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
+  {
+    if (tid == 0) hs = h;
+    const int alg1 = h.scheme == SNF_MCWEENY || h.scheme == SNF_SNF_FIXMU || h.pmm_m || h.pij_i;
+    for (int idx = tid; idx < np * np; idx += kWgThreads) {
+      const int r = idx / np, c = idx - r * np;
+      if (r > c) continue;
+      double x = 0.0;
+      if (c < n) {
+        const double v = F[r * ldf + c];
+        const bool d = r == c;
+        x = alg1 ? ((d ? h.mu : 0.0) - v) / h.gamma + (d ? h.xstar : 0.0)
+                 : ((d ? h.lambda_max : 0.0) - v) / (h.lambda_max - h.lambda_min);
+        if (d) t1 += x;
+        t2 += (d ? 1.0 : 2.0) * (x * x);
+      }
+      xbuf[at(r, c)] = x;
+      xbuf[at(c, r)] = x;
+    }
+    sum3(e2, t1, t2);
+    if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 1);
+    __syncthreads();
+  }
+  const int nb = np / 16, cnt = nb * (nb + 1) / 2;
+  int br[MB], bc[MB];                // the wave's blocks
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    int rem = wid + i * kWgWaves, r = 0;
+    while (r < nb && rem >= nb - r) {
+      rem -= nb - r;
+      ++r;
+    }
+    br[i] = __builtin_amdgcn_readfirstlane(r);
+    bc[i] = __builtin_amdgcn_readfirstlane(r + rem);
+  }
+  for (int step = 0; step < max_steps && !hs.stop; ++step) {
+    const double *A = buf(hs.ia), *B = buf(hs.ib), *L = buf(hs.ix);
+    double *Y = buf(hs.io), *Y2 = buf(hs.io2);
+    const bool dual = NB == 4 && hs.dual;
+    const double c2 = hs.c2, c1 = hs.c1, c0 = hs.c0, d2 = hs.d2, d1 = hs.d1, d0 = hs.d0;
+    double y[MB][4], y2[MB][4];
+    e2 = t1 = t2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if (wid + i * kWgWaves < cnt) {
+        dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < np; k += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[at(k + fk, br[i] * 16 + fr)],
+                                                     B[at(k + fk, bc[i] * 16 + fr)], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = br[i] * 16 + fk + 4 * v, c = bc[i] * 16 + fr;
+          const double p = acc[v], x = L[at(r, c)];
+          const bool on = r == c, in = r < n && c < n;
+          y[i][v] = in ? c2 * p + c1 * x + (on ? c0 : 0.0) : 0.0;
+          if (NB == 4) y2[i][v] = in ? d2 * p + d1 * x + (on ? d0 : 0.0) : 0.0;
+          if (r <= c) {
+            const double w = on ? 1.0 : 2.0, d = p - x;
+            e2 += w * (d * d);
+            t2 += w * (y[i][v] * y[i][v]);
+            if (on) t1 += y[i][v];
+          }
+        }
+      }
+    }
+    sum3(e2, t1, t2);                      // (its barrier: every read of the operands is done)
+    if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 0);
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      if (NB != 1 && wid + i * kWgWaves < cnt) {         // (the result is in another buffer)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = br[i] * 16 + fk + 4 * v, c = bc[i] * 16 + fr;
+          if (r > c) continue;
+          Y[at(r, c)] = y[i][v];
+          Y[at(c, r)] = y[i][v];
+          if (dual) Y2[at(r, c)] = y2[i][v];
+          if (dual) Y2[at(c, r)] = y2[i][v];
+        }
+      }
+    }
+    __syncthreads();
+    if (NB == 1) {
+      if (hs.stop) break;                  // X is the result
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        if (wid + i * kWgWaves < cnt) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int r = br[i] * 16 + fk + 4 * v, c = bc[i] * 16 + fr;
+            if (r > c) continue;
+            Y[at(r, c)] = y[i][v];
+            Y[at(c, r)] = y[i][v];
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+  const double* X = buf(hs.cur);
+  for (int r = wid; r < n; r += kWgWaves)
+    for (int c = lane; c < n; c += 64) D[r * ldd + c] = X[at(r, c)];
+  unsigned* o = (unsigned*)(SnfHeader*)out;
+  for (int i = tid; i < (int)(sizeof(SnfHeader) / 4); i += kWgThreads) o[i] = ((const unsigned*)&hs)[i];
+}
+
+template <int NB>
+static int launch_wg(size_t bytes, const SnfHeader& h, const double* F, int64_t ldf, double* D,
+                     int64_t ldd, SnfState* out, int max_steps, hipStream_t s) {
+  if (bytes > ((size_t)64 << 10) &&
+      hipFuncSetAttribute((const void*)solve_wg_kernel<NB>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+    return -1;
+  hipLaunchKernelGGL(solve_wg_kernel<NB>, dim3(1), dim3(kWgThreads), bytes, s, h, F, ldf, D, ldd,
+                     out, max_steps);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D, int64_t ldd,
+                    SnfState* out, int max_steps, hipStream_t s) {
+  const size_t bytes = solve_wg_bytes(h.n, h.scheme);
+  switch (wg_buffers(h.scheme)) {
+    case 1: return launch_wg<1>(bytes, h, F, ldf, D, ldd, out, max_steps, s);
+    case 2: return launch_wg<2>(bytes, h, F, ldf, D, ldd, out, max_steps, s);
+    default: return launch_wg<4>(bytes, h, F, ldf, D, ldd, out, max_steps, s);
+  }
 }
 
 __global__ __launch_bounds__(kReduceThreads) void schedule_kernel(SnfState* __restrict__ s,

@@ -51,9 +51,9 @@ inline int products_per_iteration(int scheme, int pi = 0, int pj = 0) {
   return (scheme == SNF_MCWEENY || scheme == SNF_SNF_FIXMU) ? 2 : 1;
 }
 
-// Scalar state of one purification, resident in device memory.  Written by the host
-// once (configuration), then only by the schedule kernel (one thread).
-struct SnfState {
+// Scalar state of one purification.  Written by the host once (configuration), then only by the
+// schedule (one thread).
+struct SnfHeader {
   // ---- configuration ----
   int32_t scheme;
   int32_t max_iter;
@@ -95,6 +95,9 @@ struct SnfState {
   int32_t want_e;         // pending product checks idempotency of its A operand
   int32_t write_lowp;     // epilogue also writes the low-precision operand copy
   int32_t nlog;
+};
+// ... with the per-iteration log behind it.
+struct SnfState : SnfHeader {
   snf_log_rec log[SNF_LOG_MAX];
 };
 
@@ -138,23 +141,45 @@ constexpr int kSplitCap = 512;   // slices held by the split buffer (64*256 doub
 // precision (so the host can enqueue all variants without knowing the device's choice).
 void launch_product(int prec, SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                     hipStream_t s);
-// Small orders: FP64 product in 32x32 tiles of the upper triangle, k split over the four
-// waves of a workgroup and summed in LDS (no split fix-up); one partial slot per tile.
-constexpr int64_t kSmallMaxNp = 896;   // padded orders that take this path (FP64 mode)
-struct SmallGrid {
-  int64_t np, n;
-  int tiles;
-  double* partials;
+// ---- FP64 solves of small and middle order (kernels_dense.hip) --------------------------
+// Work of one workgroup per step: a TxT output tile of the upper triangle, T the smallest of
+// 32, 48, 64, 80, 96 whose tiles number at most one per compute unit; 0: no such T.
+int direct_tile(int64_t n, int num_cus);
+// Row stride of the iterate buffers for that T (a multiple of 16, at least T ceil(n / T)).
+int64_t direct_stride(int64_t n, int tile);
+constexpr int kDirectSlots = 512;     // partial-sum slots per step parity (f_0's blocks, tiles)
+constexpr int kDirectF0Blocks = 256;
+struct DirectArgs {
+  Buffers bufs;            // iterate buffers of stride ld (device pointers)
+  SnfHeader* hdr;          // [2]: step s reads hdr[s & 1] and leaves the next one in the other
+  snf_log_rec* log;
+  double* partials;        // [2][kDirectSlots][4]
+  int32_t* progress;       // host-visible word: steps begun, or -1 once stopped; or null
+  int64_t n, ld;
+  int nt;                  // tiles per side
 };
-SmallGrid make_small_grid(int64_t np, int64_t n, double* partials);
-void launch_product_small(SnfState* st, const Buffers* bufs_dev, const SmallGrid& g,
-                          hipStream_t s);
-// The whole step loop of a small-order FP64 solve in one cooperative launch (one workgroup
-// per 32x32 tile, a grid barrier per step); partials2 holds 2 x tiles slots.  Returns 0, or
-// -1 when the runtime refuses the cooperative launch.
-constexpr int64_t kPersistMaxNp = 256;
-int launch_solve_small(SnfState* st, const Buffers* bufs_dev, const SmallGrid& g,
-                       double* partials2, int max_steps, hipStream_t s);
+// X_0 = f_0(F) into bufs.x[0] and the initial header into hdr[0].
+void launch_direct_f0(const DirectArgs& a, const SnfHeader& h, const double* F, int64_t ldf,
+                      hipStream_t s);
+// Step `step` of the solve: advance the state by the previous step's sums (step 0: f_0's), then,
+// unless that stopped it, the pending product.  pa, pb: the operand buffers the state will
+// name, as far as the host knows (another pair is slower, not wrong).
+void launch_direct_step(int tile, const DirectArgs& a, int step, int pa, int pb, hipStream_t s);
+// D and the final state (header of slot `slot`, log) out.
+void launch_direct_out(const DirectArgs& a, int slot, double* D, int64_t ldd, SnfState* out,
+                       hipStream_t s);
+// Operand buffers of the product of each step of a scheme, from step 0 on.
+struct StepOperands {
+  int scheme, per_it, k = 0, cur = 0, bt = 0;
+  explicit StepOperands(int scheme_, int per_it_) : scheme(scheme_), per_it(per_it_) {}
+  void next(int* pa, int* pb);
+};
+
+// The whole FP64 solve in one workgroup, iterates in LDS: the iterate buffers one scheme needs
+// at order n fit (solve_wg_bytes > 0).
+size_t solve_wg_bytes(int64_t n, int scheme);
+int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D, int64_t ldd,
+                    SnfState* out, int max_steps, hipStream_t s);
 // FP64 product with the second epilogue output (P_{i,j} schemes: launched beside
 // launch_product(kPrecF64, ...); exactly one of the two runs, as the state asks).
 void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
