@@ -961,8 +961,28 @@ int snf_step_dense(const double* A_dev, const double* B_dev, int64_t n, int64_t 
   const ProductGrid grid = make_product_grid(np, n, sym, w->num_cus, w->partials, w->split_buf,
                                              kSplitCap, stage_depth_for(precision));
   const int lk = lowp_kind_for(precision);
-  rc = upload_buffers(w, s);
-  if (rc != SNF_OK) return rc;
+  // Where the caller's matrices have the padded layout themselves (n a multiple of the tile, rows
+  // of n values, 16-byte aligned) the product reads and writes them in place; at n = 8192 the
+  // copies in and out took as long as the BF16 product itself.
+  const bool square = sym != 0;
+  auto aligned = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  auto disjoint = [&](const double* p, const double* q) {
+    const size_t bytes = (size_t)n * (size_t)ld * sizeof(double);
+    return (uintptr_t)p + bytes <= (uintptr_t)q || (uintptr_t)q + bytes <= (uintptr_t)p;
+  };
+  const bool in_place = np == n && ld == n && aligned(A_dev) && aligned(B_dev) && aligned(Y_dev) &&
+                        disjoint(Y_dev, A_dev) && disjoint(Y_dev, B_dev);
+  Buffers b;
+  for (int i = 0; i < 4; ++i) {
+    b.x[i] = w->x[i];
+    b.lp[i] = w->lp[i];
+  }
+  if (in_place) {
+    b.x[0] = const_cast<double*>(A_dev);
+    b.x[1] = const_cast<double*>(B_dev);
+    b.x[2] = Y_dev;
+  }
+  SNF_HIP(hipMemcpyAsync(w->bufs_dev, &b, sizeof(b), hipMemcpyHostToDevice, s));
   SnfState* sh = w->state_host;
   memset(sh, 0, sizeof(*sh));
   sh->mode = precision;
@@ -974,19 +994,21 @@ int snf_step_dense(const double* A_dev, const double* B_dev, int64_t n, int64_t 
   sh->kind = kKindSquare;
   sh->want_e = 1;
   sh->ia = 0;
-  sh->ib = 1;
+  sh->ib = square ? 0 : 1;
   sh->ix = 0;
   sh->io = 2;
   sh->write_lowp = 0;
   SNF_HIP(hipMemcpyAsync(w->state, sh, sizeof(SnfState), hipMemcpyHostToDevice, s));
-  launch_pad_copy(A_dev, n, ld, w->x[0], np, w->lp[0], lk, s);
-  launch_pad_copy(B_dev, n, ld, w->x[1], np, w->lp[1], lk, s);
+  if (!in_place || lk >= 0) {
+    launch_pad_copy(A_dev, n, ld, in_place ? nullptr : w->x[0], np, w->lp[0], lk, s);
+    if (!square) launch_pad_copy(B_dev, n, ld, in_place ? nullptr : w->x[1], np, w->lp[1], lk, s);
+  }
   SNF_HIP(hipEventRecord(w->ev[0], s));
   launch_product(sh->prec, w->state, w->bufs_dev, grid, s);
   launch_split_fixup(w->state, w->bufs_dev, grid, s);
   SNF_HIP(hipEventRecord(w->ev[1], s));
   launch_sum_partials(w->partials, grid.partial_count, w->sums_dev, s);
-  launch_unpad_copy(w->x[2], np, n, Y_dev, ld, s);
+  if (!in_place) launch_unpad_copy(w->x[2], np, n, Y_dev, ld, s);
   SNF_HIP(hipGetLastError());
   SNF_HIP(hipMemcpyAsync(w->sums_host, w->sums_dev, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
   SNF_HIP(hipStreamSynchronize(s));

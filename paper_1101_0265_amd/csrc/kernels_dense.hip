@@ -1832,56 +1832,98 @@ void launch_schedule(SnfState* st, const double* partials, int count, int init,
 // ---------------------------------------------------------------------------------------
 // Copies
 // ---------------------------------------------------------------------------------------
-__global__ void copy_out_kernel(const SnfState* __restrict__ st, const Buffers* __restrict__ bufs,
-                                int64_t n, int64_t np, double* __restrict__ D, int64_t ld) {
-  const double* X = bufs->x[st->cur];
-  const int64_t total = n * n;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = t / n, c = t % n;
-    D[r * ld + c] = X[r * np + c];
+static unsigned copy_blocks(int64_t rows) { return (unsigned)(rows < 2048 ? rows : 2048); }
+
+// dst[r][c] = src[r][c] for r, c < n: a row per workgroup and turn (no index division), four
+// columns per thread, as two 16-byte accesses where both rows allow them.
+__device__ __forceinline__ void copy_rows(const double* __restrict__ src, int64_t lds_,
+                                          double* __restrict__ dst, int64_t ldd, int64_t n) {
+  const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0 && !((lds_ | ldd) & 1);
+  for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
+    const double* p = src + r * lds_;
+    double* q = dst + r * ldd;
+    for (int64_t c = 4 * (int64_t)threadIdx.x; c < n; c += 4 * (int64_t)blockDim.x) {
+      if (vec && c + 4 <= n) {
+        const u32x4 v0 = gload16(p + c), v1 = gload16(p + c + 2);
+        *(u32x4*)(q + c) = v0;
+        *(u32x4*)(q + c + 2) = v1;
+      } else {
+        for (int64_t e = c; e < n && e < c + 4; ++e) q[e] = p[e];
+      }
+    }
   }
+}
+
+__global__ __launch_bounds__(256) void copy_out_kernel(const SnfState* __restrict__ st,
+                                                       const Buffers* __restrict__ bufs, int64_t n,
+                                                       int64_t np, double* __restrict__ D,
+                                                       int64_t ld) {
+  copy_rows(bufs->x[st->cur], np, D, ld, n);
 }
 
 void launch_copy_out(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
                      double* D, int64_t ld, hipStream_t s) {
-  hipLaunchKernelGGL(copy_out_kernel, dim3(kF0Blocks), dim3(256), 0, s, st, bufs_dev, n, np, D,
-                     ld);
+  hipLaunchKernelGGL(copy_out_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, st, bufs_dev, n, np,
+                     D, ld);
 }
 
-__global__ void pad_copy_kernel(const double* __restrict__ src, int64_t n, int64_t ld,
-                                double* __restrict__ dst, int64_t np, void* __restrict__ lp,
-                                int lowp_kind) {
-  const int64_t total = np * np;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = t / np, c = t % np;
-    const double v = (r < n && c < n) ? src[r * ld + c] : 0.0;
-    dst[t] = v;
-    if (lowp_kind == kPrecF32) ((float*)lp)[t] = (float)v;
-    else if (lowp_kind == kPrecBF16) ((unsigned short*)lp)[t] = f32_to_bf16_rne((float)v);
+// The padded copy of a caller's matrix, zero beyond n, and its low-precision copy; dst may be
+// null (the caller's matrix serves as it is), and so may lp.
+__global__ __launch_bounds__(256) void pad_copy_kernel(const double* __restrict__ src, int64_t n,
+                                                       int64_t ld, double* __restrict__ dst,
+                                                       int64_t np, void* __restrict__ lp,
+                                                       int lowp_kind) {
+  const bool vec = ((uintptr_t)src & 15) == 0 && !(ld & 1);
+  for (int64_t r = blockIdx.x; r < np; r += gridDim.x) {
+    const double* p = src + r * ld;
+    for (int64_t c = 4 * (int64_t)threadIdx.x; c < np; c += 4 * (int64_t)blockDim.x) {
+      double v[4] = {0.0, 0.0, 0.0, 0.0};
+      if (r < n) {
+        if (vec && c + 4 <= n) {
+          const double2 v0 = __builtin_bit_cast(double2, gload16(p + c));
+          const double2 v1 = __builtin_bit_cast(double2, gload16(p + c + 2));
+          v[0] = v0.x;
+          v[1] = v0.y;
+          v[2] = v1.x;
+          v[3] = v1.y;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (c + e < n) v[e] = p[c + e];
+        }
+      }
+      const int64_t o = r * np + c;
+      if (dst) {
+        *(double2*)(dst + o) = double2{v[0], v[1]};
+        *(double2*)(dst + o + 2) = double2{v[2], v[3]};
+      }
+      if (lowp_kind == kPrecF32) {
+        *(float4*)((float*)lp + o) = float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+      } else if (lowp_kind == kPrecBF16) {
+        unsigned b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = f32_to_bf16_rne((float)v[e]);
+        *(uint2*)((unsigned short*)lp + o) = uint2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+      }
+    }
   }
 }
 
 void launch_pad_copy(const double* src, int64_t n, int64_t ld, double* dst, int64_t np,
                      void* lp_dst, int lowp_kind, hipStream_t s) {
-  hipLaunchKernelGGL(pad_copy_kernel, dim3(kF0Blocks), dim3(256), 0, s, src, n, ld, dst, np,
+  hipLaunchKernelGGL(pad_copy_kernel, dim3(copy_blocks(np)), dim3(256), 0, s, src, n, ld, dst, np,
                      lp_dst, lowp_kind);
 }
 
-__global__ void unpad_copy_kernel(const double* __restrict__ src, int64_t np, int64_t n,
-                                  double* __restrict__ dst, int64_t ld) {
-  const int64_t total = n * n;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = t / n, c = t % n;
-    dst[r * ld + c] = src[r * np + c];
-  }
+__global__ __launch_bounds__(256) void unpad_copy_kernel(const double* __restrict__ src, int64_t np,
+                                                         int64_t n, double* __restrict__ dst,
+                                                         int64_t ld) {
+  copy_rows(src, np, dst, ld, n);
 }
 
 void launch_unpad_copy(const double* src, int64_t np, int64_t n, double* dst, int64_t ld,
                        hipStream_t s) {
-  hipLaunchKernelGGL(unpad_copy_kernel, dim3(kF0Blocks), dim3(256), 0, s, src, np, n, dst, ld);
+  hipLaunchKernelGGL(unpad_copy_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, src, np, n, dst, ld);
 }
 
 __global__ void sum_partials_kernel(const double* __restrict__ partials, int count,
