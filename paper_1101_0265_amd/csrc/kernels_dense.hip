@@ -927,14 +927,14 @@ void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid
 // Schedule: reduce the partials in a fixed order, then advance the scalar state.
 // ---------------------------------------------------------------------------------------
 // alpha of a scaled P_{i,j} step: the smaller of the two sides' roots (tables from the state)
-__device__ double pij_alpha_state(const SnfHeader* s) {
+__device__ __forceinline__ double pij_alpha_state(const SnfHeader* s) {
   const double lo = sched::pij_alpha_side_tab(s->pij_i, s->pij_j, s->pbin[0], s->xstar, s->beta);
   const double hi =
       sched::pij_alpha_side_tab(s->pij_j, s->pij_i, s->pbin[1], 1.0 - s->xstar, s->abar);
   return lo < hi ? lo : hi;
 }
 
-__device__ void decide(SnfHeader* s) {
+__device__ __forceinline__ void decide(SnfHeader* s) {
 #pragma clang fp contract(off)
   // precision phase (only for the mixed-precision modes)
   if (s->mode != SNF_P_FP64) {
@@ -1028,7 +1028,7 @@ __device__ void decide(SnfHeader* s) {
   }
 }
 
-__device__ void advance_beta(SnfHeader* s, int br, double a) {
+__device__ __forceinline__ void advance_beta(SnfHeader* s, int br, double a) {
 #pragma clang fp contract(off)
   if (br == SNF_BRANCH_SQUARE) {
     s->beta = sched::alg2_square_map(s->beta, a);
@@ -1056,7 +1056,7 @@ __device__ void advance_beta(SnfHeader* s, int br, double a) {
 // Set up the next product of a P_{m,m} iteration once the previous one finished:
 // P(1/2 + v) = 1/2 + v r(v^2), v = a (X - I/2), W = v^2.  After W: T = r_m W^2 + r_{m-1} W
 // + r_{m-2} I from W.W; then T <- W.T + r_k I down to k = 0; then X_new = 1/2 I + v T.
-__device__ void pmm_next(SnfHeader* s) {
+__device__ __forceinline__ void pmm_next(SnfHeader* s) {
 #pragma clang fp contract(off)
   const int m = s->pmm_m;
   double r[sched::kPmmMaxM + 1];
@@ -1096,7 +1096,7 @@ __device__ void pmm_next(SnfHeader* s) {
 // Set up the next product of a P_{i,j} iteration: P(x* + v) = x* + v Q(v), v = a (X - x* I),
 // W = v^2, Q(v) = sum_k (q_2k + q_(2k+1) v) W^k.  The first product gave W and the top level
 // T; then T <- T.W + q_(2k+1) V + q_2k I for k = h - 2 .. 0; then X_new = x* I + V T.
-__device__ void pij_next(SnfHeader* s) {
+__device__ __forceinline__ void pij_next(SnfHeader* s) {
 #pragma clang fp contract(off)
   const double a = s->alpha, xs = s->xstar;
   const int ta = (s->cur + 2) & 3, tb = (s->cur + 3) & 3;
@@ -1125,7 +1125,7 @@ __device__ void pij_next(SnfHeader* s) {
   s->c0 = xs;
 }
 
-__device__ void finish(SnfHeader* s, int status) {
+__device__ __forceinline__ void finish(SnfHeader* s, int status) {
   if ((status == SNF_OK || status == SNF_OK_FLOOR) && s->has_nocc) {
     const double err = s->t1 - (double)s->n_occ;
     if (fabs(err) >= 0.5) status = SNF_EMIXED;
@@ -1134,9 +1134,11 @@ __device__ void finish(SnfHeader* s, int status) {
   s->stop = 1;
 }
 
-// The scalar state machine, run by one thread on a copy of the state's header in LDS (s);
+// The scalar state machine, run by one thread on a copy of the state's header in LDS (s).  It
+// and what it calls are inlined: as calls they took the header through flat addresses and a
+// stack in scratch memory (a one-workgroup solve of order 64: 186 us, inlined 158).
 // the per-iteration log record goes straight to memory (log; not written when null).
-__device__ void schedule_step(SnfHeader* __restrict__ s, snf_log_rec* __restrict__ log, double e2,
+__device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ s, snf_log_rec* __restrict__ log, double e2,
                               double t1, double t2, int init) {
   if (init) {
     s->t1 = t1;
@@ -1226,7 +1228,7 @@ __device__ void schedule_step(SnfHeader* __restrict__ s, snf_log_rec* __restrict
 // chain of dependent single-thread loads and stores to device memory.
 constexpr int kStateHeaderBytes = (int)sizeof(SnfHeader);
 
-__device__ void schedule_body(SnfState* __restrict__ sg, const double* __restrict__ partials,
+__device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg, const double* __restrict__ partials,
                               int count, int init) {
   __shared__ double red[24];
   __shared__ __attribute__((aligned(16))) SnfHeader hs;
