@@ -692,10 +692,10 @@ static int direct_steps(const DirectArgs& a, int tile, StepOperands ops, int max
       seen = *progress;
     }
     if (seen < 0) break;
-    int pa = 0, pb = 0;
-    ops.next(&pa, &pb);
+    int op[3];
+    ops.next(op);
     if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq], s));
-    launch_direct_step(tile, a, enq, pa, pb, s);
+    launch_direct_step(tile, a, enq, op, s);
     if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq + 1], s));
     ++enq;
   }

@@ -115,9 +115,9 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
     bool stopped = false;
     while (!stopped && enq <= max_steps) {
       for (int k = 0; k < 8 && enq <= max_steps; ++k, ++enq) {
-        int pa = 0, pb = 0;
-        ops.next(&pa, &pb);
-        launch_direct_step(tile, a, enq, pa, pb, s);
+        int op[3];
+        ops.next(op);
+        launch_direct_step(tile, a, enq, op, s);
       }
       NA_HIP(hipGetLastError());
       // a synchronous read of the stop flag (no pinned staging, no events)

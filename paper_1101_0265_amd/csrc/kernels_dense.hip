@@ -59,6 +59,28 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// The same sum in another order, without the shuffles' trips through LDS: within rows of 16
+// lanes by DPP, then the four rows' sums from scalar registers (0.1 us against 0.4).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+__device__ __forceinline__ double wave_sum_rows(double v) {
+  v = dpp_add<0xB1>(v);       // lanes 1, 0, 3, 2 of each quad
+  v = dpp_add<0x4E>(v);       // lanes 2, 3, 0, 1
+  v = dpp_add<0x141>(v);      // the other quad of each eight (row_half_mirror)
+  v = dpp_add<0x140>(v);      // the other eight of each row (row_mirror)
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
 // Sum three values over the block (up to 8 waves), in wave order; result valid in thread 0.
 __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double* lds24) {
   a = wave_sum(a);
@@ -927,40 +949,39 @@ void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid
 // Schedule: reduce the partials in a fixed order, then advance the scalar state.
 // ---------------------------------------------------------------------------------------
 // alpha of a scaled P_{i,j} step: the smaller of the two sides' roots (tables from the state)
-__device__ __forceinline__ double pij_alpha_state(const SnfHeader* s) {
-  const double lo = sched::pij_alpha_side_tab(s->pij_i, s->pij_j, s->pbin[0], s->xstar, s->beta);
+__device__ __forceinline__ double pij_alpha_state(const SnfScalars* s, const SnfTables* t) {
+  const double lo = sched::pij_alpha_side_tab(s->pij_i, s->pij_j, t->pbin[0], s->xstar, s->beta);
   const double hi =
-      sched::pij_alpha_side_tab(s->pij_j, s->pij_i, s->pbin[1], 1.0 - s->xstar, s->abar);
+      sched::pij_alpha_side_tab(s->pij_j, s->pij_i, t->pbin[1], 1.0 - s->xstar, s->abar);
   return lo < hi ? lo : hi;
 }
 
-__device__ __forceinline__ void decide(SnfHeader* s) {
+__device__ __forceinline__ void decide(SnfScalars* s, const SnfConfig* c, const SnfTables* t) {
 #pragma clang fp contract(off)
   // precision phase (only for the mixed-precision modes)
-  if (s->mode != SNF_P_FP64) {
-    if (s->phase == kPhaseHigh && (s->betabar - s->beta) >= s->gap_switch) s->phase = kPhaseLow;
-    if (s->phase == kPhaseLow && s->mode != SNF_P_FP32) {
+  if (c->mode != SNF_P_FP64) {
+    if (s->phase == kPhaseHigh && (s->betabar - s->beta) >= c->gap_switch) s->phase = kPhaseLow;
+    if (s->phase == kPhaseLow && c->mode != SNF_P_FP32) {
       const double bound = s->beta > 1.0 - s->betabar ? s->beta : 1.0 - s->betabar;
-      if (bound <= s->lowp_floor) s->phase = kPhaseRefine;
+      if (bound <= c->lowp_floor) s->phase = kPhaseRefine;
     }
   }
-  s->prec = (s->phase == kPhaseLow) ? (s->mode == SNF_P_BF16_REF64 ? kPrecBF16 : kPrecF32)
+  s->prec = (s->phase == kPhaseLow) ? (c->mode == SNF_P_BF16_REF64 ? kPrecBF16 : kPrecF32)
                                     : kPrecF64;
-  s->write_lowp = (s->mode != SNF_P_FP64 && s->phase != kPhaseRefine) ? 1 : 0;
+  s->write_lowp = (c->mode != SNF_P_FP64 && s->phase != kPhaseRefine) ? 1 : 0;
 
-  int scheme = s->scheme;
-  if (s->phase == kPhaseRefine) scheme = s->has_nocc ? SNF_SP2_TRACE : SNF_MCWEENY;
+  int scheme = c->scheme;
+  if (s->phase == kPhaseRefine) scheme = c->has_nocc ? SNF_SP2_TRACE : SNF_MCWEENY;
 
   double a = 0.0;
   int br;
-  s->dual = 0;
   if (scheme_is_pij(scheme)) {
     br = SNF_BRANCH_PIJ;
     a = (scheme == SNF_SNF_FIXMU_PIJ)
-            ? pij_alpha_state(s)
+            ? pij_alpha_state(s, t)
             : 1.0;
   } else if (scheme == SNF_SP2_TRACE) {
-    br = sched::trace_square(s->t1, s->t2, (double)s->n_occ) ? SNF_BRANCH_SQUARE
+    br = sched::trace_square(s->t1, s->t2, (double)c->n_occ) ? SNF_BRANCH_SQUARE
                                                              : SNF_BRANCH_FOLD;
   } else if (scheme == SNF_TC2_BETA || scheme == SNF_SNF_VARMU) {
     const bool sq = sched::alg2_square(s->beta, s->betabar);
@@ -970,7 +991,7 @@ __device__ __forceinline__ void decide(SnfHeader* s) {
   } else if (scheme_pmm_m(scheme)) {
     br = s->pmm_m == 3 ? SNF_BRANCH_P33 : SNF_BRANCH_P55;
     a = (scheme == SNF_SNF_FIXMU3 || scheme == SNF_SNF_FIXMU5)
-            ? sched::pmm_alpha_tab(s->pmm_m, s->pbin[0], s->beta)
+            ? sched::pmm_alpha_tab(s->pmm_m, t->pbin[0], s->beta)
                                                                : 1.0;
   } else {
     br = SNF_BRANCH_P11;
@@ -978,57 +999,71 @@ __device__ __forceinline__ void decide(SnfHeader* s) {
   }
   s->branch = br;
   s->alpha = a;
+  // (results in locals, stored once: stores at the end of several branches would be merged into
+  // one through a computed address, and the state could not stay in registers)
+  double kc2, kc1, kc0, kd2 = s->d2, kd1 = s->d1, kd0 = s->d0;
   if (br == SNF_BRANCH_PIJ) {
     // W = V^2, V = a (X - x* I): W = a^2 P - 2 a^2 x* X + a^2 x*^2 I; and beside it the top
     // Horner level T = q_2h W + q_(2h-1) V + q_(2h-2) I in the same epilogue
     const double xs = s->xstar, a2 = a * a;
     const int h = (s->pij_i + s->pij_j) / 2;
-    const double qt = s->pq[2 * h], qo = s->pq[2 * h - 1], qc = s->pq[2 * h - 2];
-    s->c2 = a2;
-    s->c1 = -2.0 * a2 * xs;
-    s->c0 = a2 * xs * xs;
-    s->d2 = qt * a2;
-    s->d1 = qo * a - 2.0 * qt * a2 * xs;
-    s->d0 = qt * a2 * xs * xs - qo * a * xs + qc;
+    const double qt = t->pq[2 * h], qo = t->pq[2 * h - 1], qc = t->pq[2 * h - 2];
+    kc2 = a2;
+    kc1 = -2.0 * a2 * xs;
+    kc0 = a2 * xs * xs;
+    kd2 = qt * a2;
+    kd1 = qo * a - 2.0 * qt * a2 * xs;
+    kd0 = qt * a2 * xs * xs - qo * a * xs + qc;
   } else if (br == SNF_BRANCH_P33 || br == SNF_BRANCH_P55) {
     // W = (a (X - I/2))^2 = a^2 P - a^2 X + (a^2 / 4) I
     const double a2 = a * a;
-    s->c2 = a2;
-    s->c1 = -a2;
-    s->c0 = 0.25 * a2;
+    kc2 = a2;
+    kc1 = -a2;
+    kc0 = 0.25 * a2;
   } else if (br == SNF_BRANCH_SQUARE) {          // ((1+a) X - a I)^2 = (1+a)^2 P - 2a(1+a) X + a^2 I
-    s->c2 = (1.0 + a) * (1.0 + a);
-    s->c1 = -2.0 * a * (1.0 + a);
-    s->c0 = a * a;
+    kc2 = (1.0 + a) * (1.0 + a);
+    kc1 = -2.0 * a * (1.0 + a);
+    kc0 = a * a;
   } else if (br == SNF_BRANCH_FOLD) {     // 2(1+a) X - (1+a)^2 P
-    s->c2 = -((1.0 + a) * (1.0 + a));
-    s->c1 = 2.0 * (1.0 + a);
-    s->c0 = 0.0;
+    kc2 = -((1.0 + a) * (1.0 + a));
+    kc1 = 2.0 * (1.0 + a);
+    kc0 = 0.0;
   } else {                                // S2 = Xs^2 = a^2 P + 2 a c X + c^2 I, c = (1-a)/2
-    const double c = 0.5 * (1.0 - a);
-    s->c2 = a * a;
-    s->c1 = 2.0 * a * c;
-    s->c0 = c * c;
+    const double sh = 0.5 * (1.0 - a);
+    kc2 = a * a;
+    kc1 = 2.0 * a * sh;
+    kc0 = sh * sh;
   }
+  s->c2 = kc2;
+  s->c1 = kc1;
+  s->c0 = kc0;
+  s->d2 = kd2;
+  s->d1 = kd1;
+  s->d0 = kd0;
   s->kind = kKindSquare;
   s->want_e = 1;
   s->ia = s->ib = s->ix = s->cur;
+  const int cur = s->cur, w = (cur + 1) & 3, ta = (cur + 2) & 3;
+  int io = (br == SNF_BRANCH_P11) ? 2 : 1 - cur, left = s->horner_left, bw = s->bw, bt = s->bt;
+  int io2 = s->io2, dual = 0;
   if (br == SNF_BRANCH_P33 || br == SNF_BRANCH_P55) {
-    s->bw = (s->cur + 1) & 3;
-    s->io = s->bw;
-    s->horner_left = s->pmm_m - 1;
+    bw = io = w;
+    left = s->pmm_m - 1;
   } else if (br == SNF_BRANCH_PIJ) {
-    s->bw = (s->cur + 1) & 3;
-    s->io = s->bw;
-    s->dual = 1;
-    s->io2 = s->bt = (s->cur + 2) & 3;
-    s->horner_left = (s->pij_i + s->pij_j) / 2 - 1;
-  } else {
-    s->io = (br == SNF_BRANCH_P11) ? 2 : 1 - s->cur;
+    bw = io = w;
+    dual = 1;
+    io2 = bt = ta;
+    left = (s->pij_i + s->pij_j) / 2 - 1;
   }
+  s->io = io;
+  s->io2 = io2;
+  s->bw = bw;
+  s->bt = bt;
+  s->dual = dual;
+  s->horner_left = left;
 }
 
-__device__ __forceinline__ void advance_beta(SnfHeader* s, int br, double a) {
+__device__ __forceinline__ void advance_beta(SnfScalars* s, const SnfTables* t, int br, double a) {
 #pragma clang fp contract(off)
   if (br == SNF_BRANCH_SQUARE) {
     s->beta = sched::alg2_square_map(s->beta, a);
@@ -1041,14 +1076,14 @@ __device__ __forceinline__ void advance_beta(SnfHeader* s, int br, double a) {
     s->betabar = 1.0 - s->beta;
   } else if (br == SNF_BRANCH_PIJ) {
     const double xs = s->xstar;
-    const double an = sched::pij_side_next_tab(s->pij_i, s->pij_j, s->pbin[0], xs, s->beta, a);
+    const double an = sched::pij_side_next_tab(s->pij_i, s->pij_j, t->pbin[0], xs, s->beta, a);
     const double bn =
-        sched::pij_side_next_tab(s->pij_j, s->pij_i, s->pbin[1], 1.0 - xs, s->abar, a);
+        sched::pij_side_next_tab(s->pij_j, s->pij_i, t->pbin[1], 1.0 - xs, s->abar, a);
     s->beta = an;
     s->abar = bn;
     s->betabar = 1.0 - bn;
   } else {
-    s->beta = sched::pij_eval_tab(s->pmm_m, s->pmm_m, s->pbin[0], a * (s->beta - 0.5) + 0.5);
+    s->beta = sched::pij_eval_tab(s->pmm_m, s->pmm_m, t->pbin[0], a * (s->beta - 0.5) + 0.5);
     s->betabar = 1.0 - s->beta;
   }
 }
@@ -1056,11 +1091,10 @@ __device__ __forceinline__ void advance_beta(SnfHeader* s, int br, double a) {
 // Set up the next product of a P_{m,m} iteration once the previous one finished:
 // P(1/2 + v) = 1/2 + v r(v^2), v = a (X - I/2), W = v^2.  After W: T = r_m W^2 + r_{m-1} W
 // + r_{m-2} I from W.W; then T <- W.T + r_k I down to k = 0; then X_new = 1/2 I + v T.
-__device__ __forceinline__ void pmm_next(SnfHeader* s) {
+__device__ __forceinline__ void pmm_next(SnfScalars* s, const SnfTables* t) {
 #pragma clang fp contract(off)
   const int m = s->pmm_m;
-  double r[sched::kPmmMaxM + 1];
-  for (int k = 0; k <= m; ++k) r[k] = s->pr[k];
+  const double* r = t->pr;
   const int ta = (s->cur + 2) & 3, tb = (s->cur + 3) & 3;
   s->want_e = 0;
   if (s->kind == kKindSquare) {             // W done: first Horner level from W.W
@@ -1096,7 +1130,7 @@ __device__ __forceinline__ void pmm_next(SnfHeader* s) {
 // Set up the next product of a P_{i,j} iteration: P(x* + v) = x* + v Q(v), v = a (X - x* I),
 // W = v^2, Q(v) = sum_k (q_2k + q_(2k+1) v) W^k.  The first product gave W and the top level
 // T; then T <- T.W + q_(2k+1) V + q_2k I for k = h - 2 .. 0; then X_new = x* I + V T.
-__device__ __forceinline__ void pij_next(SnfHeader* s) {
+__device__ __forceinline__ void pij_next(SnfScalars* s, const SnfTables* t) {
 #pragma clang fp contract(off)
   const double a = s->alpha, xs = s->xstar;
   const int ta = (s->cur + 2) & 3, tb = (s->cur + 3) & 3;
@@ -1111,8 +1145,8 @@ __device__ __forceinline__ void pij_next(SnfHeader* s) {
     s->io = (s->bt == ta) ? tb : ta;
     s->bt = s->io;
     s->c2 = 1.0;
-    s->c1 = s->pq[2 * k + 1] * a;
-    s->c0 = s->pq[2 * k] - s->pq[2 * k + 1] * a * xs;
+    s->c1 = t->pq[2 * k + 1] * a;
+    s->c0 = t->pq[2 * k] - t->pq[2 * k + 1] * a * xs;
     return;
   }
   // X_new = a X.T - a x* T + x* I, written over W
@@ -1125,9 +1159,9 @@ __device__ __forceinline__ void pij_next(SnfHeader* s) {
   s->c0 = xs;
 }
 
-__device__ __forceinline__ void finish(SnfHeader* s, int status) {
-  if ((status == SNF_OK || status == SNF_OK_FLOOR) && s->has_nocc) {
-    const double err = s->t1 - (double)s->n_occ;
+__device__ __forceinline__ void finish(SnfScalars* s, const SnfConfig* c, int status) {
+  if ((status == SNF_OK || status == SNF_OK_FLOOR) && c->has_nocc) {
+    const double err = s->t1 - (double)c->n_occ;
     if (fabs(err) >= 0.5) status = SNF_EMIXED;
   }
   s->status = status;
@@ -1138,64 +1172,70 @@ __device__ __forceinline__ void finish(SnfHeader* s, int status) {
 // and what it calls are inlined: as calls they took the header through flat addresses and a
 // stack in scratch memory (a one-workgroup solve of order 64: 186 us, inlined 158).
 // the per-iteration log record goes straight to memory (log; not written when null).
-__device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ s, snf_log_rec* __restrict__ log, double e2,
-                              double t1, double t2, int init) {
+__device__ __forceinline__ void schedule_scalars(SnfScalars* __restrict__ s,
+                                                 const SnfConfig* __restrict__ c,
+                                                 const SnfTables* __restrict__ t,
+                                                 snf_log_rec* __restrict__ log, double e2,
+                                                 double t1, double t2, int init) {
   if (init) {
     s->t1 = t1;
     s->t2 = t2;
-    decide(s);
+    decide(s, c, t);
     return;
   }
   s->products += 1;
-  if (s->prec == kPrecF64) s->products_f64 += 1; else s->products_lowp += 1;
+  const int f64 = s->prec == kPrecF64 ? 1 : 0;
+  s->products_f64 += f64;
+  s->products_lowp += 1 - f64;
   if (s->kind == kKindSquare) {
     const double e = sqrt(e2);
     s->e_last = e;
     const int it = s->iter;
-    snf_log_rec dummy;
-    snf_log_rec* rec = log ? &log[it < SNF_LOG_MAX ? it : SNF_LOG_MAX - 1] : &dummy;
-    rec->i = it;
-    rec->branch = s->branch;
-    rec->precision = s->prec;
-    rec->reserved = s->phase;
-    rec->alpha = s->alpha;
-    rec->beta = s->beta;
-    rec->betabar = s->betabar;
-    rec->e = e;
-    rec->t1 = s->t1;
-    rec->t2 = s->t2;
+    snf_log_rec* rec = log ? &log[it < SNF_LOG_MAX ? it : SNF_LOG_MAX - 1] : nullptr;
+    if (rec) {
+      rec->i = it;
+      rec->branch = s->branch;
+      rec->precision = s->prec;
+      rec->reserved = s->phase;
+      rec->alpha = s->alpha;
+      rec->beta = s->beta;
+      rec->betabar = s->betabar;
+      rec->e = e;
+      rec->t1 = s->t1;
+      rec->t2 = s->t2;
+    }
     s->nlog = it + 1;
     s->e_hist[2] = s->e_hist[1];
     s->e_hist[1] = s->e_hist[0];
     s->e_hist[0] = e;
-    if (!isfinite(e)) { rec->branch = -1; finish(s, SNF_ENONFINITE); return; }
-    if (e <= s->tol) { rec->branch = -1; finish(s, SNF_OK); return; }
-    if (s->phase == kPhaseLow && s->mode == SNF_P_FP32 && it >= 2) {
+    if (!isfinite(e)) { if (rec) rec->branch = -1; finish(s, c, SNF_ENONFINITE); return; }
+    if (e <= c->tol) { if (rec) rec->branch = -1; finish(s, c, SNF_OK); return; }
+    if (s->phase == kPhaseLow && c->mode == SNF_P_FP32 && it >= 2) {
       // floor of the FP32-only mode: stop once the predicted error is below the floor
       // parameter and the measured idempotency stopped shrinking
       const double bound = s->beta > 1.0 - s->betabar ? s->beta : 1.0 - s->betabar;
-      if (bound <= s->lowp_floor && e > 0.5 * s->e_hist[2]) {
-        rec->branch = -1;
-        finish(s, SNF_OK_FLOOR);
+      if (bound <= c->lowp_floor && e > 0.5 * s->e_hist[2]) {
+        if (rec) rec->branch = -1;
+        finish(s, c, SNF_OK_FLOOR);
         return;
       }
     }
-    if (it >= s->max_iter) { rec->branch = -1; finish(s, SNF_ENOCONV); return; }
+    if (it >= c->max_iter) { if (rec) rec->branch = -1; finish(s, c, SNF_ENOCONV); return; }
     if (s->pmm_m) {
-      pmm_next(s);
+      pmm_next(s, t);
       return;
     }
     if (s->pij_i) {
-      pij_next(s);
+      pij_next(s, t);
       return;
     }
     if (s->branch == SNF_BRANCH_P11) {
       // second product of Algorithm 1: R = S2.X; X_new = (3 - 2c) S2 - 2 a R
-      const double a = s->alpha, c = 0.5 * (1.0 - a);
+      const double a = s->alpha, sh = 0.5 * (1.0 - a);
       s->kind = kKindCube;
       s->want_e = 0;
       s->c2 = -2.0 * a;
-      s->c1 = 3.0 - 2.0 * c;
+      s->c1 = 3.0 - 2.0 * sh;
       s->c0 = 0.0;
       s->ia = 2;            // S2
       s->ib = s->cur;       // X
@@ -1203,23 +1243,34 @@ __device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ s, snf_log
       s->io = 1 - s->cur;
       return;
     }
-    advance_beta(s, s->branch, s->alpha);
+    advance_beta(s, t, s->branch, s->alpha);
     s->iter = it + 1;
     s->cur = s->io;
     s->t1 = t1;
     s->t2 = t2;
-    decide(s);
+    decide(s, c, t);
   } else if (s->kind == kKindHorner) {
     s->horner_left -= 1;
-    if (s->pij_i) pij_next(s); else pmm_next(s);
+    if (s->pij_i) pij_next(s, t); else pmm_next(s, t);
   } else {                                  // kKindCube or kKindFinal: X_new is complete
-    advance_beta(s, s->branch, s->alpha);
+    advance_beta(s, t, s->branch, s->alpha);
     s->iter += 1;
     s->cur = s->io;
     s->t1 = t1;
     s->t2 = t2;
-    decide(s);
+    decide(s, c, t);
   }
+}
+
+// The same on a header in LDS: its scalars go to registers and back, as the state machine would
+// otherwise wait for a chain of single LDS reads.
+__device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ hs,
+                                              snf_log_rec* __restrict__ log, double e2, double t1,
+                                              double t2, int init) {
+  SnfScalars sc = *hs;
+  const SnfConfig cf = *hs;
+  schedule_scalars(&sc, &cf, hs, log, e2, t1, t2, init);
+  *static_cast<SnfScalars*>(hs) = sc;
 }
 
 // Reduce the partial sums in a fixed order, then advance the scalar state.  The state's
@@ -1316,17 +1367,28 @@ struct DirectOperand {
 };
 
 // NC: column groups of the tile; four waves (the k quarters) for each, so that a wave holds
-// TB x TB / NC blocks.
-template <int TB, int NC, int PD>
-__global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectArgs g, int step,
-                                                                         int pa, int pb) {
+// TB x TB / NC blocks.  SW: one more wave, which runs the schedule beside the product (where the
+// registers allow it; else wave 0 does, ahead of its share).  The product needs the schedule's
+// result only in its epilogue, as the operands are known beforehand; a flag in LDS stops the
+// waves early once the schedule has stopped the solve.
+template <int TB, int NC, int PD, bool SW>
+__global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_step_kernel(
+    DirectArgs g, int step, int pa, int pb, int px) {
   constexpr int T = 16 * TB, QB = TB / NC, NT = kDirectThreads * NC;
   static_assert(QB * NC == TB, "equal column groups");
   constexpr int P = TB / 2, O = TB & 1, QP = QB / 2, QO = QB & 1, LW = T + 2;
+  constexpr int SWAVE = SW ? 4 * NC : 0;
+  // the product starts ahead of the schedule; the largest tiles wait for it, as their product
+  // takes 20 times as long and the look at the flag costs their loop more (n = 1760: 5%)
+  constexpr bool EARLY = TB <= 4;
   __shared__ __attribute__((aligned(16))) SnfHeader hs;
-  __shared__ double red[24];
-  __shared__ __attribute__((aligned(16))) double part[4][32][LW];
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  __shared__ double red[3 * 9];
+  __shared__ int stopped;                  // set by the schedule, looked at between k-steps
+  // (more than half of a compute unit's LDS: two workgroups on one unit would leave another idle)
+  constexpr int PR = 4 * 32 * LW * 8 > (82 << 10) ? 32 : (82 << 10) / (4 * LW * 8) + 1;
+  __shared__ __attribute__((aligned(16))) double part[4][PR][LW];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool worker = !SW || wid != SWAVE;
   const int fr = lane & 15, fk = lane >> 4;
   const int kq = wid & 3, cg = wid >> 2;                // k quarter, column group
   const int64_t ld = g.ld;
@@ -1336,65 +1398,83 @@ __global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectA
   tile_coords(tile, g.nt, 1, bi, bj);
   const int64_t i0 = (int64_t)bi * T, j0 = (int64_t)bj * T;
 
-  // header and sums first: loads return in order, and these are waited for first
-  constexpr int HW = (int)(sizeof(SnfHeader) / 4);
-  static_assert(sizeof(SnfHeader) % 4 == 0 && HW <= 2 * NT, "two words a thread");
-  const unsigned* gh = (const unsigned*)(g.hdr + (step & 1));
-  const unsigned h0 = tid < HW ? gh[tid] : 0u;
-  const unsigned h1 = tid + NT < HW ? gh[tid + NT] : 0u;
-  const int count = step ? tiles : kDirectF0Blocks;
-  const double* ps = g.partials + (size_t)((step + 1) & 1) * kDirectSlots * 4;
-  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
-  if (tid < count) {
-    e2 = ps[tid * 4 + 0];
-    t1 = ps[tid * 4 + 1];
-    t2 = ps[tid * 4 + 2];
+  const SnfHeader* hd = g.hdr + (step & 1);
+  if (tid == 0) stopped = 0;
+  if (hd->stop) {
+    // a launch after the stop: hand the state on
+    if (blockIdx.x == 0) {
+      const unsigned* gh = (const unsigned*)hd;
+      unsigned* gn = (unsigned*)(g.hdr + ((step + 1) & 1));
+      for (int i = tid; i < (int)(sizeof(SnfHeader) / 4); i += blockDim.x) gn[i] = gh[i];
+    }
+    return;
   }
+  __syncthreads();
+
+  // the schedule of the step before (step 0: the first decision), by one wave
+  constexpr int HW = (int)(sizeof(SnfHeader) / 4), HL = (HW + 63) / 64;
+  static_assert(sizeof(SnfHeader) % 4 == 0, "copied by words");
+  unsigned hw[HL];
+  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
+  if (wid == SWAVE) {
+    // header and sums ahead of any operand: loads return in order
+    const unsigned* gh = (const unsigned*)hd;
+#pragma unroll
+    for (int i = 0; i < HL; ++i) hw[i] = i * 64 + lane < HW ? gh[i * 64 + lane] : 0u;
+    const int count = step ? tiles : kDirectF0Blocks;
+    const double* ps = g.partials + (size_t)((step + 1) & 1) * kDirectSlots * 4;
+#pragma unroll
+    for (int i = 0; i < kDirectThreads / 64; ++i) {
+      const int q = i * 64 + lane;
+      if (q < count) {
+        e2 += ps[q * 4 + 0];
+        t1 += ps[q * 4 + 1];
+        t2 += ps[q * 4 + 2];
+      }
+    }
+  }
+  auto schedule = [&]() {
+#pragma unroll
+    for (int i = 0; i < HL; ++i)
+      if (i * 64 + lane < HW) ((unsigned*)&hs)[i * 64 + lane] = hw[i];
+    e2 = wave_sum_rows(e2);
+    t1 = wave_sum_rows(t1);
+    t2 = wave_sum_rows(t2);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // (FP64 instructions share the matrix cores' units with the other waves' products)
+    __builtin_amdgcn_s_setprio(3);
+    if (lane == 0) {
+      schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0);
+      if (hs.stop) *(volatile int*)&stopped = 1;
+    }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (blockIdx.x == 0) {
+      unsigned* gn = (unsigned*)(g.hdr + ((step + 1) & 1));
+#pragma unroll
+      for (int i = 0; i < HL; ++i)
+        if (i * 64 + lane < HW) gn[i * 64 + lane] = ((const unsigned*)&hs)[i * 64 + lane];
+      if (lane == 0 && g.progress)
+        __hip_atomic_store(g.progress, hs.stop ? -1 : step + 1, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  };
 
   // the wave's k-steps (4 values of k each); rows n .. ld - 1 of the buffers are zero
   const int KT = (int)((g.n + 3) / 4);
   const int kb = kq * KT / 4, ke = (kq + 1) * KT / 4;
-  DirectOperand<TB, PD> A;
-  DirectOperand<QB, PD> B;
-  const double *Ap, *Bp;
-  auto load = [&](int ks, int slot) {
-    const int64_t off = (int64_t)(4 * min(ks, max(ke - 1, kb)) + fk) * ld;
-    A.load(Ap + off + i0, slot);
-    B.load(Bp + off + j0 + cg * 16 * QB, slot);
-  };
-  auto load_first = [&](int ia, int ib) {
-    Ap = pick_buf(g.bufs, ia);
-    Bp = pick_buf(g.bufs, ib);
-#pragma unroll
-    for (int u = 0; u < PD; ++u) load(kb + u, u);
-  };
-  load_first(pa, pb);
-  __builtin_amdgcn_sched_barrier(0);
-
-  // the schedule of the step before (step 0: the first decision)
-  if (tid < HW) ((unsigned*)&hs)[tid] = h0;
-  if (tid + NT < HW) ((unsigned*)&hs)[tid + NT] = h1;
-  block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
-  if (tid == 0 && !hs.stop)
-    schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0);
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    unsigned* gn = (unsigned*)(g.hdr + ((step + 1) & 1));
-    if (tid < HW) gn[tid] = ((const unsigned*)&hs)[tid];
-    if (tid + NT < HW) gn[tid + NT] = ((const unsigned*)&hs)[tid + NT];
-    if (tid == 0 && g.progress)
-      __hip_atomic_store(g.progress, hs.stop ? -1 : step + 1, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  if (hs.stop) return;
-  const int ia = __builtin_amdgcn_readfirstlane(hs.ia), ib = __builtin_amdgcn_readfirstlane(hs.ib);
-  if (ia != pa || ib != pb) load_first(ia, ib);
-
   dbl4 acc[TB][QB];
 #pragma unroll
   for (int m = 0; m < TB; ++m)
 #pragma unroll
     for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  DirectOperand<TB, PD> A;
+  DirectOperand<QB, PD> B;
+  auto load = [&](const double* Ap, const double* Bp, int ks, int slot) {
+    const int64_t off = (int64_t)(4 * min(ks, max(ke - 1, kb)) + fk) * ld;
+    A.load(Ap + off + i0, slot);
+    B.load(Bp + off + j0 + cg * 16 * QB, slot);
+  };
   auto compute = [&](int slot) {
 #pragma unroll
     for (int m = 0; m < TB; ++m)
@@ -1403,26 +1483,72 @@ __global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectA
         acc[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.get(slot, m), B.get(slot, q), acc[m][q],
                                                          0, 0, 0);
   };
-  int ks = kb;
-  for (; ks + PD <= ke; ks += PD) {
-    // (past the end the last k-step again, never used: the number of loads in flight is the
-    // same on every path, so a wait leaves the newer ones in flight)
+  // the linear term's values of a band of 32 rows; the first band's ahead of the product where
+  // the registers allow it
+  constexpr bool XA = TB <= 4;
+  constexpr int W2 = T / 2, NE = 32 * W2 / NT;           // column pairs per row, per thread
+  double2 xs[NE];
+  auto load_x = [&](const double* X, int p) {
 #pragma unroll
-    for (int u = 0; u < PD; ++u) {
-      compute(u);
-      load(ks + u + PD, u);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int e = 0; e < NE; ++e) {
+      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
+      if (worker && r < (p < P ? 32 : 16))
+        xs[e] = *(const double2*)(X + (i0 + 32 * p + r) * ld + j0 + c);
+    }
+  };
+  if (worker) {
+    const double *Ap = pick_buf(g.bufs, pa), *Bp = pick_buf(g.bufs, pb);
+#pragma unroll
+    for (int u = 0; u < PD; ++u) load(Ap, Bp, kb + u, u);
+    if (XA) load_x(pick_buf(g.bufs, px), 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!SW && wid == SWAVE) schedule();
+    if constexpr (!EARLY) {
+      __syncthreads();
+      if (hs.stop) return;
+    }
+    int ks = kb;
+    for (; ks + PD <= ke; ks += PD) {
+      if (EARLY && *(volatile int*)&stopped) break;
+      // (past the end the last k-step again, never used: the number of loads in flight is the
+      // same on every path, so a wait leaves the newer ones in flight)
+#pragma unroll
+      for (int u = 0; u < PD; ++u) {
+        compute(u);
+        load(Ap, Bp, ks + u + PD, u);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PD; ++u)
+      if (ks + u < ke) compute(u);
+  } else {
+    schedule();
+  }
+  __syncthreads();
+  if (hs.stop) return;
+  const int ia = __builtin_amdgcn_readfirstlane(hs.ia), ib = __builtin_amdgcn_readfirstlane(hs.ib);
+  if (worker && (ia != pa || ib != pb)) {
+    // not the operands the host expected: again, at leisure
+    const double *Ap = pick_buf(g.bufs, ia), *Bp = pick_buf(g.bufs, ib);
+#pragma unroll
+    for (int m = 0; m < TB; ++m)
+#pragma unroll
+      for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int ks = kb; ks < ke; ++ks) {
+      load(Ap, Bp, ks, 0);
+      compute(0);
     }
   }
-#pragma unroll
-  for (int u = 0; u < PD; ++u)
-    if (ks + u < ke) compute(u);
 
   // Bands of 32 rows (one pair of block rows; the last 16 rows for odd TB): add the four
   // partial tiles in wave order, combine, store the rows, then the mirror from LDS so that its
   // stores are contiguous too.
   const int n = (int)g.n;
-  const double* X = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.ix));
+  const int ix = __builtin_amdgcn_readfirstlane(hs.ix);
+  const double* X = pick_buf(g.bufs, ix);
+  if (!XA || ix != px) load_x(X, 0);
   double* Y = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io));
   const int dual = __builtin_amdgcn_readfirstlane(hs.dual);
   double* Y2 = dual ? pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io2)) : nullptr;
@@ -1431,33 +1557,27 @@ __global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectA
   e2 = t1 = t2 = 0.0;
 #pragma unroll
   for (int p = 0; p < P + O; ++p) {
-    constexpr int W2 = T / 2;
     const int rows = p < P ? 32 : 16;
-    constexpr int NE = 32 * W2 / NT;        // column pairs per thread, full band
-    double2 xs[NE];
+    if (worker) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
-      if (r < rows) xs[e] = *(const double2*)(X + (i0 + 32 * p + r) * ld + j0 + c);
-    }
+      for (int mm = 0; mm < (p < P ? 2 : 1); ++mm) {
+        const int m = 2 * p + mm;
 #pragma unroll
-    for (int mm = 0; mm < (p < P ? 2 : 1); ++mm) {
-      const int m = 2 * p + mm;
+        for (int v = 0; v < 4; ++v) {
+          const int t = fk + 4 * v, r = p < P ? 2 * t + mm : t;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int t = fk + 4 * v, r = p < P ? 2 * t + mm : t;
-#pragma unroll
-        for (int q = 0; q < QP; ++q)
-          *(double2*)(&part[kq][r][cg * 16 * QB + 32 * q + 2 * fr]) =
-              double2{acc[m][2 * q][v], acc[m][2 * q + 1][v]};
-        if (QO) part[kq][r][cg * 16 * QB + 32 * QP + fr] = acc[m][QB - 1][v];
+          for (int q = 0; q < QP; ++q)
+            *(double2*)(&part[kq][r][cg * 16 * QB + 32 * q + 2 * fr]) =
+                double2{acc[m][2 * q][v], acc[m][2 * q + 1][v]};
+          if (QO) part[kq][r][cg * 16 * QB + 32 * QP + fr] = acc[m][QB - 1][v];
+        }
       }
     }
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
-      if (r >= rows) continue;
+      if (!worker || r >= rows) continue;
       const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
       double y[2], y2[2];
 #pragma unroll
@@ -1486,8 +1606,9 @@ __global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectA
       *(double2*)(&part[0][r][c]) = double2{y[0], y[1]};   // (this thread's own entries)
       if (Y2) *(double2*)(&part[1][r][c]) = double2{y2[0], y2[1]};
     }
+    if (p + 1 < P + O) load_x(X, p + 1);   // (a band ahead)
     __syncthreads();
-    for (int idx = tid; idx < rows * T; idx += NT) {
+    for (int idx = worker ? tid : rows * T; idx < rows * T; idx += NT) {
       const int r = idx % rows, c = idx / rows;
       const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
       if (diag && gr >= gc) continue;
@@ -1496,13 +1617,20 @@ __global__ __launch_bounds__(kDirectThreads* NC) void direct_step_kernel(DirectA
     }
     if (p + 1 < P + O) __syncthreads();
   }
+  e2 = wave_sum_rows(e2);
+  t1 = wave_sum_rows(t1);
+  t2 = wave_sum_rows(t2);
+  if (lane == 0) {
+    red[wid * 3 + 0] = e2;
+    red[wid * 3 + 1] = t1;
+    red[wid * 3 + 2] = t2;
+  }
   __syncthreads();
-  block_sum3(e2, t1, t2, red);
-  if (tid == 0) {
-    double* po = g.partials + ((size_t)(step & 1) * kDirectSlots + tile) * 4;
-    po[0] = e2;
-    po[1] = t1;
-    po[2] = t2;
+  if (tid < 3) {                           // (waves in order)
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum += red[w * 3 + tid];
+    g.partials[((size_t)(step & 1) * kDirectSlots + tile) * 4 + tid] = sum;
   }
 }
 
@@ -1575,17 +1703,19 @@ void launch_direct_f0(const DirectArgs& a, const SnfHeader& h, const double* F, 
   hipLaunchKernelGGL(direct_f0_kernel, dim3(kDirectF0Blocks), dim3(256), 0, s, a, h, F, ldf);
 }
 
-void launch_direct_step(int tile, const DirectArgs& a, int step, int pa, int pb, hipStream_t s) {
+void launch_direct_step(int tile, const DirectArgs& a, int step, const int (&op)[3],
+                        hipStream_t s) {
   const dim3 grid(a.nt * (a.nt + 1) / 2);
-#define SNF_DIRECT(TB, NC, PD)                                                                \
-  hipLaunchKernelGGL((direct_step_kernel<TB, NC, PD>), grid, dim3(kDirectThreads * NC), 0, s, \
-                     a, step, pa, pb)
+#define SNF_DIRECT(TB, NC, PD, SW)                                                          \
+  hipLaunchKernelGGL((direct_step_kernel<TB, NC, PD, SW>), grid,                            \
+                     dim3(kDirectThreads * NC + (SW ? 64 : 0)), 0, s, a, step, op[0],  \
+                     op[1], op[2])
   switch (tile) {
-    case 32: SNF_DIRECT(2, 1, 16); break;
-    case 48: SNF_DIRECT(3, 1, 12); break;
-    case 64: SNF_DIRECT(4, 2, 8); break;
-    case 80: SNF_DIRECT(5, 1, 5); break;
-    default: SNF_DIRECT(6, 2, 4); break;
+    case 32: SNF_DIRECT(2, 1, 8, true); break;
+    case 48: SNF_DIRECT(3, 1, 10, true); break;
+    case 64: SNF_DIRECT(4, 2, 7, false); break;
+    case 80: SNF_DIRECT(5, 1, 6, false); break;
+    default: SNF_DIRECT(6, 2, 4, false); break;
   }
 #undef SNF_DIRECT
 }
@@ -1597,27 +1727,28 @@ void launch_direct_out(const DirectArgs& a, int slot, double* D, int64_t ldd, Sn
 }
 
 // The buffer sequence of decide(), pmm_next() and pij_next().
-void StepOperands::next(int* pa, int* pb) {
-  const bool chain = scheme_pmm_m(scheme) || scheme_is_pij(scheme);
+void StepOperands::next(int (&op)[3]) {
+  const bool pij = scheme_is_pij(scheme), chain = scheme_pmm_m(scheme) || pij;
   const int bw = (cur + 1) & 3, ta = (cur + 2) & 3, tb = (cur + 3) & 3;
-  if (k == 0) {
-    *pa = *pb = cur;
+  auto set = [&](int a, int b, int x) {
+    op[0] = a;
+    op[1] = b;
+    op[2] = x;
+  };
+  if (k == 0) {                            // X.X
+    set(cur, cur, cur);
     bt = ta;
   } else if (!chain) {                     // S2.X
-    *pa = 2;
-    *pb = cur;
+    set(2, cur, 2);
   } else if (k == per_it - 1) {            // X.T
-    *pa = cur;
-    *pb = bt;
-  } else if (scheme_is_pij(scheme)) {      // T <- T.W
-    *pa = bt;
-    *pb = bw;
+    set(cur, bt, bt);
+  } else if (pij) {                        // T <- T.W
+    set(bt, bw, cur);
     bt = bt == ta ? tb : ta;
   } else if (k == 1) {                     // T from W.W
-    *pa = *pb = bw;
+    set(bw, bw, bw);
   } else {                                 // T <- W.T
-    *pa = bw;
-    *pb = bt;
+    set(bw, bt, bt);
     bt = bt == ta ? tb : ta;
   }
   if (++k == per_it) {
@@ -1672,9 +1803,9 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
     return xbuf + (size_t)(NB == 1 ? 0 : NB == 2 ? (i == 2 ? 1 : 0) : i) * np * np;
   };
   auto sum3 = [&](double& a, double& b, double& c) {     // valid in thread 0
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
+    a = wave_sum_rows(a);
+    b = wave_sum_rows(b);
+    c = wave_sum_rows(c);
     if (lane == 0) {
       red[wid * 3 + 0] = a;
       red[wid * 3 + 1] = b;

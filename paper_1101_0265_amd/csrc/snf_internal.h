@@ -51,10 +51,8 @@ inline int products_per_iteration(int scheme, int pi = 0, int pj = 0) {
   return (scheme == SNF_MCWEENY || scheme == SNF_SNF_FIXMU) ? 2 : 1;
 }
 
-// Scalar state of one purification.  Written by the host once (configuration), then only by the
-// schedule (one thread).
-struct SnfHeader {
-  // ---- configuration ----
+// Scalar state of one purification: configuration, written by the host once, ...
+struct SnfConfig {
   int32_t scheme;
   int32_t max_iter;
   int32_t mode;          // snf_precision
@@ -63,7 +61,10 @@ struct SnfHeader {
   int64_t n_occ;
   double tol, lambda_min, lambda_max, mu, xi, homo, lumo;
   double gap_switch, lowp_floor;
-  // ---- evolving ----
+};
+// ... what evolves, written only by the schedule (one thread, which works on a copy in
+// registers), ...
+struct SnfScalars {
   double beta, betabar, gamma;
   double t1, t2;          // tr X_cur, ||X_cur||_F^2
   double alpha;           // alpha of the pending iteration
@@ -86,9 +87,6 @@ struct SnfHeader {
   int32_t pij_i, pij_j;   // P_{i,j} schemes: the polynomial, else 0
   double xstar;           // fixed-mu schemes: image of mu in X_0 (1/2, or x* of P_{i,j})
   double abar;            // P_{i,j}: distance of the occupied part's lower bound from 1
-  double pq[sched::kPijQ];  // P_{i,j}: P(x* + v) = x* + v sum_k pq[k] v^k
-  double pbin[2][sched::kPijMax + 1];   // C(i+k, k) (k <= j) and C(j+k, k) (k <= i)
-  double pr[sched::kPmmMaxM + 1];       // P_{m,m}: r_0 .. r_m
   int32_t dual;           // pending product also writes Y2 = d2 P + d1 X + d0 I to x[io2]
   int32_t io2;
   double d2, d1, d0;
@@ -96,6 +94,13 @@ struct SnfHeader {
   int32_t write_lowp;     // epilogue also writes the low-precision operand copy
   int32_t nlog;
 };
+// ... and the polynomials' tables, written once at set-up and indexed at run time.
+struct SnfTables {
+  double pq[sched::kPijQ];  // P_{i,j}: P(x* + v) = x* + v sum_k pq[k] v^k
+  double pbin[2][sched::kPijMax + 1];   // C(i+k, k) (k <= j) and C(j+k, k) (k <= i)
+  double pr[sched::kPmmMaxM + 1];       // P_{m,m}: r_0 .. r_m
+};
+struct SnfHeader : SnfConfig, SnfScalars, SnfTables {};
 // ... with the per-iteration log behind it.
 struct SnfState : SnfHeader {
   snf_log_rec log[SNF_LOG_MAX];
@@ -162,17 +167,18 @@ struct DirectArgs {
 void launch_direct_f0(const DirectArgs& a, const SnfHeader& h, const double* F, int64_t ldf,
                       hipStream_t s);
 // Step `step` of the solve: advance the state by the previous step's sums (step 0: f_0's), then,
-// unless that stopped it, the pending product.  pa, pb: the operand buffers the state will
-// name, as far as the host knows (another pair is slower, not wrong).
-void launch_direct_step(int tile, const DirectArgs& a, int step, int pa, int pb, hipStream_t s);
+// unless that stopped it, the pending product.  op: the operand and linear-term buffers the state
+// will name, as far as the host knows (others are slower, not wrong).
+void launch_direct_step(int tile, const DirectArgs& a, int step, const int (&op)[3],
+                        hipStream_t s);
 // D and the final state (header of slot `slot`, log) out.
 void launch_direct_out(const DirectArgs& a, int slot, double* D, int64_t ldd, SnfState* out,
                        hipStream_t s);
-// Operand buffers of the product of each step of a scheme, from step 0 on.
+// Operand and linear-term buffers of the product of each step of a scheme, from step 0 on.
 struct StepOperands {
   int scheme, per_it, k = 0, cur = 0, bt = 0;
   explicit StepOperands(int scheme_, int per_it_) : scheme(scheme_), per_it(per_it_) {}
-  void next(int* pa, int* pb);
+  void next(int (&op)[3]);
 };
 
 // The whole FP64 solve in one workgroup, iterates in LDS: the iterate buffers one scheme needs
