@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 
+#include <type_traits>
+
 #include "schedule_math.h"
 #include "snf_internal.h"
 
@@ -1308,14 +1310,16 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg, const d
 //    accumulators, so nothing is shared until the end: no LDS staging and no barrier in the main
 //    loop, operands go from L2 straight to registers, PD k-steps ahead;
 //  * the four partial tiles are added in LDS in wave order, a band of 32 rows at a time;
-//  * the schedule of step s runs at the head of step s + 1, in every workgroup for itself, while
-//    the first operands are on their way.
+//  * the schedule of step s runs at the head of step s + 1, in every workgroup for itself, beside
+//    the product: the host knows which buffers a step reads.
 // The bound is the matrix cores (FP64: 64 cycles an instruction and SIMD) plus, per step, about
-// 8 us of launch boundary, cold operand loads and schedule.
+// 6 us of launch boundary, cold operand loads and epilogue.
 // A scale-and-fold solve of 19 products (wall time), this against the engine's three kernels (n
 // > 896), 32x32 tiles and a schedule kernel (256 < n <= 896), those in one cooperative launch
-// with grid barriers (n <= 256): n = 256 0.36 / 0.44 ms, 512 0.44 / 0.59, 704 0.50 / 0.89, 1000
-// 0.82 / 1.12, 1400 1.38 / 1.97, 2000 3.2 / 4.2, 2112 3.3 / 4.5.
+// with grid barriers (n <= 256): n = 256 0.27 / 0.44 ms, 400 0.33 / 0.58, 704 0.47 / 0.89, 1056
+// 0.79 / 1.31, 1408 1.32 / 1.97, 1760 2.1 / 3.1, 2112 3.2 / 4.5.  A step at n = 256 takes 8 us: 1.7
+// until the operands are there (the schedule, 2.5 us from its sums on, beside the 3 us of
+// products), 2 the epilogue, 2 to the next launch's first instruction.
 // ---------------------------------------------------------------------------------------
 constexpr int kDirectThreads = 256;
 
@@ -1759,13 +1763,14 @@ void StepOperands::next(int (&op)[3]) {
 
 // ---------------------------------------------------------------------------------------
 // The smallest orders: the whole solve in one workgroup, the iterates in LDS (160 KB: two
-// buffers up to order 96, four up to 64).  A step of such a solve is bound by
+// buffers up to order 80, four up to 64).  A step of such a solve is bound by
 // latency, so nothing leaves the compute unit between steps: no launch, no grid barrier, no
 // memory.  Eight waves share the 16x16 blocks of the upper triangle; a step's results stay in
 // registers until the sums are known, so X needs no second buffer and is still whole when the
-// stop test passes.  The same 19 products at n = 17 / 64 / 96: 0.13 / 0.19 / 0.30 ms, against
-// 0.38 ms in a cooperative launch of 32x32 tiles.  Beyond order 96 one unit's matrix cores are
-// too few (n = 128: 0.47 ms, the direct steps 0.33).
+// stop test passes.  A step at n = 64 takes 4.9 us: 2.6 the products, 0.4 the sums, 1.4 the
+// schedule, 0.4 the writes.  The 19 products of the solves above at n = 17 / 40 / 64 / 80: 0.10 /
+// 0.12 / 0.14 / 0.17 ms, against 0.38 ms in a cooperative launch of 32x32 tiles.  At order 96 the
+// direct steps take as long (0.23 against 0.22 ms, 31 products 0.30 against 0.32).
 // ---------------------------------------------------------------------------------------
 constexpr int kWgThreads = 512, kWgWaves = kWgThreads / 64;
 
@@ -1775,7 +1780,7 @@ static int wg_buffers(int scheme) {
 }
 
 size_t solve_wg_bytes(int64_t n, int scheme) {
-  if (n > 96) return 0;
+  if (n > 80) return 0;
   const int64_t np = (n + 15) / 16 * 16;
   const size_t bytes = (size_t)wg_buffers(scheme) * np * np * sizeof(double);
   return bytes <= (size_t)144 << 10 ? bytes : 0;
@@ -1795,10 +1800,12 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
   const int n = (int)h.n, np = (n + 15) / 16 * 16;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int fr = lane & 15, fk = lane >> 4;
-  // columns of odd rows are swapped 16 by 16 where rows are a multiple of 256 B apart: two rows
-  // of 16 values then cover the banks once
+  // The columns of row r are permuted within each 16 by r mod 16 (a mirrored write of 16 rows of
+  // one column then touches every bank once, as 16 columns of one row do), and odd rows swap 16
+  // by 16 where rows are a multiple of 256 B apart (two rows of 16 values then cover the banks
+  // once).  Unpermuted, the writes took 1.1 us a step at order 64 and 2.3 at 96.
   const int sw = np % 32 ? 0 : 16;
-  auto at = [&](int r, int c) { return r * np + (c ^ ((r & 1) ? sw : 0)); };
+  auto at = [&](int r, int c) { return r * np + (c ^ ((r & 15) | ((r & 1) ? sw : 0))); };
   auto buf = [&](int i) {
     return xbuf + (size_t)(NB == 1 ? 0 : NB == 2 ? (i == 2 ? 1 : 0) : i) * np * np;
   };
@@ -1856,6 +1863,7 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
     br[i] = __builtin_amdgcn_readfirstlane(r);
     bc[i] = __builtin_amdgcn_readfirstlane(r + rem);
   }
+  const int mine = __builtin_amdgcn_readfirstlane((cnt - wid + kWgWaves - 1) / kWgWaves);
   for (int step = 0; step < max_steps && !hs.stop; ++step) {
     const double *A = buf(hs.ia), *B = buf(hs.ib), *L = buf(hs.ix);
     double *Y = buf(hs.io), *Y2 = buf(hs.io2);
@@ -1863,17 +1871,33 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
     const double c2 = hs.c2, c1 = hs.c1, c0 = hs.c0, d2 = hs.d2, d1 = hs.d1, d0 = hs.d0;
     double y[MB][4], y2[MB][4];
     e2 = t1 = t2 = 0.0;
+    // the wave's blocks side by side, four k-steps of operands at a time
+    auto product = [&](auto countc) {
+      constexpr int C = decltype(countc)::value;
+      dbl4 acc[C];
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      if (wid + i * kWgWaves < cnt) {
-        dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
-        for (int k = 0; k < np; k += 4)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[at(k + fk, br[i] * 16 + fr)],
-                                                     B[at(k + fk, bc[i] * 16 + fr)], acc, 0, 0, 0);
+      for (int i = 0; i < C; ++i) acc[i] = dbl4{0.0, 0.0, 0.0, 0.0};
+      for (int k = 0; k < np; k += 16) {
+        double av[C][4], bv[C][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < C; ++i) {
+            av[i][u] = A[at(k + 4 * u + fk, br[i] * 16 + fr)];
+            bv[i][u] = B[at(k + 4 * u + fk, bc[i] * 16 + fr)];
+          }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < C; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][u], bv[i][u], acc[i], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < C; ++i)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int r = br[i] * 16 + fk + 4 * v, c = bc[i] * 16 + fr;
-          const double p = acc[v], x = L[at(r, c)];
+          const double p = acc[i][v], x = L[at(r, c)];
           const bool on = r == c, in = r < n && c < n;
           y[i][v] = in ? c2 * p + c1 * x + (on ? c0 : 0.0) : 0.0;
           if (NB == 4) y2[i][v] = in ? d2 * p + d1 * x + (on ? d0 : 0.0) : 0.0;
@@ -1884,8 +1908,10 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
             if (on) t1 += y[i][v];
           }
         }
-      }
-    }
+    };
+    if (MB >= 3 && mine >= 3) product(std::integral_constant<int, MB >= 3 ? 3 : 1>());
+    else if (mine == 2) product(std::integral_constant<int, 2>());
+    else if (mine == 1) product(std::integral_constant<int, 1>());
     sum3(e2, t1, t2);                      // (its barrier: every read of the operands is done)
     if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 0);
 #pragma unroll
