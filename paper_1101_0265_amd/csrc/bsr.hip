@@ -90,39 +90,65 @@ __global__ __launch_bounds__(64) void bsr_bitmap_kernel(const int32_t* __restric
 
 // ---- 2. symbolic ------------------------------------------------------------------------
 // Pattern of A.B (both symmetric patterns): row I is the OR of the bitmaps of B's block rows
-// K over the blocks (I, K) of A.
-__global__ __launch_bounds__(64) void bsr_symbolic_kernel(const int32_t* __restrict__ row_ptrA,
-                                                          const int32_t* __restrict__ colA,
-                                                          const int32_t* __restrict__ row_ptrB,
-                                                          const uint32_t* __restrict__ bm, int W,
-                                                          const int32_t* __restrict__ pre,
-                                                          uint32_t* __restrict__ bmP,
-                                                          int32_t* __restrict__ preP,
-                                                          int32_t* __restrict__ cntP,
-                                                          int64_t* __restrict__ triples) {
+// K over the blocks (I, K) of A.  256 threads share the (block, word) pairs of a row, so the
+// chain of dependent loads (column, then that row's word) is as long as a row has pairs / 256:
+// with one wave, lane = word and the blocks in turn, a row waited for every block in turn (30 us
+// at n = 4096, 106 us at 65536).
+__global__ __launch_bounds__(256) void bsr_symbolic_kernel(const int32_t* __restrict__ row_ptrA,
+                                                           const int32_t* __restrict__ colA,
+                                                           const int32_t* __restrict__ row_ptrB,
+                                                           const uint32_t* __restrict__ bm, int W,
+                                                           const int32_t* __restrict__ pre,
+                                                           uint32_t* __restrict__ bmP,
+                                                           int32_t* __restrict__ preP,
+                                                           int32_t* __restrict__ cntP,
+                                                           int64_t* __restrict__ triples) {
   extern __shared__ uint32_t acc[];
-  const int I = blockIdx.x;
-  for (int w = threadIdx.x; w < W; w += blockDim.x) acc[w] = 0u;
-  int64_t tri = 0;   // block triples (I, K, J), J >= I: the useful work of row I
-  for (int p = row_ptrA[I]; p < row_ptrA[I + 1]; ++p) {
-    const int K = colA[p];
-    for (int w = threadIdx.x; w < W; w += blockDim.x) acc[w] |= bm[(size_t)K * W + w];
-    if (threadIdx.x == 0) {
-      const uint32_t word = bm[(size_t)K * W + (I >> 5)];
-      const int below = pre[(size_t)K * W + (I >> 5)] + __popc(word & ((1u << (I & 31)) - 1u));
-      tri += (row_ptrB[K + 1] - row_ptrB[K]) - below;
+  __shared__ unsigned long long tri;       // block triples (I, K, J), J >= I: the useful work
+  const int I = blockIdx.x, tid = threadIdx.x;
+  for (int w = tid; w < W; w += 256) acc[w] = 0u;
+  if (tid == 0) tri = 0ull;
+  __syncthreads();
+  const int p0 = row_ptrA[I], p1 = row_ptrA[I + 1];
+  if (W <= 256) {
+    // thread = (block of the turn, word): the same word every turn
+    const int per = 256 / W, w = tid % W, q = tid / W;
+    uint32_t o = 0u;
+    if (q < per)
+      for (int p = p0 + q; p < p1; p += per) o |= bm[(size_t)colA[p] * W + w];
+    if (o) atomicOr(&acc[w], o);
+  } else {
+    for (int w = tid; w < W; w += 256) {
+      uint32_t o = 0u;
+      for (int p = p0; p < p1; ++p) o |= bm[(size_t)colA[p] * W + w];
+      acc[w] = o;
     }
   }
-  if (threadIdx.x == 0) triples[I] = tri;
+  unsigned long long mine = 0ull;
+  for (int p = p0 + tid; p < p1; p += 256) {
+    const int K = colA[p];
+    const uint32_t word = bm[(size_t)K * W + (I >> 5)];
+    const int below = pre[(size_t)K * W + (I >> 5)] + __popc(word & ((1u << (I & 31)) - 1u));
+    mine += (unsigned long long)((row_ptrB[K + 1] - row_ptrB[K]) - below);
+  }
+  if (mine) atomicAdd(&tri, mine);
   __syncthreads();
-  for (int w = threadIdx.x; w < W; w += blockDim.x) bmP[(size_t)I * W + w] = acc[w];
-  if (threadIdx.x == 0) {
-    int s = 0;
-    for (int w = 0; w < W; ++w) {
-      preP[(size_t)I * W + w] = s;
-      s += __popc(acc[w]);
+  if (tid == 0) triples[I] = (int64_t)tri;
+  for (int w = tid; w < W; w += 256) bmP[(size_t)I * W + w] = acc[w];
+  if (tid < 64) {                          // prefix popcounts, 64 words at a time
+    int base = 0;
+    for (int w0 = 0; w0 < W; w0 += 64) {
+      const int c = w0 + tid < W ? __popc(acc[w0 + tid]) : 0;
+      int incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (tid >= o) incl += v;
+      }
+      if (w0 + tid < W) preP[(size_t)I * W + w0 + tid] = base + incl - c;
+      base += __shfl(incl, 63, 64);
     }
-    cntP[I] = s;
+    if (tid == 0) cntP[I] = base;
   }
 }
 
@@ -423,6 +449,7 @@ __global__ __launch_bounds__(512, 4) void bsr_product_kernel(const SnfState* __r
 #pragma unroll
       for (int a = 0; a < kSup; ++a)
         if ((ba >> a) & 1u) m |= bb << (4 * a);
+      if (TI == TJ) m &= 0x8CEFu;          // (a diagonal tile's lower blocks are mirrors)
       if (g.screen2 > 0.0 && m) {
         double na[kSup], nbv[kSup];
 #pragma unroll
@@ -575,8 +602,8 @@ __global__ __launch_bounds__(512, 4) void bsr_product_kernel(const SnfState* __r
 }
 
 // ---- 5. truncation ----------------------------------------------------------------------
-// One workgroup per block row; thread 0 walks the row in order (ranks and the FP64 sum of
-// kept squared norms in a fixed order).
+// One wave per block row, 64 blocks a turn: ranks by ballot, the FP64 sum of the kept squared
+// norms by lane and then across the lanes (fixed order).
 __global__ __launch_bounds__(64) void bsr_truncate_kernel(const int32_t* __restrict__ row_ptrP,
                                                           const int32_t* __restrict__ colP,
                                                           const double* __restrict__ normP,
@@ -584,23 +611,54 @@ __global__ __launch_bounds__(64) void bsr_truncate_kernel(const int32_t* __restr
                                                           int32_t* __restrict__ cnt,
                                                           double* __restrict__ partials,
                                                           int slot0) {
-  const int I = blockIdx.x;
-  if (threadIdx.x != 0) return;
+  const int I = blockIdx.x, lane = threadIdx.x;
+  const int p1 = row_ptrP[I + 1];
   int k = 0;
   double t2 = 0.0;
-  for (int p = row_ptrP[I]; p < row_ptrP[I + 1]; ++p) {
-    const bool keep = (colP[p] == I) || (normP[p] >= tau2);
-    rank[p] = keep ? k : -1;
-    if (keep) {
-      ++k;
-      t2 += normP[p];
-    }
+  for (int p0 = row_ptrP[I]; p0 < p1; p0 += 64) {
+    const int p = p0 + lane;
+    const double s = p < p1 ? normP[p] : 0.0;
+    const bool keep = p < p1 && ((colP[p] == I) || (s >= tau2));
+    const unsigned long long kept = __ballot(keep);
+    if (p < p1) rank[p] = keep ? k + __popcll(kept & ((1ull << lane) - 1ull)) : -1;
+    if (keep) t2 += s;
+    k += __popcll(kept);
   }
+  t2 = bsr_wave_sum(t2);
+  if (lane != 0) return;
   cnt[I] = k;
   partials[(slot0 + I) * 4 + 0] = 0.0;
   partials[(slot0 + I) * 4 + 1] = 0.0;
   partials[(slot0 + I) * 4 + 2] = t2;
   partials[(slot0 + I) * 4 + 3] = 0.0;
+}
+
+// Partial sums of many slots to kSumSlots of them (fixed order): the schedule's one workgroup
+// would walk the 60000 slots of n = 65536 in 175 us.
+constexpr int kSumSlots = 128;
+__global__ __launch_bounds__(256) void bsr_sum_slots_kernel(const double* __restrict__ partials,
+                                                            int count, double* __restrict__ out) {
+  __shared__ double red[12];
+  const int per = (count + kSumSlots - 1) / kSumSlots;
+  const int i0 = blockIdx.x * per, i1 = min(count, i0 + per);
+  double v[3] = {0.0, 0.0, 0.0};
+  for (int i = i0 + (int)threadIdx.x; i < i1; i += 256) {
+    v[0] += partials[i * 4 + 0];
+    v[1] += partials[i * 4 + 1];
+    v[2] += partials[i * 4 + 2];
+  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    v[k] = bsr_wave_sum(v[k]);
+    if (lane == 0) red[wid * 3 + k] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 4)
+    out[blockIdx.x * 4 + threadIdx.x] =
+        threadIdx.x < 3 ? ((red[threadIdx.x] + red[3 + threadIdx.x]) + red[6 + threadIdx.x]) +
+                              red[9 + threadIdx.x]
+                        : 0.0;
 }
 
 // ---- 5a. error-controlled truncation: histogram of block norms ------------------------
@@ -664,19 +722,26 @@ static double error_control_tau2(const uint32_t* counts, double eps_i) {
 }
 
 // ---- 6. compaction ----------------------------------------------------------------------
+// Workgroups (I, y) share row I's blocks, every gridDim.y-th each.  nrmN (optional) takes the kept
+// blocks' squared norms along, for the next product's screening.
 __global__ __launch_bounds__(256) void bsr_compact_kernel(const int32_t* __restrict__ row_ptrP,
                                                           const int32_t* __restrict__ colP,
                                                           const float* __restrict__ valP,
                                                           const int32_t* __restrict__ rank,
                                                           const int32_t* __restrict__ row_ptrN,
                                                           int32_t* __restrict__ colN,
-                                                          float* __restrict__ valN) {
+                                                          float* __restrict__ valN,
+                                                          const double* __restrict__ normP,
+                                                          double* __restrict__ nrmN) {
   const int I = blockIdx.x;
-  for (int p = row_ptrP[I]; p < row_ptrP[I + 1]; ++p) {
+  for (int p = row_ptrP[I] + (int)blockIdx.y; p < row_ptrP[I + 1]; p += gridDim.y) {
     const int k = rank[p];
     if (k < 0) continue;
     const int dst = row_ptrN[I] + k;
-    if (threadIdx.x == 0) colN[dst] = colP[p];
+    if (threadIdx.x == 0) {
+      colN[dst] = colP[p];
+      if (nrmN) nrmN[dst] = normP[p];
+    }
     const u32x4 v = *(const u32x4*)(valP + (size_t)p * kBB + threadIdx.x * 4);
     *(u32x4*)(valN + (size_t)dst * kBB + threadIdx.x * 4) = v;
   }
@@ -811,6 +876,8 @@ struct BsrBuf {                 // one BSR matrix owned by the library, with loo
   DevArr<float> val;
   DevArr<uint32_t> bm;
   DevArr<int32_t> pre;
+  DevArr<double> nrm;           // squared block norms (screening), valid while nrm_ok
+  bool nrm_ok = false;
   int64_t nnzb = 0;
   void release() {
     row_ptr.release();
@@ -818,6 +885,8 @@ struct BsrBuf {                 // one BSR matrix owned by the library, with loo
     val.release();
     bm.release();
     pre.release();
+    nrm.release();
+    nrm_ok = false;
     nnzb = 0;
   }
   BsrMat view() const { return BsrMat{row_ptr.p, bm.p, pre.p, val.p}; }
@@ -831,7 +900,7 @@ struct BsrWorkspace {
   // the schedule's buffer indices 0..3 (operands, linear term and output of each product)
   BsrBuf& buf(int i) { return i == 0 ? X[0] : i == 1 ? X[1] : i == 2 ? S : T; }
   DevArr<double> normP, partials, sums;
-  DevArr<double> nrmX, nrmY;    // norm screening: squared norms of the operands' blocks
+  DevArr<double> slot_sums;     // [kSumSlots][4]
   DevArr<int32_t> cnt, rank, tiles;
   DevArr<int64_t> triples;
   int64_t last_triples = 0;
@@ -874,8 +943,7 @@ void bsr_release_all_devices() {
     w->normP.release();
     w->partials.release();
     w->sums.release();
-    w->nrmX.release();
-    w->nrmY.release();
+    w->slot_sums.release();
     w->val2.release();
     w->cnt.release();
     w->rank.release();
@@ -953,27 +1021,50 @@ static int build_lookup(BsrBuf& b, int nb, int W, hipStream_t s) {
   return SNF_OK;
 }
 
-// exclusive scan of cnt (device, nb) into row_ptr (device, nb + 1) through pinned memory;
-// returns the total
-static int scan_counts(BsrWorkspace* w, const int32_t* cnt_dev, int nb, DevArr<int32_t>& row_ptr,
-                       int64_t* total, hipStream_t s) {
-  int rc = ensure_pinned(w, (size_t)(2 * nb + 2) * sizeof(int32_t));
-  if (rc) return rc;
-  int32_t* h = w->pinned;
-  BSR_HIP(hipMemcpyAsync(h, cnt_dev, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  BSR_HIP(hipStreamSynchronize(s));
-  int32_t* rp = h + nb + 1;
+// Pinned staging of one step (offsets in bytes from the workspace's pinned block): what the
+// device hands back and takes in one step, each in its own place, so that a copy in flight is
+// never overwritten.
+struct StepStage {
+  size_t cntP, rpP, cntN, rpN, tri, flags, tiles, total;
+  StepStage(int nb, int64_t nflags) {
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = o;
+      o += (bytes + 63) / 64 * 64;
+      return at;
+    };
+    tri = take((size_t)nb * 8);
+    cntP = take((size_t)nb * 4);
+    rpP = take((size_t)(nb + 1) * 4);
+    cntN = take((size_t)nb * 4);
+    rpN = take((size_t)(nb + 1) * 4);
+    flags = take((size_t)nflags);
+    tiles = take((size_t)nflags * 4);
+    total = o;
+  }
+};
+
+// Exclusive scan of the counts cnt[0, nb) into rp[0, nb]; the total, or -1 beyond 32 bits.
+static int64_t scan_counts(const int32_t* cnt, int32_t* rp, int nb) {
   int64_t acc = 0;
   for (int i = 0; i < nb; ++i) {
     rp[i] = (int32_t)acc;
-    acc += h[i];
+    acc += cnt[i];
   }
   rp[nb] = (int32_t)acc;
-  if (acc > INT32_MAX) return SNF_ENOMEM;
-  rc = row_ptr.reserve(nb + 1);
+  return acc > INT32_MAX ? -1 : acc;
+}
+
+// Squared block norms of a screened product's operand, unless the compaction that made it left
+// them.
+static int ensure_norms(BsrBuf& X, hipStream_t s) {
+  if (X.nrm_ok || X.nnzb == 0) return SNF_OK;
+  int rc = X.nrm.reserve(X.nnzb);
   if (rc) return rc;
-  BSR_HIP(hipMemcpyAsync(row_ptr.p, rp, (nb + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  *total = acc;
+  hipLaunchKernelGGL(bsr_block_norms_kernel, dim3((unsigned)((X.nnzb + 3) / 4)), dim3(256), 0, s,
+                     X.val.p, X.nnzb, X.nrm.p);
+  BSR_HIP(hipGetLastError());
+  X.nrm_ok = true;
   return SNF_OK;
 }
 
@@ -982,44 +1073,53 @@ static int scan_counts(BsrWorkspace* w, const int32_t* cnt_dev, int nb, DevArr<i
 // square has A = B = L = X; the other products of a fixed-mu iteration (Algorithm 1's S2.X,
 // the Horner levels and the last product of P_{m,m} and P_{i,j}) multiply polynomials in the
 // same matrix, so A.B is symmetric and so is its pattern.  N2 (optional) receives the second
-// output d2 A.B + d1 L + d0 I with the same kept blocks (P_{i,j}'s first product).  Partial sums
-// land in slots [0, tiles) (product) and [tiles, tiles + nb) (kept norms); *slots = total.
+// output d2 A.B + d1 L + d0 I with the same kept blocks (P_{i,j}'s first product).  The FP64 sums
+// (product tiles, then kept norms) end in sums->p, sums->count slots.  advance: the schedule
+// runs on them, the state comes back to the host with the kept counts (one wait for both), and
+// a product that stopped the loop is not compacted.
 // eps_i >= 0 selects the error-controlled rule (tau2 is then derived from the block-norm
 // histogram of this product); eps_i < 0 keeps the fixed threshold tau2.
+struct SlotSums {
+  const double* p;
+  int count;
+};
+
 static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N, int nb,
-                    int W, double tau2, int* slots, hipEvent_t ev_a, hipEvent_t ev_b,
-                    hipStream_t s, double eps_i = -1.0, double screen2 = 0.0,
+                    int W, double tau2, SlotSums* sums, bool advance, hipEvent_t ev_a,
+                    hipEvent_t ev_b, hipStream_t s, double eps_i = -1.0, double screen2 = 0.0,
                     BsrBuf* N2 = nullptr) {
   BsrBuf& P = w->P;
   int rc;
-  // 1b. operand block norms for the screening (B's own when it is another matrix)
-  if (screen2 > 0.0 && X.nnzb > 0) {
-    if ((rc = w->nrmX.reserve(X.nnzb))) return rc;
-    hipLaunchKernelGGL(bsr_block_norms_kernel, dim3((unsigned)((X.nnzb + 3) / 4)), dim3(256), 0,
-                       s, X.val.p, X.nnzb, w->nrmX.p);
-    BSR_HIP(hipGetLastError());
-  }
-  if (screen2 > 0.0 && &B != &X && B.nnzb > 0) {
-    if ((rc = w->nrmY.reserve(B.nnzb))) return rc;
-    hipLaunchKernelGGL(bsr_block_norms_kernel, dim3((unsigned)((B.nnzb + 3) / 4)), dim3(256), 0,
-                       s, B.val.p, B.nnzb, w->nrmY.p);
-    BSR_HIP(hipGetLastError());
-  }
-  // 2. symbolic
+  const bool screen = screen2 > 0.0;
+  // 1b. operand block norms for the screening
+  if (screen && ((rc = ensure_norms(X, s)) || (rc = ensure_norms(B, s)))) return rc;
+  // 2. symbolic, and 3. the super-tiles it leaves; one wait for what the host needs of both
+  const int NT = (nb + kSup - 1) / kSup;
+  const int64_t nflags = (int64_t)NT * NT;
+  const StepStage st(nb, nflags);
   if ((rc = P.bm.reserve((size_t)nb * W)) || (rc = P.pre.reserve((size_t)nb * W)) ||
-      (rc = w->cnt.reserve(nb)))
+      (rc = w->cnt.reserve(nb)) || (rc = w->triples.reserve(nb)) ||
+      (rc = w->flags.reserve((size_t)nflags)) || (rc = ensure_pinned(w, st.total)) ||
+      (rc = P.row_ptr.reserve(nb + 1)))
     return rc;
-  if ((rc = w->triples.reserve(nb))) return rc;
-  hipLaunchKernelGGL(bsr_symbolic_kernel, dim3(nb), dim3(64), W * sizeof(uint32_t), s,
+  char* pin = (char*)w->pinned;
+  hipLaunchKernelGGL(bsr_symbolic_kernel, dim3(nb), dim3(256), W * sizeof(uint32_t), s,
                      X.row_ptr.p, X.col.p, B.row_ptr.p, B.bm.p, W, B.pre.p, P.bm.p, P.pre.p,
                      w->cnt.p, w->triples.p);
+  hipLaunchKernelGGL(bsr_tile_flags_kernel, dim3((unsigned)((nflags + 255) / 256)), dim3(256), 0,
+                     s, P.bm.p, nb, W, NT, w->flags.p);
   BSR_HIP(hipGetLastError());
-  int64_t nnzP = 0;
-  if ((rc = scan_counts(w, w->cnt.p, nb, P.row_ptr, &nnzP, s))) return rc;
+  BSR_HIP(hipMemcpyAsync(pin + st.cntP, w->cnt.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  BSR_HIP(hipMemcpyAsync(pin + st.tri, w->triples.p, nb * sizeof(int64_t), hipMemcpyDeviceToHost,
+                         s));
+  BSR_HIP(hipMemcpyAsync(pin + st.flags, w->flags.p, nflags, hipMemcpyDeviceToHost, s));
+  BSR_HIP(hipStreamSynchronize(s));
+  int32_t* rpP = (int32_t*)(pin + st.rpP);
+  const int64_t nnzP = scan_counts((const int32_t*)(pin + st.cntP), rpP, nb);
+  if (nnzP < 0) return SNF_ENOMEM;
+  BSR_HIP(hipMemcpyAsync(P.row_ptr.p, rpP, (nb + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
   {
-    // useful block triples of this product (the symbolic kernel finished: scan synced)
-    std::vector<int64_t> tri(nb);
-    BSR_HIP(hipMemcpy(tri.data(), w->triples.p, nb * sizeof(int64_t), hipMemcpyDeviceToHost));
+    const int64_t* tri = (const int64_t*)(pin + st.tri);
     int64_t t = 0;
     for (int i = 0; i < nb; ++i) t += tri[i];
     w->last_triples = t;
@@ -1030,32 +1130,25 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   P.nnzb = nnzP;
   hipLaunchKernelGGL(bsr_fill_cols_kernel, dim3(nb), dim3(64), 0, s, P.bm.p, P.pre.p,
                      P.row_ptr.p, W, P.col.p);
-  // 3. super-tiles
-  const int NT = (nb + kSup - 1) / kSup;
-  if ((rc = w->flags.reserve((size_t)NT * NT))) return rc;
-  const int64_t nflags = (int64_t)NT * NT;
-  hipLaunchKernelGGL(bsr_tile_flags_kernel, dim3((unsigned)((nflags + 255) / 256)), dim3(256), 0,
-                     s, P.bm.p, nb, W, NT, w->flags.p);
-  BSR_HIP(hipGetLastError());
-  if ((rc = ensure_pinned(w, (size_t)nflags + (size_t)nflags * 4 + 128))) return rc;
-  uint8_t* hf = (uint8_t*)w->pinned;
-  BSR_HIP(hipMemcpyAsync(hf, w->flags.p, nflags, hipMemcpyDeviceToHost, s));
-  BSR_HIP(hipStreamSynchronize(s));
-  int32_t* tl = (int32_t*)(hf + ((nflags + 63) / 64) * 64);
+  const uint8_t* hf = (const uint8_t*)(pin + st.flags);
+  int32_t* tl = (int32_t*)(pin + st.tiles);
   int ntiles = 0;
   // super-tiles in squares of SQ x SQ (squares in row-major order of the upper triangle,
   // tiles row-major inside): the ~512 workgroups resident at once cover 8 bands of A rows and
   // 64 of B rows instead of one band and 512, and an XCD (workgroups go to the 8 XCDs in
-  // turn) takes one column of each square, whose 8 tiles stream the same B rows
+  // turn) takes one column of each square, whose 8 tiles stream the same B rows.  The tiles on
+  // the diagonal come last: they hold 10 block pairs a stage at most instead of 16, and are
+  // what is left over where the others just fill the chip (n = 4096: 496 others, 512 places).
   constexpr int SQ = 8;
   for (int sa = 0; sa < NT; sa += SQ)
     for (int sb = sa; sb < NT; sb += SQ)
       for (int ti = sa; ti < sa + SQ && ti < NT; ++ti)
         for (int tj = sb; tj < sb + SQ && tj < NT; ++tj)
-          if (hf[(int64_t)ti * NT + tj]) tl[ntiles++] = (int32_t)((ti << 16) | tj);
+          if (ti != tj && hf[(int64_t)ti * NT + tj]) tl[ntiles++] = (int32_t)((ti << 16) | tj);
+  for (int t = 0; t < NT; ++t)
+    if (hf[(int64_t)t * NT + t]) tl[ntiles++] = (int32_t)((t << 16) | t);
   if ((rc = w->tiles.reserve(ntiles + 1)) || (rc = w->partials.reserve((size_t)(ntiles + nb) * 4)))
     return rc;
-  // pinned source: the copy runs in stream order, before any later read-back reuses it
   BSR_HIP(hipMemcpyAsync(w->tiles.p, tl, ntiles * sizeof(int32_t), hipMemcpyHostToDevice, s));
   // 4. numeric
   BsrProductArgs args;
@@ -1071,9 +1164,9 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   args.normP = w->normP.p;
   args.tiles = w->tiles.p;
   args.partials = w->partials.p;
-  args.nrmX = screen2 > 0.0 ? w->nrmX.p : nullptr;
-  args.nrmY = screen2 > 0.0 ? (&B == &X ? w->nrmX.p : w->nrmY.p) : nullptr;
-  args.screen2 = screen2 > 0.0 ? screen2 : 0.0;
+  args.nrmX = screen ? X.nrm.p : nullptr;
+  args.nrmY = screen ? B.nrm.p : nullptr;
+  args.screen2 = screen ? screen2 : 0.0;
   args.nb = nb;
   args.W = W;
   if (ev_a) BSR_HIP(hipEventRecord(ev_a, s));
@@ -1097,26 +1190,53 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   hipLaunchKernelGGL(bsr_truncate_kernel, dim3(nb), dim3(64), 0, s, P.row_ptr.p, P.col.p,
                      w->normP.p, tau2, w->rank.p, w->cnt.p, w->partials.p, ntiles);
   BSR_HIP(hipGetLastError());
-  int64_t nnzN = 0;
-  if ((rc = scan_counts(w, w->cnt.p, nb, N.row_ptr, &nnzN, s))) return rc;
-  if ((rc = N.col.reserve(nnzN)) || (rc = N.val.reserve((size_t)nnzN * kBB))) return rc;
+  sums->p = w->partials.p;
+  sums->count = ntiles + nb;
+  if (sums->count > 16 * kSumSlots) {
+    if ((rc = w->slot_sums.reserve(kSumSlots * 4))) return rc;
+    hipLaunchKernelGGL(bsr_sum_slots_kernel, dim3(kSumSlots), dim3(256), 0, s, w->partials.p,
+                       sums->count, w->slot_sums.p);
+    BSR_HIP(hipGetLastError());
+    sums->p = w->slot_sums.p;
+    sums->count = kSumSlots;
+  }
+  if (advance) {
+    launch_schedule(w->state, sums->p, sums->count, 0, s);
+    BSR_HIP(hipGetLastError());
+    BSR_HIP(hipMemcpyAsync(w->state_host, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));
+  }
+  BSR_HIP(hipMemcpyAsync(pin + st.cntN, w->cnt.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  BSR_HIP(hipStreamSynchronize(s));
+  if (advance && w->state_host->stop) return SNF_OK;   // (the result is the product's operand)
+  int32_t* rpN = (int32_t*)(pin + st.rpN);
+  const int64_t nnzN = scan_counts((const int32_t*)(pin + st.cntN), rpN, nb);
+  if (nnzN < 0) return SNF_ENOMEM;
+  if ((rc = N.row_ptr.reserve(nb + 1)) || (rc = N.col.reserve(nnzN)) ||
+      (rc = N.val.reserve((size_t)nnzN * kBB)) || (screen && (rc = N.nrm.reserve(nnzN))))
+    return rc;
+  BSR_HIP(hipMemcpyAsync(N.row_ptr.p, rpN, (nb + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
   N.nnzb = nnzN;
-  // 6. compaction
-  hipLaunchKernelGGL(bsr_compact_kernel, dim3(nb), dim3(256), 0, s, P.row_ptr.p, P.col.p, P.val.p,
-                     w->rank.p, N.row_ptr.p, N.col.p, N.val.p);
+  // 6. compaction: enough workgroups for the memory's rate where the rows are few (n = 4096: 44
+  // us with one per row)
+  const dim3 cgrid(nb, (unsigned)std::min(32, std::max(1, 2048 / nb)));
+  hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, P.row_ptr.p, P.col.p, P.val.p,
+                     w->rank.p, N.row_ptr.p, N.col.p, N.val.p, w->normP.p,
+                     screen ? N.nrm.p : nullptr);
+  N.nrm_ok = screen;
   BSR_HIP(hipGetLastError());
   if (N2) {                              // the same kept blocks of the second output
     if ((rc = N2->row_ptr.reserve(nb + 1)) || (rc = N2->col.reserve(nnzN)) ||
         (rc = N2->val.reserve((size_t)nnzN * kBB)))
       return rc;
     N2->nnzb = nnzN;
+    N2->nrm_ok = false;
     BSR_HIP(hipMemcpyAsync(N2->row_ptr.p, N.row_ptr.p, (nb + 1) * sizeof(int32_t),
                            hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(bsr_compact_kernel, dim3(nb), dim3(256), 0, s, P.row_ptr.p, P.col.p,
-                       w->val2.p, w->rank.p, N2->row_ptr.p, N2->col.p, N2->val.p);
+    hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, P.row_ptr.p, P.col.p,
+                       w->val2.p, w->rank.p, N2->row_ptr.p, N2->col.p, N2->val.p, w->normP.p,
+                       (double*)nullptr);
     BSR_HIP(hipGetLastError());
   }
-  *slots = ntiles + nb;
   return SNF_OK;
 }
 
@@ -1173,6 +1293,7 @@ static int bsr_init(BsrWorkspace* w, const snf_bsr* F, int W, hipStream_t s) {
       (rc = X.val.reserve((size_t)F->nnzb * kBB)) || (rc = w->partials.reserve(kF0Blocks * 4)))
     return rc;
   X.nnzb = F->nnzb;
+  X.nrm_ok = false;
   BSR_HIP(hipMemcpyAsync(X.row_ptr.p, F->row_ptr, (nb + 1) * 4, hipMemcpyDeviceToDevice, s));
   BSR_HIP(hipMemcpyAsync(X.col.p, F->col_idx, F->nnzb * 4, hipMemcpyDeviceToDevice, s));
   hipLaunchKernelGGL(bsr_f0_kernel, dim3(kF0Blocks), dim3(256), 0, s, w->Fl.row_ptr.p,
@@ -1401,7 +1522,7 @@ static int purify_bsr_body(const snf_bsr* F, const snf_params* params, snf_schem
   // that completes an iteration is truncated: the intermediates keep every candidate block,
   // as the oracle's mask applies to each f_i's result.
   for (int pass = 0; pass <= 8 * (p.max_iter + 1); ++pass) {
-    int slots = 0;
+    SlotSums slots{nullptr, 0};
     const bool last = sh->kind == kKindCube || sh->kind == kKindFinal ||
                       (sh->kind == kKindSquare && (sh->branch == SNF_BRANCH_SQUARE ||
                                                    sh->branch == SNF_BRANCH_FOLD));
@@ -1409,14 +1530,10 @@ static int purify_bsr_body(const snf_bsr* F, const snf_params* params, snf_schem
     BsrBuf& out = w->buf(sh->io);
     BsrBuf* out2 = sh->dual ? &w->buf(sh->io2) : nullptr;
     rc = bsr_step(w, w->buf(sh->ia), w->buf(sh->ib), w->buf(sh->ix), out, nb, W,
-                  last ? tau2 : 0.0, &slots, timing ? w->ev[2] : nullptr,
+                  last ? tau2 : 0.0, &slots, true, timing ? w->ev[2] : nullptr,
                   timing ? w->ev[3] : nullptr, s, last ? eps_i : -1.0,
                   p.screen_tau * p.screen_tau, out2);
     if (rc) return fail(rc);
-    launch_schedule(w->state, w->partials.p, slots, 0, s);
-    BSR_HIP(hipGetLastError());
-    BSR_HIP(hipMemcpyAsync(sh, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));
-    BSR_HIP(hipStreamSynchronize(s));
     if (timing) {
       float ms = 0.f;
       BSR_HIP(hipEventElapsedTime(&ms, w->ev[2], w->ev[3]));
@@ -1506,18 +1623,19 @@ int snf_step_bsr(const snf_bsr* Xin, double c2, double c1, double c0, double tru
       (rc = X.val.reserve((size_t)Xin->nnzb * kBB)))
     return rc;
   X.nnzb = Xin->nnzb;
+  X.nrm_ok = false;
   BSR_HIP(hipMemcpyAsync(X.row_ptr.p, Xin->row_ptr, (nb + 1) * 4, hipMemcpyDeviceToDevice, s));
   BSR_HIP(hipMemcpyAsync(X.col.p, Xin->col_idx, Xin->nnzb * 4, hipMemcpyDeviceToDevice, s));
   if ((rc = build_lookup(X, nb, W, s))) return rc;
   hipLaunchKernelGGL(bsr_sym_copy_kernel, dim3(kF0Blocks), dim3(256), 0, s, X.row_ptr.p, X.col.p,
                      X.bm.p, X.pre.p, W, Xin->val, X.val.p, nb);
   BSR_HIP(hipGetLastError());
-  int slots = 0;
-  if ((rc = bsr_step(w, X, X, X, w->X[1], nb, W, trunc_tau * trunc_tau, &slots, w->ev[2],
+  SlotSums slots{nullptr, 0};
+  if ((rc = bsr_step(w, X, X, X, w->X[1], nb, W, trunc_tau * trunc_tau, &slots, false, w->ev[2],
                      w->ev[3], s, -1.0, screen_tau * screen_tau)))
     return rc;
   if ((rc = ensure_pinned(w, 64)) || (rc = w->sums.reserve(4))) return rc;
-  launch_sum_partials(w->partials.p, slots, w->sums.p, s);
+  launch_sum_partials(slots.p, slots.count, w->sums.p, s);
   BSR_HIP(hipGetLastError());
   BSR_HIP(hipMemcpyAsync(w->pinned, w->sums.p, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
   rc = make_output(w->X[1], Xin->n, nb, Y_out, s);
