@@ -901,10 +901,9 @@ struct BsrWorkspace {
   BsrBuf& buf(int i) { return i == 0 ? X[0] : i == 1 ? X[1] : i == 2 ? S : T; }
   DevArr<double> normP, partials, sums;
   DevArr<double> slot_sums;     // [kSumSlots][4]
-  DevArr<int32_t> cnt, rank, tiles;
-  DevArr<int64_t> triples;
+  DevArr<int32_t> rank;
+  DevArr<int32_t> plan;         // row_ptr of P, then the product's super-tiles
   int64_t last_triples = 0;
-  DevArr<uint8_t> flags;
   SnfState* state = nullptr;
   SnfState* state_host = nullptr;
   int32_t* pinned = nullptr;    // scratch for small read-backs
@@ -945,11 +944,8 @@ void bsr_release_all_devices() {
     w->sums.release();
     w->slot_sums.release();
     w->val2.release();
-    w->cnt.release();
     w->rank.release();
-    w->tiles.release();
-    w->triples.release();
-    w->flags.release();
+    w->plan.release();
     w->hist.release();
     if (w->state) (void)hipFree(w->state);
     w->state = nullptr;
@@ -1022,10 +1018,12 @@ static int build_lookup(BsrBuf& b, int nb, int W, hipStream_t s) {
 }
 
 // Pinned staging of one step (offsets in bytes from the workspace's pinned block): what the
-// device hands back and takes in one step, each in its own place, so that a copy in flight is
-// never overwritten.
+// device hands back in one step, written there by the kernels themselves (a copy each took
+// longer than the kernels at n = 4096), and what it takes, each in its own place, so that a
+// copy in flight is never overwritten.
 struct StepStage {
-  size_t cntP, rpP, cntN, rpN, tri, flags, tiles, total;
+  size_t cntP, plan, cntN, rpN, tri, flags, total;
+  size_t tiles0;                  // first tile of the plan, in words: row_ptr of P comes first
   StepStage(int nb, int64_t nflags) {
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1035,11 +1033,11 @@ struct StepStage {
     };
     tri = take((size_t)nb * 8);
     cntP = take((size_t)nb * 4);
-    rpP = take((size_t)(nb + 1) * 4);
     cntN = take((size_t)nb * 4);
     rpN = take((size_t)(nb + 1) * 4);
     flags = take((size_t)nflags);
-    tiles = take((size_t)nflags * 4);
+    tiles0 = ((size_t)nb + 1 + 15) / 16 * 16;
+    plan = take((tiles0 + (size_t)nflags) * 4);
     total = o;
   }
 };
@@ -1098,26 +1096,19 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   const int64_t nflags = (int64_t)NT * NT;
   const StepStage st(nb, nflags);
   if ((rc = P.bm.reserve((size_t)nb * W)) || (rc = P.pre.reserve((size_t)nb * W)) ||
-      (rc = w->cnt.reserve(nb)) || (rc = w->triples.reserve(nb)) ||
-      (rc = w->flags.reserve((size_t)nflags)) || (rc = ensure_pinned(w, st.total)) ||
-      (rc = P.row_ptr.reserve(nb + 1)))
+      (rc = ensure_pinned(w, st.total)) || (rc = w->plan.reserve(st.tiles0 + nflags)))
     return rc;
   char* pin = (char*)w->pinned;
   hipLaunchKernelGGL(bsr_symbolic_kernel, dim3(nb), dim3(256), W * sizeof(uint32_t), s,
                      X.row_ptr.p, X.col.p, B.row_ptr.p, B.bm.p, W, B.pre.p, P.bm.p, P.pre.p,
-                     w->cnt.p, w->triples.p);
+                     (int32_t*)(pin + st.cntP), (int64_t*)(pin + st.tri));
   hipLaunchKernelGGL(bsr_tile_flags_kernel, dim3((unsigned)((nflags + 255) / 256)), dim3(256), 0,
-                     s, P.bm.p, nb, W, NT, w->flags.p);
+                     s, P.bm.p, nb, W, NT, (uint8_t*)(pin + st.flags));
   BSR_HIP(hipGetLastError());
-  BSR_HIP(hipMemcpyAsync(pin + st.cntP, w->cnt.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  BSR_HIP(hipMemcpyAsync(pin + st.tri, w->triples.p, nb * sizeof(int64_t), hipMemcpyDeviceToHost,
-                         s));
-  BSR_HIP(hipMemcpyAsync(pin + st.flags, w->flags.p, nflags, hipMemcpyDeviceToHost, s));
   BSR_HIP(hipStreamSynchronize(s));
-  int32_t* rpP = (int32_t*)(pin + st.rpP);
-  const int64_t nnzP = scan_counts((const int32_t*)(pin + st.cntP), rpP, nb);
+  int32_t* plan = (int32_t*)(pin + st.plan);           // row_ptr of P, then the super-tiles
+  const int64_t nnzP = scan_counts((const int32_t*)(pin + st.cntP), plan, nb);
   if (nnzP < 0) return SNF_ENOMEM;
-  BSR_HIP(hipMemcpyAsync(P.row_ptr.p, rpP, (nb + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
   {
     const int64_t* tri = (const int64_t*)(pin + st.tri);
     int64_t t = 0;
@@ -1128,10 +1119,8 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
       (rc = w->normP.reserve(nnzP)) || (rc = w->rank.reserve(nnzP)))
     return rc;
   P.nnzb = nnzP;
-  hipLaunchKernelGGL(bsr_fill_cols_kernel, dim3(nb), dim3(64), 0, s, P.bm.p, P.pre.p,
-                     P.row_ptr.p, W, P.col.p);
   const uint8_t* hf = (const uint8_t*)(pin + st.flags);
-  int32_t* tl = (int32_t*)(pin + st.tiles);
+  int32_t* tl = plan + st.tiles0;
   int ntiles = 0;
   // super-tiles in squares of SQ x SQ (squares in row-major order of the upper triangle,
   // tiles row-major inside): the ~512 workgroups resident at once cover 8 bands of A rows and
@@ -1147,22 +1136,25 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
           if (ti != tj && hf[(int64_t)ti * NT + tj]) tl[ntiles++] = (int32_t)((ti << 16) | tj);
   for (int t = 0; t < NT; ++t)
     if (hf[(int64_t)t * NT + t]) tl[ntiles++] = (int32_t)((t << 16) | t);
-  if ((rc = w->tiles.reserve(ntiles + 1)) || (rc = w->partials.reserve((size_t)(ntiles + nb) * 4)))
-    return rc;
-  BSR_HIP(hipMemcpyAsync(w->tiles.p, tl, ntiles * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  if ((rc = w->partials.reserve((size_t)(ntiles + nb) * 4))) return rc;
+  BSR_HIP(hipMemcpyAsync(w->plan.p, plan, (st.tiles0 + ntiles) * sizeof(int32_t),
+                         hipMemcpyHostToDevice, s));
+  const int32_t* rowP = w->plan.p;
+  hipLaunchKernelGGL(bsr_fill_cols_kernel, dim3(nb), dim3(64), 0, s, P.bm.p, P.pre.p, rowP, W,
+                     P.col.p);
   // 4. numeric
   BsrProductArgs args;
   args.X = X.view();
   args.Y = B.view();
   args.L = L.view();
-  args.P = P.view();
+  args.P = BsrMat{rowP, P.bm.p, P.pre.p, P.val.p};
   args.val2 = nullptr;
   if (N2) {                              // second output, same candidate pattern
     if ((rc = w->val2.reserve((size_t)nnzP * kBB))) return rc;
     args.val2 = w->val2.p;
   }
   args.normP = w->normP.p;
-  args.tiles = w->tiles.p;
+  args.tiles = w->plan.p + st.tiles0;
   args.partials = w->partials.p;
   args.nrmX = screen ? X.nrm.p : nullptr;
   args.nrmY = screen ? B.nrm.p : nullptr;
@@ -1178,7 +1170,7 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   if (eps_i >= 0.0) {
     if ((rc = w->hist.reserve(kNumBins))) return rc;
     BSR_HIP(hipMemsetAsync(w->hist.p, 0, kNumBins * sizeof(uint32_t), s));
-    hipLaunchKernelGGL(bsr_norm_hist_kernel, dim3(nb), dim3(64), 0, s, P.row_ptr.p, P.col.p,
+    hipLaunchKernelGGL(bsr_norm_hist_kernel, dim3(nb), dim3(64), 0, s, rowP, P.col.p,
                        w->normP.p, w->hist.p);
     BSR_HIP(hipGetLastError());
     BSR_HIP(hipMemcpyAsync(w->hist_host, w->hist.p, kNumBins * sizeof(uint32_t),
@@ -1187,8 +1179,8 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
     tau2 = error_control_tau2(w->hist_host, eps_i);
     w->last_tau2 = tau2;
   }
-  hipLaunchKernelGGL(bsr_truncate_kernel, dim3(nb), dim3(64), 0, s, P.row_ptr.p, P.col.p,
-                     w->normP.p, tau2, w->rank.p, w->cnt.p, w->partials.p, ntiles);
+  hipLaunchKernelGGL(bsr_truncate_kernel, dim3(nb), dim3(64), 0, s, rowP, P.col.p, w->normP.p,
+                     tau2, w->rank.p, (int32_t*)(pin + st.cntN), w->partials.p, ntiles);
   BSR_HIP(hipGetLastError());
   sums->p = w->partials.p;
   sums->count = ntiles + nb;
@@ -1201,11 +1193,9 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
     sums->count = kSumSlots;
   }
   if (advance) {
-    launch_schedule(w->state, sums->p, sums->count, 0, s);
+    launch_schedule(w->state, sums->p, sums->count, 0, s, w->state_host);
     BSR_HIP(hipGetLastError());
-    BSR_HIP(hipMemcpyAsync(w->state_host, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));
   }
-  BSR_HIP(hipMemcpyAsync(pin + st.cntN, w->cnt.p, nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   BSR_HIP(hipStreamSynchronize(s));
   if (advance && w->state_host->stop) return SNF_OK;   // (the result is the product's operand)
   int32_t* rpN = (int32_t*)(pin + st.rpN);
@@ -1219,7 +1209,7 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   // 6. compaction: enough workgroups for the memory's rate where the rows are few (n = 4096: 44
   // us with one per row)
   const dim3 cgrid(nb, (unsigned)std::min(32, std::max(1, 2048 / nb)));
-  hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, P.row_ptr.p, P.col.p, P.val.p,
+  hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, rowP, P.col.p, P.val.p,
                      w->rank.p, N.row_ptr.p, N.col.p, N.val.p, w->normP.p,
                      screen ? N.nrm.p : nullptr);
   N.nrm_ok = screen;
@@ -1232,7 +1222,7 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
     N2->nrm_ok = false;
     BSR_HIP(hipMemcpyAsync(N2->row_ptr.p, N.row_ptr.p, (nb + 1) * sizeof(int32_t),
                            hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, P.row_ptr.p, P.col.p,
+    hipLaunchKernelGGL(bsr_compact_kernel, cgrid, dim3(256), 0, s, rowP, P.col.p,
                        w->val2.p, w->rank.p, N2->row_ptr.p, N2->col.p, N2->val.p, w->normP.p,
                        (double*)nullptr);
     BSR_HIP(hipGetLastError());
@@ -1550,6 +1540,7 @@ static int purify_bsr_body(const snf_bsr* F, const snf_params* params, snf_schem
   rc = make_output(w->buf(cur), F->n, nb, D_out, s);
   if (rc) return fail(rc);
   BSR_HIP(hipEventRecord(w->ev[1], s));
+  BSR_HIP(hipMemcpyAsync(sh, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));   // the log
   BSR_HIP(hipStreamSynchronize(s));
   const int status = sh->stop ? sh->status : SNF_ENOCONV;
   out->status = status;

@@ -1279,15 +1279,16 @@ __device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ hs,
 // header (everything before the log) is staged in LDS by all threads, advanced there by
 // thread 0 and written back by all threads: one pass of coalesced accesses instead of a
 // chain of dependent single-thread loads and stores to device memory.
-constexpr int kStateHeaderBytes = (int)sizeof(SnfHeader);
-
-__device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg, const double* __restrict__ partials,
-                              int count, int init) {
+__device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
+                                              const double* __restrict__ partials, int count,
+                                              int init, SnfHeader* __restrict__ host) {
   __shared__ double red[24];
   __shared__ __attribute__((aligned(16))) SnfHeader hs;
-  unsigned char* hb = (unsigned char*)&hs;
-  const unsigned char* gb = (const unsigned char*)sg;
-  for (int i = threadIdx.x; i < kStateHeaderBytes; i += kReduceThreads) hb[i] = gb[i];
+  static_assert(sizeof(SnfHeader) % 4 == 0, "copied by words");
+  constexpr int words = (int)(sizeof(SnfHeader) / 4);
+  unsigned* hb = (unsigned*)&hs;
+  unsigned* gb = (unsigned*)(SnfHeader*)sg;
+  for (int i = threadIdx.x; i < words; i += kReduceThreads) hb[i] = gb[i];
   double e2 = 0.0, t1 = 0.0, t2 = 0.0;
   for (int i = threadIdx.x; i < count; i += kReduceThreads) {
     e2 += partials[i * 4 + 0];
@@ -1297,8 +1298,10 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg, const d
   block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
   if (threadIdx.x == 0) schedule_step(&hs, sg->log, e2, t1, t2, init);
   __syncthreads();
-  unsigned char* gw = (unsigned char*)sg;
-  for (int i = threadIdx.x; i < kStateHeaderBytes; i += kReduceThreads) gw[i] = hb[i];
+  for (int i = threadIdx.x; i < words; i += kReduceThreads) {
+    gb[i] = hb[i];
+    if (host) ((unsigned*)host)[i] = hb[i];
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1977,15 +1980,16 @@ int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D,
 
 __global__ __launch_bounds__(kReduceThreads) void schedule_kernel(SnfState* __restrict__ s,
                                                                   const double* __restrict__ partials,
-                                                                  int count, int init) {
+                                                                  int count, int init,
+                                                                  SnfHeader* __restrict__ host) {
   if (s->stop) return;
-  schedule_body(s, partials, count, init);
+  schedule_body(s, partials, count, init, host);
 }
 
-void launch_schedule(SnfState* st, const double* partials, int count, int init,
-                     hipStream_t s) {
+void launch_schedule(SnfState* st, const double* partials, int count, int init, hipStream_t s,
+                     SnfHeader* host) {
   hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(kReduceThreads), 0, s, st, partials,
-                     count, init);
+                     count, init, host);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2314,7 +2318,7 @@ __global__ __launch_bounds__(kReduceThreads) void grouped_schedule_kernel(const 
                                                                           const int* __restrict__ active) {
   const SlotDesc sd = slots[active[blockIdx.x]];
   if (sd.st->stop) return;
-  schedule_body(sd.st, sd.partials, num_product_tiles_dev(sd.np), 0);
+  schedule_body(sd.st, sd.partials, num_product_tiles_dev(sd.np), 0, nullptr);
 }
 
 __global__ void grouped_stop_kernel(const SlotDesc* __restrict__ slots, const int* __restrict__ active,

@@ -117,8 +117,9 @@ struct Buffers {
 // ---- kernels launched by the host drivers (defined in kernels_dense.hip) ----------------
 void launch_f0(const double* F, int64_t n, int64_t ld, int64_t np, SnfState* st,
                const Buffers* bufs_dev, int lowp_kind, double* partials, hipStream_t s);
-void launch_schedule(SnfState* st, const double* partials, int count, int init,
-                     hipStream_t s);
+// host: host-visible memory that takes the header too, or null.
+void launch_schedule(SnfState* st, const double* partials, int count, int init, hipStream_t s,
+                     SnfHeader* host = nullptr);
 // Work decomposition of one product launch (see make_product_grid).
 struct ProductGrid {
   int64_t np, n;       // padded and true order
