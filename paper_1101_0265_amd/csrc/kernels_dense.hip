@@ -556,26 +556,29 @@ __device__ __forceinline__ void store_slice(const AccT (&acc)[MT][QT], int wr0, 
 //   sB[k][j] = B[k0+k][j0+j]; A[i][k] = A[k][i] because A is symmetric, so both panels are
 //   read with contiguous, coalesced rows.  MFMA operand of lane l: row/col (l % 16), k (l / 16).
 // ---------------------------------------------------------------------------------------
-// Thread layout: NT threads = (NT/64) waves in WR x WC, each wave a (128/WR) x (128/WC)
+// Thread layout: NT threads = (NT/64) waves in WR x WC, each wave a (TILE/WR) x (TILE/WC)
 // piece of the tile made of MT x QT MFMA 16x16 blocks.
-template <typename T> struct Layout;
-template <> struct Layout<double> {   // 8 waves of 64x32: 64 accumulator registers per lane,
-  static constexpr int NT = 512, WC = 4;   // so 4 waves fit on each SIMD
+template <typename T, int TILE> struct Layout;
+template <> struct Layout<double, kTile> {   // 8 waves of 64x32: 64 accumulator registers per
+  static constexpr int NT = 512, WC = 4;     // lane, so 4 waves fit on each SIMD
 };
-template <> struct Layout<float> {    // 8 waves of 32x64: 32 accumulator registers per lane,
-  static constexpr int NT = 512, WC = 2;   // 4 waves per SIMD
+template <> struct Layout<float, kTile> {    // 8 waves of 32x64: 32 accumulator registers per
+  static constexpr int NT = 512, WC = 2;     // lane, 4 waves per SIMD
+};
+template <> struct Layout<float, kFineTile> {   // 4 waves of 32x32
+  static constexpr int NT = 256, WC = 2;
 };
 
-template <typename T, int PREC, bool DUAL = false>
+template <typename T, int PREC, bool DUAL = false, int TILE = kTile>
 __device__ __forceinline__ void product_body(const SnfState* __restrict__ st,
                                              const Buffers* __restrict__ bufs,
                                              const ProductGrid& g, const WorkItem& wi) {
   typedef Mfma<T> M;
-  constexpr int NT = Layout<T>::NT, WC = Layout<T>::WC, WR = NT / 64 / WC;
-  constexpr int TR = kTile / WR, TC = kTile / WC, MT = TR / 16, QT = TC / 16;
-  constexpr int BK = M::kBK, LDS_W = kTile + M::kPad;
+  constexpr int NT = Layout<T, TILE>::NT, WC = Layout<T, TILE>::WC, WR = NT / 64 / WC;
+  constexpr int TR = TILE / WR, TC = TILE / WC, MT = TR / 16, QT = TC / 16;
+  constexpr int BK = M::kBK, LDS_W = TILE + M::kPad;
   constexpr int VE = 16 / sizeof(T);          // elements per 16-byte vector
-  constexpr int VPR = kTile / VE;             // vectors per LDS row
+  constexpr int VPR = TILE / VE;             // vectors per LDS row
   constexpr int RPP = NT / VPR;               // rows per load pass
   constexpr int PASSES = BK / RPP;
   __shared__ __attribute__((aligned(16))) T sA[2][BK][LDS_W];
@@ -586,8 +589,8 @@ __device__ __forceinline__ void product_body(const SnfState* __restrict__ st,
   const T* B = (PREC == kPrecF64) ? (const T*)bufs->x[st->ib] : (const T*)bufs->lp[st->ib];
 
   int bi, bj;
-  tile_coords(wi.tile, (int)(np / kTile), g.sym, bi, bj);
-  const int64_t i0 = (int64_t)bi * kTile, j0 = (int64_t)bj * kTile;
+  tile_coords(wi.tile, (int)(np / TILE), g.sym, bi, bj);
+  const int64_t i0 = (int64_t)bi * TILE, j0 = (int64_t)bj * TILE;
 
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wr = wid / WC, wc = wid % WC;
@@ -924,10 +927,10 @@ void launch_product(int prec, SnfState* st, const Buffers* bufs_dev, const Produ
                     hipStream_t s) {
   const int grid = g.dp_tiles + g.tail_tiles * g.split_s;
   if (prec == kPrecF64) {
-    hipLaunchKernelGGL(product_f64_kernel, dim3(grid), dim3(Layout<double>::NT), 0, s, st,
+    hipLaunchKernelGGL(product_f64_kernel, dim3(grid), dim3(Layout<double, kTile>::NT), 0, s, st,
                        bufs_dev, g);
   } else if (prec == kPrecF32) {
-    hipLaunchKernelGGL(product_f32_kernel, dim3(grid), dim3(Layout<float>::NT), 0, s, st,
+    hipLaunchKernelGGL(product_f32_kernel, dim3(grid), dim3(Layout<float, kTile>::NT), 0, s, st,
                        bufs_dev, g);
   } else {
     hipLaunchKernelGGL(product_bf16_kernel, dim3(grid), dim3(kThreads), 0, s, st, bufs_dev, g);
@@ -937,7 +940,7 @@ void launch_product(int prec, SnfState* st, const Buffers* bufs_dev, const Produ
 void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                          hipStream_t s) {
   const int grid = g.dp_tiles + g.tail_tiles * g.split_s;
-  hipLaunchKernelGGL(product_f64_dual_kernel, dim3(grid), dim3(Layout<double>::NT), 0, s, st,
+  hipLaunchKernelGGL(product_f64_dual_kernel, dim3(grid), dim3(Layout<double, kTile>::NT), 0, s, st,
                      bufs_dev, g);
 }
 
@@ -1373,6 +1376,105 @@ struct DirectOperand {
   }
 };
 
+// Combination, sums and stores of one tile: bands of 32 rows (one pair of block rows; the last 16
+// rows for odd TB): add the four partial tiles in wave order, combine, store the rows, then the
+// mirror from LDS so that its stores are contiguous too.  load_x(p) fetches band p of the linear
+// term into xs (band 0 is there already).
+struct DirectOut {
+  double* Y;
+  double* Y2;              // second output, or null
+  void* lp;                // low-precision copy of Y (LOWP), of kind lowp_kind (-1: none)
+  int lowp_kind, n;
+  int64_t ld;
+  double c2, c1, c0, d2, d1, d0;
+};
+
+__device__ __forceinline__ void direct_lowp(const DirectOut& o, int64_t at, double y) {
+  if (o.lowp_kind == kPrecF32) ((float*)o.lp)[at] = (float)y;
+  else if (o.lowp_kind == kPrecBF16) ((unsigned short*)o.lp)[at] = f32_to_bf16_rne((float)y);
+}
+
+template <int TB, int NC, bool LOWP, int PR, int NE, typename LoadX>
+__device__ __forceinline__ void direct_bands(const dbl4 (&acc)[TB][TB / NC],
+                                             double (&part)[4][PR][16 * TB + 2], double2 (&xs)[NE],
+                                             LoadX load_x, const DirectOut& o, int64_t i0,
+                                             int64_t j0, bool worker, double& e2, double& t1,
+                                             double& t2) {
+  constexpr int T = 16 * TB, QB = TB / NC, NT = kDirectThreads * NC, W2 = T / 2;
+  constexpr int P = TB / 2, O = TB & 1, QP = QB / 2, QO = QB & 1;
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, fk = lane >> 4, kq = wid & 3, cg = wid >> 2;
+  const bool diag = i0 == j0;
+#pragma unroll
+  for (int p = 0; p < P + O; ++p) {
+    const int rows = p < P ? 32 : 16;
+    if (worker) {
+#pragma unroll
+      for (int mm = 0; mm < (p < P ? 2 : 1); ++mm) {
+        const int m = 2 * p + mm;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int t = fk + 4 * v, r = p < P ? 2 * t + mm : t;
+#pragma unroll
+          for (int q = 0; q < QP; ++q)
+            *(double2*)(&part[kq][r][cg * 16 * QB + 32 * q + 2 * fr]) =
+                double2{acc[m][2 * q][v], acc[m][2 * q + 1][v]};
+          if (QO) part[kq][r][cg * 16 * QB + 32 * QP + fr] = acc[m][QB - 1][v];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
+      if (!worker || r >= rows) continue;
+      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
+      double y[2], y2[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double pr = ((part[0][r][c + h] + part[1][r][c + h]) + part[2][r][c + h]) +
+                          part[3][r][c + h];
+        const double x = h ? xs[e].y : xs[e].x;
+        const bool on = gr == gc + h, in = gr < o.n && gc + h < o.n;
+        y[h] = in ? o.c2 * pr + o.c1 * x + (on ? o.c0 : 0.0) : 0.0;
+        y2[h] = in ? o.d2 * pr + o.d1 * x + (on ? o.d0 : 0.0) : 0.0;
+        if (!diag || gr <= gc + h) {       // (a diagonal tile keeps its upper half)
+          const double w = on ? 1.0 : 2.0, d = pr - x;
+          e2 += w * (d * d);
+          t2 += w * (y[h] * y[h]);
+          if (on) t1 += y[h];
+          if (diag) {
+            o.Y[(int64_t)gr * o.ld + gc + h] = y[h];
+            if (o.Y2) o.Y2[(int64_t)gr * o.ld + gc + h] = y2[h];
+            if (LOWP) direct_lowp(o, (int64_t)gr * o.ld + gc + h, y[h]);
+          }
+        }
+      }
+      if (!diag) {
+        *(double2*)(o.Y + (int64_t)gr * o.ld + gc) = double2{y[0], y[1]};
+        if (o.Y2) *(double2*)(o.Y2 + (int64_t)gr * o.ld + gc) = double2{y2[0], y2[1]};
+        if (LOWP) {
+          direct_lowp(o, (int64_t)gr * o.ld + gc, y[0]);
+          direct_lowp(o, (int64_t)gr * o.ld + gc + 1, y[1]);
+        }
+      }
+      *(double2*)(&part[0][r][c]) = double2{y[0], y[1]};   // (this thread's own entries)
+      if (o.Y2) *(double2*)(&part[1][r][c]) = double2{y2[0], y2[1]};
+    }
+    if (p + 1 < P + O) load_x(p + 1);   // (a band ahead)
+    __syncthreads();
+    for (int idx = worker ? tid : rows * T; idx < rows * T; idx += NT) {
+      const int r = idx % rows, c = idx / rows;
+      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
+      if (diag && gr >= gc) continue;
+      o.Y[(int64_t)gc * o.ld + gr] = part[0][r][c];
+      if (o.Y2) o.Y2[(int64_t)gc * o.ld + gr] = part[1][r][c];
+      if (LOWP) direct_lowp(o, (int64_t)gc * o.ld + gr, part[0][r][c]);
+    }
+    if (p + 1 < P + O) __syncthreads();
+  }
+}
+
 // NC: column groups of the tile; four waves (the k quarters) for each, so that a wave holds
 // TB x TB / NC blocks.  SW: one more wave, which runs the schedule beside the product (where the
 // registers allow it; else wave 0 does, ahead of its share).  The product needs the schedule's
@@ -1383,7 +1485,7 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     DirectArgs g, int step, int pa, int pb, int px) {
   constexpr int T = 16 * TB, QB = TB / NC, NT = kDirectThreads * NC;
   static_assert(QB * NC == TB, "equal column groups");
-  constexpr int P = TB / 2, O = TB & 1, QP = QB / 2, QO = QB & 1, LW = T + 2;
+  constexpr int P = TB / 2, LW = T + 2;
   constexpr int SWAVE = SW ? 4 * NC : 0;
   // the product starts ahead of the schedule; the largest tiles wait for it, as their product
   // takes 20 times as long and the look at the flag costs their loop more (n = 1760: 5%)
@@ -1549,81 +1651,27 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     }
   }
 
-  // Bands of 32 rows (one pair of block rows; the last 16 rows for odd TB): add the four
-  // partial tiles in wave order, combine, store the rows, then the mirror from LDS so that its
-  // stores are contiguous too.
-  const int n = (int)g.n;
+  // the tile's results
   const int ix = __builtin_amdgcn_readfirstlane(hs.ix);
   const double* X = pick_buf(g.bufs, ix);
   if (!XA || ix != px) load_x(X, 0);
-  double* Y = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io));
-  const int dual = __builtin_amdgcn_readfirstlane(hs.dual);
-  double* Y2 = dual ? pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io2)) : nullptr;
-  const double c2 = hs.c2, c1 = hs.c1, c0 = hs.c0, d2 = hs.d2, d1 = hs.d1, d0 = hs.d0;
-  const bool diag = bi == bj;
+  DirectOut o;
+  o.Y = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io));
+  o.Y2 = __builtin_amdgcn_readfirstlane(hs.dual)
+             ? pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io2)) : nullptr;
+  o.lp = nullptr;
+  o.lowp_kind = -1;
+  o.n = (int)g.n;
+  o.ld = ld;
+  o.c2 = hs.c2;
+  o.c1 = hs.c1;
+  o.c0 = hs.c0;
+  o.d2 = hs.d2;
+  o.d1 = hs.d1;
+  o.d0 = hs.d0;
   e2 = t1 = t2 = 0.0;
-#pragma unroll
-  for (int p = 0; p < P + O; ++p) {
-    const int rows = p < P ? 32 : 16;
-    if (worker) {
-#pragma unroll
-      for (int mm = 0; mm < (p < P ? 2 : 1); ++mm) {
-        const int m = 2 * p + mm;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int t = fk + 4 * v, r = p < P ? 2 * t + mm : t;
-#pragma unroll
-          for (int q = 0; q < QP; ++q)
-            *(double2*)(&part[kq][r][cg * 16 * QB + 32 * q + 2 * fr]) =
-                double2{acc[m][2 * q][v], acc[m][2 * q + 1][v]};
-          if (QO) part[kq][r][cg * 16 * QB + 32 * QP + fr] = acc[m][QB - 1][v];
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
-      if (!worker || r >= rows) continue;
-      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
-      double y[2], y2[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const double pr = ((part[0][r][c + h] + part[1][r][c + h]) + part[2][r][c + h]) +
-                          part[3][r][c + h];
-        const double x = h ? xs[e].y : xs[e].x;
-        const bool on = gr == gc + h, in = gr < n && gc + h < n;
-        y[h] = in ? c2 * pr + c1 * x + (on ? c0 : 0.0) : 0.0;
-        y2[h] = in ? d2 * pr + d1 * x + (on ? d0 : 0.0) : 0.0;
-        if (!diag || gr <= gc + h) {       // (a diagonal tile keeps its upper half)
-          const double w = on ? 1.0 : 2.0, d = pr - x;
-          e2 += w * (d * d);
-          t2 += w * (y[h] * y[h]);
-          if (on) t1 += y[h];
-          if (diag) {
-            Y[(int64_t)gr * ld + gc + h] = y[h];
-            if (Y2) Y2[(int64_t)gr * ld + gc + h] = y2[h];
-          }
-        }
-      }
-      if (!diag) {
-        *(double2*)(Y + (int64_t)gr * ld + gc) = double2{y[0], y[1]};
-        if (Y2) *(double2*)(Y2 + (int64_t)gr * ld + gc) = double2{y2[0], y2[1]};
-      }
-      *(double2*)(&part[0][r][c]) = double2{y[0], y[1]};   // (this thread's own entries)
-      if (Y2) *(double2*)(&part[1][r][c]) = double2{y2[0], y2[1]};
-    }
-    if (p + 1 < P + O) load_x(X, p + 1);   // (a band ahead)
-    __syncthreads();
-    for (int idx = worker ? tid : rows * T; idx < rows * T; idx += NT) {
-      const int r = idx % rows, c = idx / rows;
-      const int gr = (int)i0 + 32 * p + r, gc = (int)j0 + c;
-      if (diag && gr >= gc) continue;
-      Y[(int64_t)gc * ld + gr] = part[0][r][c];
-      if (Y2) Y2[(int64_t)gc * ld + gr] = part[1][r][c];
-    }
-    if (p + 1 < P + O) __syncthreads();
-  }
+  direct_bands<TB, NC, false>(acc, part, xs, [&](int p) { load_x(X, p); }, o, i0, j0, worker, e2,
+                              t1, t2);
   e2 = wave_sum_rows(e2);
   t1 = wave_sum_rows(t1);
   t2 = wave_sum_rows(t2);
@@ -2264,12 +2312,19 @@ __device__ __forceinline__ int group_find(const int* __restrict__ offs, int nact
   return lo;
 }
 
-__device__ __forceinline__ ProductGrid slot_grid(const SlotDesc& sd) {
+__device__ __forceinline__ int slot_tiles(const SlotDesc& sd, int prec) {
+  const int nt = (int)(sd.np / (prec == kPrecF64   ? sd.tile[kPrecF64]
+                                : prec == kPrecF32 ? sd.tile[kPrecF32]
+                                                   : sd.tile[kPrecBF16]));
+  return nt * (nt + 1) / 2;
+}
+
+__device__ __forceinline__ ProductGrid slot_grid(const SlotDesc& sd, int prec) {
   ProductGrid g;
   g.np = sd.np;
   g.n = sd.n;
   g.sym = 1;
-  g.dp_tiles = num_product_tiles_dev(sd.np);
+  g.dp_tiles = slot_tiles(sd, prec);
   g.tail_tiles = 0;
   g.split_s = 1;
   g.partial_count = g.dp_tiles;
@@ -2278,10 +2333,128 @@ __device__ __forceinline__ ProductGrid slot_grid(const SlotDesc& sd) {
   return g;
 }
 
+// Requests with 64x64 tiles.  A group of requests seldom fills the chip evenly: with 128x128
+// tiles a step lasted as long as the longest tile of its largest request (FP64 at n = 2048: 440
+// us on one compute unit, FP32 220), the rest waiting.  FP32: the same sum order per entry in a
+// quarter of the tile, four waves of 32x32.
+__global__ __launch_bounds__((Layout<float, kFineTile>::NT), 2) void grouped_fine_f32_kernel(
+    const SlotDesc* __restrict__ slots, const int* __restrict__ active,
+    const int* __restrict__ offs, int nactive) {
+  const int a = group_find(offs, nactive, blockIdx.x);
+  const SlotDesc sd = slots[active[a]];
+  if (sd.st->stop || sd.st->prec != kPrecF32) return;
+  const ProductGrid g = slot_grid(sd, kPrecF32);
+  WorkItem wi;
+  wi.tile = xcd_remap(blockIdx.x - offs[a], g.dp_tiles);
+  wi.piece = -1;
+  wi.kt_begin = 0;
+  wi.kt_end = (int)(sd.np / Mfma<float>::kBK);
+  product_body<float, kPrecF32, false, kFineTile>(sd.st, sd.bufs, g, wi);
+}
+
+// FP64: the direct step's product (k quarters to the waves of two column groups), on the state
+// that the schedule kernel left.
+__global__ __launch_bounds__(2 * kDirectThreads) void grouped_fine_f64_kernel(
+    const SlotDesc* __restrict__ slots, const int* __restrict__ active,
+    const int* __restrict__ offs, int nactive) {
+  constexpr int TB = kFineTile / 16, NC = 2, PD = 7, T = kFineTile, QB = TB / NC;
+  constexpr int NT = kDirectThreads * NC, W2 = T / 2, NE = 32 * W2 / NT;
+  const int a = group_find(offs, nactive, blockIdx.x);
+  const SlotDesc sd = slots[active[a]];
+  const SnfHeader* st = sd.st;
+  if (st->stop || st->prec != kPrecF64) return;
+  __shared__ double red[3 * 8];
+  __shared__ __attribute__((aligned(16))) double part[4][32][T + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fk = lane >> 4, kq = wid & 3, cg = wid >> 2;
+  const int64_t ld = sd.np;
+  const int tile = xcd_remap(blockIdx.x - offs[a], slot_tiles(sd, kPrecF64));
+  int bi, bj;
+  tile_coords(tile, (int)(sd.np / T), 1, bi, bj);
+  const int64_t i0 = (int64_t)bi * T, j0 = (int64_t)bj * T;
+  const Buffers& bufs = *sd.bufs;
+  const double *Ap = bufs.x[st->ia], *Bp = bufs.x[st->ib], *X = bufs.x[st->ix];
+  double2 xs[NE];
+  auto load_x = [&](int p) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int idx = e * NT + tid, r = idx / W2, c = 2 * (idx % W2);
+      xs[e] = *(const double2*)(X + (i0 + 32 * p + r) * ld + j0 + c);
+    }
+  };
+  const int KT = (int)((sd.n + 3) / 4), kb = kq * KT / 4, ke = (kq + 1) * KT / 4;
+  dbl4 acc[TB][QB];
+#pragma unroll
+  for (int m = 0; m < TB; ++m)
+#pragma unroll
+    for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  DirectOperand<TB, PD> A;
+  DirectOperand<QB, PD> B;
+  auto load = [&](int ks, int slot) {
+    const int64_t off = (int64_t)(4 * min(ks, max(ke - 1, kb)) + fk) * ld;
+    A.load(Ap + off + i0, slot);
+    B.load(Bp + off + j0 + cg * 16 * QB, slot);
+  };
+  auto compute = [&](int slot) {
+#pragma unroll
+    for (int m = 0; m < TB; ++m)
+#pragma unroll
+      for (int q = 0; q < QB; ++q)
+        acc[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.get(slot, m), B.get(slot, q), acc[m][q],
+                                                         0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < PD; ++u) load(kb + u, u);
+  load_x(0);
+  __builtin_amdgcn_sched_barrier(0);
+  int ks = kb;
+  for (; ks + PD <= ke; ks += PD) {
+#pragma unroll
+    for (int u = 0; u < PD; ++u) {
+      compute(u);
+      load(ks + u + PD, u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < PD; ++u)
+    if (ks + u < ke) compute(u);
+  DirectOut o;
+  o.Y = bufs.x[st->io];
+  o.Y2 = st->dual ? bufs.x[st->io2] : nullptr;
+  o.lp = bufs.lp[st->io];
+  o.lowp_kind = st->write_lowp ? (st->mode == SNF_P_BF16_REF64 ? kPrecBF16 : kPrecF32) : -1;
+  o.n = (int)sd.n;
+  o.ld = ld;
+  o.c2 = st->c2;
+  o.c1 = st->c1;
+  o.c0 = st->c0;
+  o.d2 = st->d2;
+  o.d1 = st->d1;
+  o.d0 = st->d0;
+  double e2 = 0.0, t1 = 0.0, t2 = 0.0;
+  direct_bands<TB, NC, true>(acc, part, xs, load_x, o, i0, j0, true, e2, t1, t2);
+  e2 = wave_sum_rows(e2);
+  t1 = wave_sum_rows(t1);
+  t2 = wave_sum_rows(t2);
+  if (lane == 0) {
+    red[wid * 3 + 0] = e2;
+    red[wid * 3 + 1] = t1;
+    red[wid * 3 + 2] = t2;
+  }
+  __syncthreads();
+  if (tid < 3) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum += red[w * 3 + tid];
+    sd.partials[(size_t)tile * 4 + tid] = sum;
+  }
+}
+
 // DUAL: the FP64 variant whose epilogue also writes the second output (the first product of
 // a P_{i,j} iteration); each request's state selects exactly one of the two FP64 variants.
 template <typename T, int PREC, bool DUAL = false>
-__global__ __launch_bounds__(Layout<T>::NT, 2) void grouped_product_kernel(const SlotDesc* __restrict__ slots,
+__global__ __launch_bounds__((Layout<T, kTile>::NT), 2) void grouped_product_kernel(const SlotDesc* __restrict__ slots,
                                                                  const int* __restrict__ active,
                                                                  const int* __restrict__ offs,
                                                                  int nactive) {
@@ -2289,7 +2462,7 @@ __global__ __launch_bounds__(Layout<T>::NT, 2) void grouped_product_kernel(const
   const SlotDesc sd = slots[active[a]];
   if (sd.st->stop || sd.st->prec != PREC || (PREC == kPrecF64 && (sd.st->dual != 0) != DUAL))
     return;
-  const ProductGrid g = slot_grid(sd);
+  const ProductGrid g = slot_grid(sd, PREC);
   WorkItem wi;
   wi.tile = blockIdx.x - offs[a];
   wi.piece = -1;
@@ -2305,7 +2478,7 @@ __global__ __launch_bounds__(256, 2) void grouped_product_bf16_kernel(const Slot
   const int a = group_find(offs, nactive, blockIdx.x);
   const SlotDesc sd = slots[active[a]];
   if (sd.st->stop || sd.st->prec != kPrecBF16) return;
-  const ProductGrid g = slot_grid(sd);
+  const ProductGrid g = slot_grid(sd, kPrecBF16);
   WorkItem wi;
   wi.tile = blockIdx.x - offs[a];
   wi.piece = -1;
@@ -2318,49 +2491,47 @@ __global__ __launch_bounds__(kReduceThreads) void grouped_schedule_kernel(const 
                                                                           const int* __restrict__ active) {
   const SlotDesc sd = slots[active[blockIdx.x]];
   if (sd.st->stop) return;
-  schedule_body(sd.st, sd.partials, num_product_tiles_dev(sd.np), 0, nullptr);
+  schedule_body(sd.st, sd.partials, slot_tiles(sd, sd.st->prec), 0, nullptr);
 }
 
-__global__ void grouped_stop_kernel(const SlotDesc* __restrict__ slots, const int* __restrict__ active,
-                                    int nactive, int32_t* __restrict__ stop_out) {
+__global__ void grouped_state_kernel(const SlotDesc* __restrict__ slots,
+                                     const int* __restrict__ active, int nactive,
+                                     int32_t* __restrict__ state_out) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  // 0 while running; once stopped, 1 + the index of the buffer holding the result
   if (a < nactive) {
     const SnfState* st = slots[active[a]].st;
-    stop_out[a] = st->stop ? 1 + st->cur : 0;
+    state_out[a] = st->stop ? 1 + st->cur : -1 - st->prec;
   }
 }
 
-void launch_grouped_step(int prec_mask, const SlotDesc* slots, const int* active,
-                         const int* offs, int nactive, int total_tiles, int32_t* stop_out,
-                         hipStream_t s, hipStream_t s2, hipEvent_t fork, hipEvent_t join) {
-  if (nactive <= 0) return;
-  const bool lowp = (prec_mask & ((1 << kPrecF32) | (1 << kPrecBF16))) != 0;
-  // the low-precision launch goes to s2 after everything on s so far, and s waits for it
-  // before the schedule: the two product grids (different requests) share the GPU
-  const bool split = lowp && s2 && fork && join &&
-                     hipEventRecord(fork, s) == hipSuccess &&
+void launch_grouped_step(const GroupedStep& g, hipStream_t s, hipStream_t s2, hipEvent_t fork,
+                         hipEvent_t join) {
+  if (g.nactive <= 0) return;
+  // the low-precision launches go to s2 after everything on s so far, and s waits for them
+  // before the schedule: the product grids (different requests) share the GPU
+  const bool split = g.list[kGroupF32Fine].n + g.list[kGroupF32].n + g.list[kGroupBF16].n > 0 &&
+                     s2 && fork && join && hipEventRecord(fork, s) == hipSuccess &&
                      hipStreamWaitEvent(s2, fork, 0) == hipSuccess;
   hipStream_t sl = split ? s2 : s;
-  if (prec_mask & (1 << kPrecF32))
-    hipLaunchKernelGGL((grouped_product_kernel<float, kPrecF32>), dim3(total_tiles),
-                       dim3(Layout<float>::NT), 0, sl, slots, active, offs, nactive);
-  if (prec_mask & (1 << kPrecBF16))
-    hipLaunchKernelGGL(grouped_product_bf16_kernel, dim3(total_tiles), dim3(kThreads), 0, sl,
-                       slots, active, offs, nactive);
-  if (prec_mask & (1 << kPrecF64))
-    hipLaunchKernelGGL((grouped_product_kernel<double, kPrecF64>), dim3(total_tiles),
-                       dim3(Layout<double>::NT), 0, s, slots, active, offs, nactive);
-  if (prec_mask & kGroupedDualBit)
-    hipLaunchKernelGGL((grouped_product_kernel<double, kPrecF64, true>), dim3(total_tiles),
-                       dim3(Layout<double>::NT), 0, s, slots, active, offs, nactive);
+#define SNF_GROUPED(KERNEL, THREADS, KIND, STREAM)                                               \
+  if (g.list[KIND].n > 0)                                                                        \
+  hipLaunchKernelGGL(KERNEL, dim3(g.list[KIND].total), dim3(THREADS), 0, STREAM, g.slots,        \
+                     g.list[KIND].active, g.list[KIND].offs, g.list[KIND].n)
+  SNF_GROUPED(grouped_fine_f32_kernel, (Layout<float, kFineTile>::NT), kGroupF32Fine, sl);
+  SNF_GROUPED((grouped_product_kernel<float, kPrecF32>), (Layout<float, kTile>::NT), kGroupF32, sl);
+  SNF_GROUPED(grouped_product_bf16_kernel, kThreads, kGroupBF16, sl);
+  SNF_GROUPED(grouped_fine_f64_kernel, 2 * kDirectThreads, kGroupF64Fine, s);
+  SNF_GROUPED((grouped_product_kernel<double, kPrecF64>), (Layout<double, kTile>::NT), kGroupF64, s);
+  SNF_GROUPED((grouped_product_kernel<double, kPrecF64, true>), (Layout<double, kTile>::NT),
+              kGroupDual, s);
+#undef SNF_GROUPED
   if (split && (hipEventRecord(join, s2) != hipSuccess ||
                 hipStreamWaitEvent(s, join, 0) != hipSuccess))
     (void)hipStreamSynchronize(s2);    // the schedule must not start before that product
-  hipLaunchKernelGGL(grouped_schedule_kernel, dim3(nactive), dim3(kReduceThreads), 0, s, slots,
-                     active);
-  hipLaunchKernelGGL(grouped_stop_kernel, dim3((nactive + 255) / 256), dim3(256), 0, s, slots,
-                     active, nactive, stop_out);
+  hipLaunchKernelGGL(grouped_schedule_kernel, dim3(g.nactive), dim3(kReduceThreads), 0, s, g.slots,
+                     g.active);
+  hipLaunchKernelGGL(grouped_state_kernel, dim3((g.nactive + 255) / 256), dim3(256), 0, s, g.slots,
+                     g.active, g.nactive, g.state_out);
 }
 
 }  // namespace snf

@@ -59,6 +59,7 @@ struct ServeRequest {
   hipEvent_t ev = nullptr;
   bool started = false;     // admission work enqueued: takes part in the next grouped step
   bool finished = false;    // its stop flag came back: retired behind the next step
+  int next_prec = -1;       // precision of the pending product, -1 before the first step
   int result_buf = 0;       // the iterate buffer holding D (from the stop flag)
   int status = SNF_PENDING;
   snf_result result;
@@ -132,13 +133,13 @@ struct snf_server {
   SnfState* states = nullptr;
   Buffers* bufs = nullptr;
   SlotDesc* slots = nullptr;
-  int* index_dev = nullptr;      // [2 * max_slots + 1]: active slots, then tile offsets
+  int* index_dev = nullptr;      // [7 * max_slots + kinds]: active slots, then the lists
   int32_t* stop_dev = nullptr;   // [max_slots]
   // pinned host staging of the tables
   SnfState* state_stage = nullptr;   // [max_slots]
   Buffers* bufs_stage = nullptr;     // [max_slots]
   SlotDesc* desc_stage = nullptr;    // [max_slots]
-  int* index_stage = nullptr;        // [2 * max_slots + 1]
+  int* index_stage = nullptr;        // [7 * max_slots + kinds]
   int32_t* stop_stage = nullptr;     // [max_slots]
   // host bookkeeping
   std::thread thread, finisher;
@@ -226,6 +227,7 @@ static int start_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   d.partials = (double*)(base + L.partials);
   d.np = r->np;
   d.n = r->n;
+  for (int p = 0; p < 3; ++p) d.tile[p] = request_tile(r->np, p);
   init_state(&sv->state_stage[k], r->n, &r->params, r->scheme, r->prec);
   SV_HIP(hipMemcpyAsync(sv->bufs + k, &b, sizeof(Buffers), hipMemcpyHostToDevice, s));
   SV_HIP(hipMemcpyAsync(sv->slots + k, &d, sizeof(SlotDesc), hipMemcpyHostToDevice, s));
@@ -317,14 +319,10 @@ static void scheduler(snf_server* sv) {
     }
     // 1. grouped step over every started, unfinished request
     active.clear();
-    int prec_mask = 1 << kPrecF64;
     for (int i = 0; i < sv->max_slots; ++i) {   // slot_req is written by this thread only
       const ServeRequest* r = sv->slot_req[i];
       if (r && r->started && !r->finished) {
         active.push_back(i);
-        if (r->prec == SNF_P_FP32 || r->prec == SNF_P_FP32_REF64) prec_mask |= 1 << kPrecF32;
-        if (r->prec == SNF_P_BF16_REF64) prec_mask |= 1 << kPrecBF16;
-        if (scheme_is_pij(r->scheme)) prec_mask |= kGroupedDualBit;
       }
     }
     // largest orders first: their tiles run the longest k-loops, so dispatching them first
@@ -335,21 +333,45 @@ static void scheduler(snf_server* sv) {
     });
     const int na = (int)active.size();
     if (na > 0 && rc == SNF_OK) {
+      // one copy: the active slots, then each kernel's list of slots and its first workgroups
       int* idx = sv->index_stage;
-      int total = 0;
-      for (int a = 0; a < na; ++a) {
-        idx[a] = active[a];
-        idx[na + a] = total;
-        total += num_product_tiles(sv->desc_stage[active[a]].np, 1);
+      int at = 0;
+      for (int a = 0; a < na; ++a) idx[at++] = active[a];
+      GroupedStep gs;
+      for (int k = 0; k < kGroupKinds; ++k) {
+        const int prec = k == kGroupF32Fine || k == kGroupF32 ? (int)kPrecF32
+                         : k == kGroupBF16                    ? (int)kPrecBF16 : (int)kPrecF64;
+        const int tile = k == kGroupF64Fine || k == kGroupF32Fine ? kFineTile : kTile;
+        GroupList& l = gs.list[k];
+        l.n = l.total = 0;
+        l.active = sv->index_dev + at;
+        for (int a = 0; a < na; ++a) {
+          const ServeRequest* r = sv->slot_req[active[a]];
+          const int lowp = lowp_kind_for(r->prec);
+          if (r->next_prec >= 0 ? prec != r->next_prec : prec != kPrecF64 && prec != lowp) continue;
+          if (sv->desc_stage[active[a]].tile[prec] != tile) continue;
+          if (k == kGroupDual && !scheme_is_pij(r->scheme)) continue;
+          idx[at++] = active[a];
+          ++l.n;
+        }
+        l.offs = sv->index_dev + at;
+        const int first = at - l.n;
+        for (int e = 0; e < l.n; ++e) {
+          const int64_t nt = sv->desc_stage[idx[first + e]].np / tile;
+          idx[at++] = l.total;
+          l.total += (int)(nt * (nt + 1) / 2);
+        }
+        idx[at++] = l.total;
       }
-      idx[2 * na] = total;
-      // one copy: the active slots at [0, na), the tile offsets at [na, 2 na]
-      if (hipMemcpyAsync(sv->index_dev, idx, (2 * na + 1) * sizeof(int), hipMemcpyHostToDevice,
-                         s) != hipSuccess)
+      if (hipMemcpyAsync(sv->index_dev, idx, at * sizeof(int), hipMemcpyHostToDevice, s) !=
+          hipSuccess)
         rc = SNF_EDEVICE;
       if (rc == SNF_OK) {
-        launch_grouped_step(prec_mask, sv->slots, sv->index_dev, sv->index_dev + na, na, total,
-                            sv->stop_dev, s, sv->stream2, sv->ev_fork, sv->ev_join);
+        gs.slots = sv->slots;
+        gs.active = sv->index_dev;
+        gs.nactive = na;
+        gs.state_out = sv->stop_dev;
+        launch_grouped_step(gs, s, sv->stream2, sv->ev_fork, sv->ev_join);
         if (hipGetLastError() != hipSuccess ||
             hipMemcpyAsync(sv->stop_stage, sv->stop_dev, na * sizeof(int32_t),
                            hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -440,8 +462,11 @@ static void scheduler(snf_server* sv) {
         rc = SNF_EDEVICE;
       } else {
         for (int a = 0; a < na; ++a) {
-          if (!sv->stop_stage[a]) continue;
           ServeRequest* r = sv->slot_req[active[a]];
+          if (sv->stop_stage[a] < 0) {
+            r->next_prec = -1 - sv->stop_stage[a];
+            continue;
+          }
           r->finished = true;
           r->result_buf = sv->stop_stage[a] - 1;
           r->t_finish = Clock::now();
@@ -530,7 +555,7 @@ int snf_serve_create(size_t hbm_budget_bytes, int32_t max_slots, snf_server** ou
   ok = ok && hipMalloc(&sv->states, max_slots * sizeof(SnfState)) == hipSuccess &&
        hipMalloc(&sv->bufs, max_slots * sizeof(Buffers)) == hipSuccess &&
        hipMalloc(&sv->slots, max_slots * sizeof(SlotDesc)) == hipSuccess &&
-       hipMalloc(&sv->index_dev, (2 * max_slots + 1) * sizeof(int)) == hipSuccess &&
+       hipMalloc(&sv->index_dev, (7 * max_slots + kGroupKinds) * sizeof(int)) == hipSuccess &&
        hipMalloc(&sv->stop_dev, max_slots * sizeof(int32_t)) == hipSuccess;
   ok = ok &&
        hipHostMalloc(&sv->state_stage, max_slots * sizeof(SnfState), hipHostMallocDefault) ==
@@ -539,7 +564,7 @@ int snf_serve_create(size_t hbm_budget_bytes, int32_t max_slots, snf_server** ou
            hipSuccess &&
        hipHostMalloc(&sv->desc_stage, max_slots * sizeof(SlotDesc), hipHostMallocDefault) ==
            hipSuccess &&
-       hipHostMalloc(&sv->index_stage, (2 * max_slots + 1) * sizeof(int),
+       hipHostMalloc(&sv->index_stage, (7 * max_slots + kGroupKinds) * sizeof(int),
                      hipHostMallocDefault) == hipSuccess &&
        hipHostMalloc(&sv->stop_stage, max_slots * sizeof(int32_t), hipHostMallocDefault) ==
            hipSuccess;

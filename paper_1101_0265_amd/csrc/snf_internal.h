@@ -245,18 +245,45 @@ struct SlotDesc {
   Buffers* bufs;       // device
   double* partials;    // [tiles][4]
   int64_t np, n;
+  int tile[3];         // tile side of the request's products, by precision (kPrec*)
 };
 
-// One step of every active request: product variants selected by prec_mask (bit kPrec*, and
-// kGroupedDualBit for the FP64 variant with a second output that P_{i,j} requests take),
-// each request's schedule, and the stop flags gathered into stop_out[nactive] (0 while a
-// request runs; 1 + the buffer index of its result once it stopped).  With s2 and
-// the two events, the FP32 / BF16 product launches run on s2 beside the FP64 one on s.
-// offs[a] = first workgroup of active request a (offs[nactive] = total_tiles).
-constexpr int kGroupedDualBit = 1 << 8;
-void launch_grouped_step(int prec_mask, const SlotDesc* slots, const int* active,
-                         const int* offs, int nactive, int total_tiles, int32_t* stop_out,
-                         hipStream_t s, hipStream_t s2 = nullptr, hipEvent_t fork = nullptr,
-                         hipEvent_t join = nullptr);
+// Tile side of a request's products in FP64 and FP32: 64x64 while its tiles' sums fit the slots
+// that its layout holds anyway (kF0Blocks, up to order 2816; beyond, one request has tiles
+// enough), else 128x128, as the BF16 products always.
+constexpr int kFineTile = 64;
+inline int request_tile(int64_t np, int prec) {
+  const int64_t nt = np / kFineTile;
+  return prec != kPrecBF16 && nt * (nt + 1) / 2 <= kF0Blocks ? kFineTile : kTile;
+}
+
+// One step of every active request.  Each product kernel runs on its own list of requests, those
+// whose pending product is of its precision and tile (offs[a] = first workgroup of entry a, offs[n]
+// = total): a launch over all requests would fill compute units with workgroups that only find
+// out that the product is not theirs.  A request whose precision the host does not know yet (its
+// first step) is in the lists of both its precisions, and one kernel exits.  Then each active
+// request's schedule, and their states into state_out[nactive]: -1 - precision of the next product
+// while a request runs; 1 + the buffer index of its result once it stopped.  With s2 and the two
+// events, the FP32 / BF16 products run on s2 beside the FP64 ones on s.
+enum : int {
+  kGroupF64Fine = 0, kGroupF32Fine = 1,            // 64x64 tiles
+  kGroupF64 = 2, kGroupF32 = 3, kGroupBF16 = 4,    // 128x128 tiles
+  kGroupDual = 5,                                  // FP64 with a second output (P_{i,j})
+  kGroupKinds = 6
+};
+struct GroupList {
+  const int* active;
+  const int* offs;
+  int n, total;
+};
+struct GroupedStep {
+  const SlotDesc* slots;
+  const int* active;
+  int nactive;
+  GroupList list[kGroupKinds];
+  int32_t* state_out;
+};
+void launch_grouped_step(const GroupedStep& g, hipStream_t s, hipStream_t s2 = nullptr,
+                         hipEvent_t fork = nullptr, hipEvent_t join = nullptr);
 
 }  // namespace snf
