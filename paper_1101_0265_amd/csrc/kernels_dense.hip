@@ -112,19 +112,15 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
 // ---------------------------------------------------------------------------------------
 // f0: X_0 = f_0(F)
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void f0_kernel(const double* __restrict__ F, int64_t n,
-                                                 int64_t ld, int64_t np,
-                                                 const SnfState* __restrict__ st,
-                                                 const Buffers* __restrict__ bufs,
-                                                 int lowp_kind, double* __restrict__ partials) {
+__device__ __forceinline__ void f0_body(const double* __restrict__ F, int64_t n, int64_t ld,
+                                        int64_t np, const SnfHeader& h, double* __restrict__ X,
+                                        void* __restrict__ LP, int lowp_kind,
+                                        double* __restrict__ partials) {
   __shared__ double tile[32][33];
   __shared__ double red[24];
-  const int alg1 = (st->scheme == SNF_MCWEENY || st->scheme == SNF_SNF_FIXMU || st->pmm_m ||
-                    st->pij_i);
-  const double lmin = st->lambda_min, lmax = st->lambda_max, mu = st->mu, gamma = st->gamma;
-  const double xs = st->xstar;
-  double* X = bufs->x[st->cur];
-  void* LP = bufs->lp[st->cur];
+  const int alg1 = (h.scheme == SNF_MCWEENY || h.scheme == SNF_SNF_FIXMU || h.pmm_m || h.pij_i);
+  const double lmin = h.lambda_min, lmax = h.lambda_max, mu = h.mu, gamma = h.gamma;
+  const double xs = h.xstar;
   const int64_t nt = np / 32;
   const int64_t ntiles = nt * nt;
   double t1 = 0.0, t2 = 0.0;
@@ -168,6 +164,14 @@ __global__ __launch_bounds__(256) void f0_kernel(const double* __restrict__ F, i
     partials[blockIdx.x * 4 + 2] = t2;
     partials[blockIdx.x * 4 + 3] = 0.0;
   }
+}
+
+__global__ __launch_bounds__(256) void f0_kernel(const double* __restrict__ F, int64_t n,
+                                                 int64_t ld, int64_t np,
+                                                 const SnfState* __restrict__ st,
+                                                 const Buffers* __restrict__ bufs,
+                                                 int lowp_kind, double* __restrict__ partials) {
+  f0_body(F, n, ld, np, *st, bufs->x[st->cur], bufs->lp[st->cur], lowp_kind, partials);
 }
 
 void launch_f0(const double* F, int64_t n, int64_t ld, int64_t np, SnfState* st,
@@ -2335,8 +2339,11 @@ __device__ __forceinline__ ProductGrid slot_grid(const SlotDesc& sd, int prec) {
 
 // Requests with 64x64 tiles.  A group of requests seldom fills the chip evenly: with 128x128
 // tiles a step lasted as long as the longest tile of its largest request (FP64 at n = 2048: 440
-// us on one compute unit, FP32 220), the rest waiting.  FP32: the same sum order per entry in a
-// quarter of the tile, four waves of 32x32.
+// us on one compute unit, FP32 220), the rest waiting.  Bursts, 128x128 to 64x64: 48 requests of
+// order 64 to 2048 with an FP32 start 19.6 to 18.0 ms, 20 SP2 up to 700 7.6 to 5.1, 40 in FP64 up
+// to 2048 15.6 to 14.9; the matrix cores are busy 65% of such a step.  FP32: the same sum order per
+// entry in a quarter of the tile, four waves of 32x32 (k-panels of 16 rather than 32, or two waves
+// of 64x32: no faster).
 __global__ __launch_bounds__((Layout<float, kFineTile>::NT), 2) void grouped_fine_f32_kernel(
     const SlotDesc* __restrict__ slots, const int* __restrict__ active,
     const int* __restrict__ offs, int nactive) {
@@ -2492,6 +2499,52 @@ __global__ __launch_bounds__(kReduceThreads) void grouped_schedule_kernel(const 
   const SlotDesc sd = slots[active[blockIdx.x]];
   if (sd.st->stop) return;
   schedule_body(sd.st, sd.partials, slot_tiles(sd, sd.st->prec), 0, nullptr);
+}
+
+// Admission of a request: its tables from the kernel arguments and X_0 = f_0(F) straight from F.
+// A burst waits for its admissions one after the other, so their count of launches and copies is
+// what bounds it: with a copy for each of the three tables and for F, and a retirement that copied
+// the whole state (the full log) after D, 48 requests of order 64 to 256 took 4.8 ms, with one
+// launch each 2.8.  The grid has no more workgroups than X_0 has 32x32 tiles.
+__global__ __launch_bounds__(256) void serve_admit_kernel(ServeAdmit a, const double* __restrict__ F,
+                                                          int lowp_kind) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *static_cast<SnfHeader*>(a.desc.st) = a.header;
+    *a.desc.bufs = a.bufs;
+    *a.slot = a.desc;
+  }
+  f0_body(F, a.desc.n, a.desc.n, a.desc.np, a.header, a.bufs.x[0], a.bufs.lp[0], lowp_kind,
+          a.desc.partials);
+}
+
+int launch_serve_admit(const ServeAdmit& a, const double* F, int lowp_kind, hipStream_t s) {
+  const int64_t nt = a.desc.np / 32;
+  const int blocks = (int)(nt * nt < kF0Blocks ? nt * nt : kF0Blocks);
+  hipLaunchKernelGGL(serve_admit_kernel, dim3(blocks), dim3(256), 0, s, a, F, lowp_kind);
+  launch_schedule(a.desc.st, a.desc.partials, blocks, 1, s);
+  return blocks;
+}
+
+// Retirement: D, and the final state into host-visible memory (the header and the log written).
+__global__ __launch_bounds__(256) void serve_retire_kernel(const SnfState* __restrict__ st,
+                                                           const Buffers* __restrict__ bufs,
+                                                           int64_t n, int64_t np,
+                                                           double* __restrict__ D, int64_t ld,
+                                                           SnfState* __restrict__ out) {
+  copy_rows(bufs->x[st->cur], np, D, ld, n);
+  if (blockIdx.x != 0) return;
+  const unsigned* h = (const unsigned*)static_cast<const SnfHeader*>(st);
+  unsigned* o = (unsigned*)static_cast<SnfHeader*>(out);
+  for (int i = threadIdx.x; i < (int)(sizeof(SnfHeader) / 4); i += 256) o[i] = h[i];
+  const int words = min(st->nlog, SNF_LOG_MAX) * (int)(sizeof(snf_log_rec) / 4);
+  for (int i = threadIdx.x; i < words; i += 256)
+    ((unsigned*)out->log)[i] = ((const unsigned*)st->log)[i];
+}
+
+void launch_serve_retire(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
+                         double* D, int64_t ld, SnfState* out, hipStream_t s) {
+  hipLaunchKernelGGL(serve_retire_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, st, bufs_dev, n, np,
+                     D, ld, out);
 }
 
 __global__ void grouped_state_kernel(const SlotDesc* __restrict__ slots,

@@ -3,13 +3,14 @@
 // A scheduler thread owns three HIP streams and a device arena (the HBM budget).  Each loop
 // turn
 //   1. launches one grouped step over every started request: the product tiles of all of
-//      them in one launch per precision variant (FP64 and low precision on two streams),
-//      then every request's schedule, then a gather of their stop flags;
+//      them in one launch per precision and tile (FP64 and low precision on two streams),
+//      then every request's schedule, then a gather of their states (running, with the
+//      precision of the next product, or stopped);
 //   2. while that step runs, enqueues on the third stream the retirement of the requests
-//      whose stop flag came back from the previous step (D and the result to the host,
+//      that came back stopped from the previous step (D and the result to the host,
 //      arena and slot released) and admits queued requests (FIFO) while a slot is free and
 //      the arena can hold the request's workspace (F in, f_0 and the initial schedule);
-//   3. waits for the step and reads its stop flags.
+//   3. waits for the step and reads its states.
 // Nothing is allocated on the device while serving (the arena is sub-allocated), so a
 // finishing request never waits on a device-wide free.
 #include <hip/hip_runtime.h>
@@ -51,16 +52,16 @@ struct ServeRequest {
   double* F_pin = nullptr;
   double* D_pin = nullptr;
   SnfState* st_pin = nullptr;
-  // submitted; admitted (slot and memory taken); finished (the scheduler read the stop flag
-  // of its last step); done (result complete on the host)
+  // submitted; admitted (slot and memory taken); finished (the scheduler saw its
+  // last step stop it); done (result complete on the host)
   Clock::time_point t_submit, t_admit, t_finish, t_done;
   int slot = -1;
   size_t off = 0, bytes = 0;
   hipEvent_t ev = nullptr;
   bool started = false;     // admission work enqueued: takes part in the next grouped step
-  bool finished = false;    // its stop flag came back: retired behind the next step
+  bool finished = false;    // it came back stopped: retired behind the next step
   int next_prec = -1;       // precision of the pending product, -1 before the first step
-  int result_buf = 0;       // the iterate buffer holding D (from the stop flag)
+  int result_buf = 0;       // the iterate buffer holding D (from its last state)
   int status = SNF_PENDING;
   snf_result result;
 };
@@ -121,7 +122,7 @@ struct snf_server {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipStream_t stream3 = nullptr;      // admissions and retirements, beside the steps
   hipEvent_t ev_adm = nullptr;        // recorded on stream3 behind the latest admissions
-  hipEvent_t ev_step = nullptr;       // recorded behind a step's stop flags
+  hipEvent_t ev_step = nullptr;       // recorded behind a step's states
   size_t budget = 0;
   int max_slots = 0;
   char* arena_base = nullptr;     // device arena (the HBM budget)
@@ -136,7 +137,7 @@ struct snf_server {
   int* index_dev = nullptr;      // [7 * max_slots + kinds]: active slots, then the lists
   int32_t* stop_dev = nullptr;   // [max_slots]
   // pinned host staging of the tables
-  SnfState* state_stage = nullptr;   // [max_slots]
+  SnfState state_stage;              // the request being admitted
   Buffers* bufs_stage = nullptr;     // [max_slots]
   SlotDesc* desc_stage = nullptr;    // [max_slots]
   int* index_stage = nullptr;        // [7 * max_slots + kinds]
@@ -209,8 +210,9 @@ static hipEvent_t take_event_locked(snf_server* sv) {
     if ((call) != hipSuccess) return SNF_EDEVICE; \
   } while (0)
 
-// Admission of one request into slot r->slot: tables, F into x[2] (row stride n), f_0 and
-// the initial schedule -- all stream-ordered, no host waits.
+// Admission of one request into slot r->slot: F from the caller's device memory, or through x[2]
+// (row stride n); tables and f_0 in one launch and the initial schedule -- all stream-ordered, no
+// host waits.
 static int start_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   const int k = r->slot;
   const RequestLayout L = request_layout(r->n, r->prec, request_buffers(r->scheme));
@@ -228,19 +230,19 @@ static int start_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   d.np = r->np;
   d.n = r->n;
   for (int p = 0; p < 3; ++p) d.tile[p] = request_tile(r->np, p);
-  init_state(&sv->state_stage[k], r->n, &r->params, r->scheme, r->prec);
-  SV_HIP(hipMemcpyAsync(sv->bufs + k, &b, sizeof(Buffers), hipMemcpyHostToDevice, s));
-  SV_HIP(hipMemcpyAsync(sv->slots + k, &d, sizeof(SlotDesc), hipMemcpyHostToDevice, s));
-  SV_HIP(hipMemcpyAsync(sv->states + k, &sv->state_stage[k], sizeof(SnfState),
-                        hipMemcpyHostToDevice, s));
-  const size_t fbytes = (size_t)r->n * r->n * sizeof(double);
-  if (r->device_io)
-    SV_HIP(hipMemcpyAsync(b.x[2], r->F_dev, fbytes, hipMemcpyDeviceToDevice, s));
-  else
-    SV_HIP(hipMemcpyAsync(b.x[2], r->F_pin, fbytes, hipMemcpyHostToDevice, s));
-  launch_f0(b.x[2], r->n, r->n, r->np, sv->states + k, sv->bufs + k, lowp_kind_for(r->prec),
-            d.partials, s);
-  launch_schedule(sv->states + k, d.partials, kF0Blocks, 1, s);
+  ServeAdmit ad;
+  init_state(&sv->state_stage, r->n, &r->params, r->scheme, r->prec);
+  ad.header = sv->state_stage;
+  ad.bufs = b;
+  ad.desc = d;
+  ad.slot = sv->slots + k;
+  const double* F = r->F_dev;
+  if (!r->device_io) {
+    SV_HIP(hipMemcpyAsync(b.x[2], r->F_pin, (size_t)r->n * r->n * sizeof(double),
+                          hipMemcpyHostToDevice, s));
+    F = b.x[2];
+  }
+  launch_serve_admit(ad, F, lowp_kind_for(r->prec), s);
   SV_HIP(hipGetLastError());
   return SNF_OK;
 }
@@ -252,16 +254,15 @@ static int retire_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   const int k = r->slot;
   const Buffers& b = sv->bufs_stage[k];
   if (r->device_io) {
-    launch_copy_out(sv->states + k, sv->bufs + k, r->n, r->np, r->D_dev, r->n, s);
+    launch_serve_retire(sv->states + k, sv->bufs + k, r->n, r->np, r->D_dev, r->n, r->st_pin, s);
   } else {
     // D leaves through an iterate buffer other than the one holding it (x[2] unless D is
     // there: a P_{m,m} or P_{i,j} iteration rotates its result over all four)
     double* stage = b.x[r->result_buf == 2 ? 0 : 2];
-    launch_copy_out(sv->states + k, sv->bufs + k, r->n, r->np, stage, r->n, s);
+    launch_serve_retire(sv->states + k, sv->bufs + k, r->n, r->np, stage, r->n, r->st_pin, s);
     SV_HIP(hipMemcpyAsync(r->D_pin, stage, (size_t)r->n * r->n * sizeof(double),
                           hipMemcpyDeviceToHost, s));
   }
-  SV_HIP(hipMemcpyAsync(r->st_pin, sv->states + k, sizeof(SnfState), hipMemcpyDeviceToHost, s));
   SV_HIP(hipEventRecord(r->ev, s));
   SV_HIP(hipGetLastError());
   return SNF_OK;
@@ -300,11 +301,11 @@ static void finisher(snf_server* sv) {
 }
 
 // One iteration: launch the grouped step over the requests started earlier; while it runs,
-// enqueue on a third stream the retirement of the requests whose stop flag came back from the
+// enqueue on a third stream the retirement of the requests that came back stopped from the
 // previous step and the admission of pending requests into free slots (none of them is in
-// the step, so both overlap its products); then wait for the step and read its stop flags.
+// the step, so both overlap its products); then wait for the step and read its states.
 // The next step waits for the admissions (event).  A request joins the step after the one
-// during which it was admitted and is copied out during the step after its stop flag.
+// during which it was admitted and is copied out during the step after it stopped.
 static void scheduler(snf_server* sv) {
   (void)hipSetDevice(sv->device);
   std::vector<ServeRequest*> admitted, finished;
@@ -452,7 +453,7 @@ static void scheduler(snf_server* sv) {
       if (hipEventRecord(sv->ev_adm, s3) != hipSuccess) rc = SNF_EDEVICE;
       adm_pending = true;
     }
-    // 4. wait for the step (and the work enqueued behind it); read its stop flags
+    // 4. wait for the step (and the work enqueued behind it); read its states
     if (rc == SNF_OK && na > 0) {
       // poll the step's event: a blocking wait would add the wake-up latency of the
       // runtime's sleep to every step
@@ -558,8 +559,6 @@ int snf_serve_create(size_t hbm_budget_bytes, int32_t max_slots, snf_server** ou
        hipMalloc(&sv->index_dev, (7 * max_slots + kGroupKinds) * sizeof(int)) == hipSuccess &&
        hipMalloc(&sv->stop_dev, max_slots * sizeof(int32_t)) == hipSuccess;
   ok = ok &&
-       hipHostMalloc(&sv->state_stage, max_slots * sizeof(SnfState), hipHostMallocDefault) ==
-           hipSuccess &&
        hipHostMalloc(&sv->bufs_stage, max_slots * sizeof(Buffers), hipHostMallocDefault) ==
            hipSuccess &&
        hipHostMalloc(&sv->desc_stage, max_slots * sizeof(SlotDesc), hipHostMallocDefault) ==
@@ -698,7 +697,6 @@ int snf_serve_destroy(snf_server* sv) {
   if (sv->slots) (void)hipFree(sv->slots);
   if (sv->index_dev) (void)hipFree(sv->index_dev);
   if (sv->stop_dev) (void)hipFree(sv->stop_dev);
-  if (sv->state_stage) (void)hipHostFree(sv->state_stage);
   if (sv->bufs_stage) (void)hipHostFree(sv->bufs_stage);
   if (sv->desc_stage) (void)hipHostFree(sv->desc_stage);
   if (sv->index_stage) (void)hipHostFree(sv->index_stage);

@@ -248,6 +248,19 @@ struct SlotDesc {
   int tile[3];         // tile side of the request's products, by precision (kPrec*)
 };
 
+// Admission of a request in one launch and its first schedule: what its slot's tables hold, by
+// value, and X_0 from F (row stride n).
+struct ServeAdmit {
+  SnfHeader header;
+  Buffers bufs;
+  SlotDesc desc;
+  SlotDesc* slot;      // where desc goes
+};
+int launch_serve_admit(const ServeAdmit& a, const double* F, int lowp_kind, hipStream_t s);
+// D and the final state (out: host-visible) of a finished request.
+void launch_serve_retire(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
+                         double* D, int64_t ld, SnfState* out, hipStream_t s);
+
 // Tile side of a request's products in FP64 and FP32: 64x64 while its tiles' sums fit the slots
 // that its layout holds anyway (kF0Blocks, up to order 2816; beyond, one request has tiles
 // enough), else 128x128, as the BF16 products always.
