@@ -4,10 +4,10 @@
 // pair (product kernel, schedule kernel); the schedule kernel writes the next step's
 // coefficients, buffer indices and precision into the device-resident state, and sets a
 // stop flag once ||X^2 - X||_F <= tol (or an error / iteration limit).  Kernels enqueued after
-// the stop exit immediately.  The host keeps two chunks of steps in flight and reads the
-// stop flag of the older chunk from pinned memory, so the GPU never waits for the host and
-// at most one chunk of empty launches follows convergence.  At the smallest orders the whole
-// loop is one cooperative launch instead.
+// the stop exit immediately.  The host keeps a few steps in flight ahead of the step that the
+// device reports in pinned memory, so the GPU never waits for the host and few empty launches
+// follow convergence.  FP64 solves of small and middle order take one launch a step (the
+// schedule at its head), those whose iterates fit one compute unit's LDS one launch in all.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -56,7 +56,7 @@ struct Workspace {
   SnfState* state_host = nullptr;    // pinned
   SnfHeader* hdr = nullptr;          // [2] state headers of a direct solve, by step parity
   double* direct_partials = nullptr; // [2][kDirectSlots][4]
-  int32_t* flags_host = nullptr;     // pinned, [2] stop flags of in-flight chunks
+  int32_t* flags_host = nullptr;     // pinned: [0] a stop flag, [4] the step loop's progress
   double* sums_dev = nullptr;
   double* sums_host = nullptr;       // pinned
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -669,38 +669,41 @@ static int finish_direct(Workspace* w, snf_result* out, snf_log_rec* log, int32_
   return status;
 }
 
-// ---- direct solves (FP64, small and middle order) ------------------------------------------
-// The step loop of a direct solve: one launch per step, kept kDirectLead steps ahead of the
-// step the device reports to have begun (a word in host-visible memory that the step kernels
-// write), so the GPU never waits for the host and few empty launches follow the stop.
-constexpr int kDirectLead = 4;
+// ---- the step loop ------------------------------------------------------------------------
+// Steps are enqueued `lead` ahead of the one that the device reports to have begun (a word in
+// host-visible memory that the kernels write, -1 once the solve has stopped), so the GPU never
+// waits for the host and few empty launches follow the stop.  Chunks of 2 to 8 steps, two in
+// flight, each with a copy of the stop flag, left up to 15 empty steps of four launches behind a
+// solve of 19 products: with an FP32 start n = 130 0.59 ms, this 0.51; n = 300 0.66, 0.61; n =
+// 700 0.91, 0.87; from 1000 on the two are equal.
+//  * one launch a step, or short steps: four ahead;
+//  * steps of several launches above a padded order of 512: two, as an empty step costs 15 us
+//    there and a step lasts longer than the host takes for its launches (n = 1500: 1.62 ms with
+//    two, 1.66 with four; n = 130: 0.54 with two, 0.51 with four).
+constexpr int kShortLead = 2, kLongLead = 4;
+constexpr int64_t kLongLeadNp = 512;
 
-static int direct_steps(const DirectArgs& a, int tile, StepOperands ops, int max_steps,
-                        volatile int32_t* progress, const std::vector<hipEvent_t>* ev, int* slot,
-                        hipStream_t s) {
+template <typename Launch>
+static int lead_steps(int max_steps, int lead, volatile int32_t* progress, hipStream_t s, int* enqueued,
+                      const Launch& launch) {
   int enq = 0;
-  *progress = 0;
-  // (the step after the last product only advances the state)
-  while (enq <= max_steps) {
+  while (enq < max_steps) {
     int seen = *progress;
-    for (int spins = 1; seen >= 0 && enq - seen >= kDirectLead; ++spins) {
+    for (int spins = 1; seen >= 0 && enq - seen >= lead; ++spins) {
       if (spins % 4096 == 0) {                 // a device error would leave the word as it is
         const hipError_t q = hipStreamQuery(s);
-        if (q != hipErrorNotReady && q != hipSuccess) return dev_error(q, "a direct step");
-        if (q == hipSuccess && *progress == seen) return dev_error(hipErrorUnknown, "a direct step");
+        if (q != hipErrorNotReady && q != hipSuccess) return dev_error(q, "a step");
+        if (q == hipSuccess && *progress == seen) return dev_error(hipErrorUnknown, "a step");
       }
       seen = *progress;
     }
     if (seen < 0) break;
-    int op[3];
-    ops.next(op);
-    if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq], s));
-    launch_direct_step(tile, a, enq, op, s);
-    if (ev) SNF_HIP(hipEventRecord((*ev)[2 * enq + 1], s));
+    const int rc = launch(enq);
+    if (rc != SNF_OK) return rc;
     ++enq;
   }
   SNF_HIP(hipGetLastError());
-  *slot = enq & 1;
+  *enqueued = enq;
   return SNF_OK;
 }
 
@@ -767,9 +770,8 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
     SNF_HIP(hipStreamSynchronize(s));
     return finish_direct(w, out, log, log_cap, time_products, 0);
   }
-  // chunk: steps enqueued between two looks at the stop flag
-  const int chunk = np >= 2048 ? 2 : (np >= 1024 ? 4 : 8);
-  volatile int32_t* flags = w->flags_host;
+  int32_t* progress = w->flags_host + 4;
+  *(volatile int32_t*)progress = 0;
   int ev_used = 0;
   if (tile) {
     DirectArgs a;
@@ -780,17 +782,25 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
     a.hdr = w->hdr;
     a.log = w->state->log;
     a.partials = w->direct_partials;
-    a.progress = w->flags_host + 4;
+    a.progress = progress;
     a.n = n;
     a.ld = dld;
     a.nt = (int)((newton ? np : n) + tile - 1) / tile;
     SNF_HIP(hipEventRecord(w->ev[0], s));
     launch_direct_f0(a, *w->state_host, F_dev, ld, s);
-    int slot = 0;
-    rc = direct_steps(a, tile, StepOperands(scheme, per_it), max_steps, w->flags_host + 4,
-                      time_products ? &w->prod_ev : nullptr, &slot, s);
+    StepOperands ops(scheme, per_it);
+    int enq = 0;
+    // (the step after the last product only advances the state)
+    rc = lead_steps(max_steps + 1, kLongLead, a.progress, s, &enq, [&](int k) -> int {
+      int op[3];
+      ops.next(op);
+      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k], s));
+      launch_direct_step(tile, a, k, op, s);
+      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k + 1], s));
+      return SNF_OK;
+    });
     if (rc != SNF_OK) return rc;
-    launch_direct_out(a, slot, D_dev, ld, w->state_host, s);
+    launch_direct_out(a, enq & 1, D_dev, ld, w->state_host, s);
     SNF_HIP(hipGetLastError());
     SNF_HIP(hipEventRecord(w->ev[1], s));
     SNF_HIP(hipStreamSynchronize(s));
@@ -802,47 +812,36 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
     if (rc != SNF_OK) return rc;
     SNF_HIP(hipMemcpyAsync(w->state, w->state_host, sizeof(SnfState), hipMemcpyHostToDevice, s));
   } else {
-    rc = upload_buffers(w, s);
-    if (rc != SNF_OK) return out->status = rc;
-    SNF_HIP(hipMemcpyAsync(w->state, w->state_host, sizeof(SnfState), hipMemcpyHostToDevice, s));
+    SolveStart st;
+    st.header = *w->state_host;
+    for (int i = 0; i < 4; ++i) {
+      st.bufs.x[i] = w->x[i];
+      st.bufs.lp[i] = w->lp[i];
+    }
+    st.desc.st = w->state;
+    st.desc.bufs = w->bufs_dev;
+    st.desc.partials = w->partials;
+    st.desc.np = np;
+    st.desc.n = n;
+    st.slot = nullptr;
     SNF_HIP(hipEventRecord(w->ev[0], s));
-    launch_f0(F_dev, n, ld, np, w->state, w->bufs_dev, lowp_kind_for(precision), w->partials, s);
-    launch_schedule(w->state, w->partials, kF0Blocks, 1, s);
-    SNF_HIP(hipGetLastError());
-
-    // Launch-ahead loop: chunks of `chunk` steps, two chunks in flight.
+    launch_solve_start(st, F_dev, ld, lowp_kind_for(precision), s, progress);
     const bool lowp = precision != SNF_P_FP64;
     const bool pij = scheme_is_pij(scheme);
-    int enq = 0, chunks = 0, checked = 0;
-    bool stopped = false;
-    auto enqueue_chunk = [&]() -> int {
-      for (int k = 0; k < chunk && enq < max_steps; ++k, ++enq) {
-        if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used], s));
-        launch_product(kPrecF64, w->state, w->bufs_dev, grid, s);
-        if (pij) launch_product_dual(w->state, w->bufs_dev, grid, s);
-        if (lowp) launch_product(lowp_kind_for(precision), w->state, w->bufs_dev, grid, s);
-        launch_split_fixup(w->state, w->bufs_dev, grid, s);
-        if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[ev_used + 1], s));
-        if (time_products) ev_used += 2;
-        launch_schedule(w->state, w->partials, grid.partial_count, 0, s);
-      }
-      SNF_HIP(hipGetLastError());
-      SNF_HIP(hipMemcpyAsync((void*)(flags + (chunks & 1)), &w->state->stop, sizeof(int32_t),
-                             hipMemcpyDeviceToHost, s));
-      SNF_HIP(hipEventRecord(w->ev[2 + (chunks & 1)], s));
-      ++chunks;
+    int enq = 0;
+    rc = lead_steps(max_steps, np <= kLongLeadNp ? kLongLead : kShortLead, progress, s, &enq,
+                     [&](int k) -> int {
+      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k], s));
+      launch_product(kPrecF64, w->state, w->bufs_dev, grid, s);
+      if (pij) launch_product_dual(w->state, w->bufs_dev, grid, s);
+      if (lowp) launch_product(lowp_kind_for(precision), w->state, w->bufs_dev, grid, s);
+      launch_split_fixup(w->state, w->bufs_dev, grid, s);
+      if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k + 1], s));
+      launch_schedule(w->state, w->partials, grid.partial_count, 0, s, nullptr, progress, k + 1);
       return SNF_OK;
-    };
-    rc = enqueue_chunk();
+    });
     if (rc != SNF_OK) return out->status = rc;
-    while (!stopped && enq < max_steps) {
-      rc = enqueue_chunk();
-      if (rc != SNF_OK) return out->status = rc;
-      // wait for the older in-flight chunk and look at its stop flag
-      SNF_HIP(hipEventSynchronize(w->ev[2 + (checked & 1)]));
-      stopped = flags[checked & 1] != 0;
-      ++checked;
-    }
+    if (time_products) ev_used = 2 * enq;
   }
   // subspace correction of the solve's result, then its FP64 refinement
   std::unique_ptr<SnfState> main_st;
@@ -858,6 +857,9 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
       const int target = main_st->cur == 0 ? 1 : 0;
       rc = newton_correct(w, F_dev, n, ld, np, params, precision, main_st->cur, target, s, &ns);
       if (rc != SNF_OK) return rc;
+      // (steps enqueued between two looks at the stop flag)
+      const int chunk = np >= 2048 ? 2 : (np >= 1024 ? 4 : 8);
+      volatile int32_t* flags = w->flags_host;
       bool rstop = false;
       for (int renq = 0; !rstop && renq < params->max_iter + 1;) {
         for (int k = 0; k < chunk && renq < params->max_iter + 1; ++k, ++renq) {
@@ -873,10 +875,9 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
       }
     }
   }
-  launch_copy_out(w->state, w->bufs_dev, n, np, D_dev, ld, s);
+  launch_solve_finish(w->state, w->bufs_dev, n, np, D_dev, ld, w->state_host, s);
   SNF_HIP(hipGetLastError());
   SNF_HIP(hipEventRecord(w->ev[1], s));
-  SNF_HIP(hipMemcpyAsync(w->state_host, w->state, sizeof(SnfState), hipMemcpyDeviceToHost, s));
   SNF_HIP(hipStreamSynchronize(s));
 
   const SnfState* st = main_st ? main_st.get() : w->state_host;

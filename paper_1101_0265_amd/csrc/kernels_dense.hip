@@ -1288,7 +1288,9 @@ __device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ hs,
 // chain of dependent single-thread loads and stores to device memory.
 __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
                                               const double* __restrict__ partials, int count,
-                                              int init, SnfHeader* __restrict__ host) {
+                                              int init, SnfHeader* __restrict__ host,
+                                              int32_t* __restrict__ progress = nullptr,
+                                              int done = 0) {
   __shared__ double red[24];
   __shared__ __attribute__((aligned(16))) SnfHeader hs;
   static_assert(sizeof(SnfHeader) % 4 == 0, "copied by words");
@@ -1302,6 +1304,10 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
     t1 += partials[i * 4 + 1];
     t2 += partials[i * 4 + 2];
   }
+  // one thread tells the host, ahead of the schedule: the store's way to host memory (1.5 us at
+  // the end of the kernel) passes beside it
+  const bool teller = progress && threadIdx.x == kReduceThreads - 64;
+  if (teller) __hip_atomic_store(progress, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
   if (threadIdx.x == 0) schedule_step(&hs, sg->log, e2, t1, t2, init);
   __syncthreads();
@@ -1309,6 +1315,8 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
     gb[i] = hb[i];
     if (host) ((unsigned*)host)[i] = hb[i];
   }
+  if (teller && hs.stop)
+    __hip_atomic_store(progress, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2033,15 +2041,17 @@ int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D,
 __global__ __launch_bounds__(kReduceThreads) void schedule_kernel(SnfState* __restrict__ s,
                                                                   const double* __restrict__ partials,
                                                                   int count, int init,
-                                                                  SnfHeader* __restrict__ host) {
+                                                                  SnfHeader* __restrict__ host,
+                                                                  int32_t* __restrict__ progress,
+                                                                  int done) {
   if (s->stop) return;
-  schedule_body(s, partials, count, init, host);
+  schedule_body(s, partials, count, init, host, progress, done);
 }
 
 void launch_schedule(SnfState* st, const double* partials, int count, int init, hipStream_t s,
-                     SnfHeader* host) {
+                     SnfHeader* host, int32_t* progress, int done) {
   hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(kReduceThreads), 0, s, st, partials,
-                     count, init, host);
+                     count, init, host, progress, done);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2067,19 +2077,6 @@ __device__ __forceinline__ void copy_rows(const double* __restrict__ src, int64_
       }
     }
   }
-}
-
-__global__ __launch_bounds__(256) void copy_out_kernel(const SnfState* __restrict__ st,
-                                                       const Buffers* __restrict__ bufs, int64_t n,
-                                                       int64_t np, double* __restrict__ D,
-                                                       int64_t ld) {
-  copy_rows(bufs->x[st->cur], np, D, ld, n);
-}
-
-void launch_copy_out(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
-                     double* D, int64_t ld, hipStream_t s) {
-  hipLaunchKernelGGL(copy_out_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, st, bufs_dev, n, np,
-                     D, ld);
 }
 
 // The padded copy of a caller's matrix, zero beyond n, and its low-precision copy; dst may be
@@ -2501,32 +2498,32 @@ __global__ __launch_bounds__(kReduceThreads) void grouped_schedule_kernel(const 
   schedule_body(sd.st, sd.partials, slot_tiles(sd, sd.st->prec), 0, nullptr);
 }
 
-// Admission of a request: its tables from the kernel arguments and X_0 = f_0(F) straight from F.
-// A burst waits for its admissions one after the other, so their count of launches and copies is
-// what bounds it: with a copy for each of the three tables and for F, and a retirement that copied
-// the whole state (the full log) after D, 48 requests of order 64 to 256 took 4.8 ms, with one
-// launch each 2.8.  The grid has no more workgroups than X_0 has 32x32 tiles.
-__global__ __launch_bounds__(256) void serve_admit_kernel(ServeAdmit a, const double* __restrict__ F,
-                                                          int lowp_kind) {
+// Start of a solve: its tables from the kernel arguments and X_0 = f_0(F) straight from F.  The
+// serving loop waits for a burst's admissions one after the other, so their count of launches and
+// copies is what bounds it: with a copy for each of the three tables and for F, and a retirement
+// that copied the whole state (the full log) after D, 48 requests of order 64 to 256 took 4.8 ms,
+// with one launch each 2.8.  The grid has no more workgroups than X_0 has 32x32 tiles.
+__global__ __launch_bounds__(256) void solve_start_kernel(SolveStart a, const double* __restrict__ F,
+                                                          int64_t ld, int lowp_kind) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *static_cast<SnfHeader*>(a.desc.st) = a.header;
     *a.desc.bufs = a.bufs;
-    *a.slot = a.desc;
+    if (a.slot) *a.slot = a.desc;
   }
-  f0_body(F, a.desc.n, a.desc.n, a.desc.np, a.header, a.bufs.x[0], a.bufs.lp[0], lowp_kind,
+  f0_body(F, a.desc.n, ld, a.desc.np, a.header, a.bufs.x[0], a.bufs.lp[0], lowp_kind,
           a.desc.partials);
 }
 
-int launch_serve_admit(const ServeAdmit& a, const double* F, int lowp_kind, hipStream_t s) {
+void launch_solve_start(const SolveStart& a, const double* F, int64_t ld, int lowp_kind,
+                        hipStream_t s, int32_t* progress) {
   const int64_t nt = a.desc.np / 32;
   const int blocks = (int)(nt * nt < kF0Blocks ? nt * nt : kF0Blocks);
-  hipLaunchKernelGGL(serve_admit_kernel, dim3(blocks), dim3(256), 0, s, a, F, lowp_kind);
-  launch_schedule(a.desc.st, a.desc.partials, blocks, 1, s);
-  return blocks;
+  hipLaunchKernelGGL(solve_start_kernel, dim3(blocks), dim3(256), 0, s, a, F, ld, lowp_kind);
+  launch_schedule(a.desc.st, a.desc.partials, blocks, 1, s, nullptr, progress, 0);
 }
 
-// Retirement: D, and the final state into host-visible memory (the header and the log written).
-__global__ __launch_bounds__(256) void serve_retire_kernel(const SnfState* __restrict__ st,
+// End of a solve: D, and the final state into host-visible memory (the header and the log written).
+__global__ __launch_bounds__(256) void solve_finish_kernel(const SnfState* __restrict__ st,
                                                            const Buffers* __restrict__ bufs,
                                                            int64_t n, int64_t np,
                                                            double* __restrict__ D, int64_t ld,
@@ -2541,9 +2538,9 @@ __global__ __launch_bounds__(256) void serve_retire_kernel(const SnfState* __res
     ((unsigned*)out->log)[i] = ((const unsigned*)st->log)[i];
 }
 
-void launch_serve_retire(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
+void launch_solve_finish(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
                          double* D, int64_t ld, SnfState* out, hipStream_t s) {
-  hipLaunchKernelGGL(serve_retire_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, st, bufs_dev, n, np,
+  hipLaunchKernelGGL(solve_finish_kernel, dim3(copy_blocks(n)), dim3(256), 0, s, st, bufs_dev, n, np,
                      D, ld, out);
 }
 

@@ -230,7 +230,7 @@ static int start_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   d.np = r->np;
   d.n = r->n;
   for (int p = 0; p < 3; ++p) d.tile[p] = request_tile(r->np, p);
-  ServeAdmit ad;
+  SolveStart ad;
   init_state(&sv->state_stage, r->n, &r->params, r->scheme, r->prec);
   ad.header = sv->state_stage;
   ad.bufs = b;
@@ -242,7 +242,7 @@ static int start_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
                           hipMemcpyHostToDevice, s));
     F = b.x[2];
   }
-  launch_serve_admit(ad, F, lowp_kind_for(r->prec), s);
+  launch_solve_start(ad, F, r->n, lowp_kind_for(r->prec), s);
   SV_HIP(hipGetLastError());
   return SNF_OK;
 }
@@ -254,12 +254,12 @@ static int retire_request(snf_server* sv, ServeRequest* r, hipStream_t s) {
   const int k = r->slot;
   const Buffers& b = sv->bufs_stage[k];
   if (r->device_io) {
-    launch_serve_retire(sv->states + k, sv->bufs + k, r->n, r->np, r->D_dev, r->n, r->st_pin, s);
+    launch_solve_finish(sv->states + k, sv->bufs + k, r->n, r->np, r->D_dev, r->n, r->st_pin, s);
   } else {
     // D leaves through an iterate buffer other than the one holding it (x[2] unless D is
     // there: a P_{m,m} or P_{i,j} iteration rotates its result over all four)
     double* stage = b.x[r->result_buf == 2 ? 0 : 2];
-    launch_serve_retire(sv->states + k, sv->bufs + k, r->n, r->np, stage, r->n, r->st_pin, s);
+    launch_solve_finish(sv->states + k, sv->bufs + k, r->n, r->np, stage, r->n, r->st_pin, s);
     SV_HIP(hipMemcpyAsync(r->D_pin, stage, (size_t)r->n * r->n * sizeof(double),
                           hipMemcpyDeviceToHost, s));
   }

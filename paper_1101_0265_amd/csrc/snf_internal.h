@@ -117,9 +117,10 @@ struct Buffers {
 // ---- kernels launched by the host drivers (defined in kernels_dense.hip) ----------------
 void launch_f0(const double* F, int64_t n, int64_t ld, int64_t np, SnfState* st,
                const Buffers* bufs_dev, int lowp_kind, double* partials, hipStream_t s);
-// host: host-visible memory that takes the header too, or null.
+// host: host-visible memory that takes the header too, or null.  progress: a host-visible word
+// that takes `done`, or -1 once the solve has stopped, or null.
 void launch_schedule(SnfState* st, const double* partials, int count, int init, hipStream_t s,
-                     SnfHeader* host = nullptr);
+                     SnfHeader* host = nullptr, int32_t* progress = nullptr, int done = 0);
 // Work decomposition of one product launch (see make_product_grid).
 struct ProductGrid {
   int64_t np, n;       // padded and true order
@@ -193,8 +194,6 @@ void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGri
                          hipStream_t s);
 void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                         hipStream_t s);
-void launch_copy_out(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
-                     double* D, int64_t ld, hipStream_t s);
 // Padded copy helpers for the stand-alone step.
 void launch_pad_copy(const double* src, int64_t n, int64_t ld, double* dst, int64_t np,
                      void* lp_dst, int lowp_kind, hipStream_t s);
@@ -248,17 +247,18 @@ struct SlotDesc {
   int tile[3];         // tile side of the request's products, by precision (kPrec*)
 };
 
-// Admission of a request in one launch and its first schedule: what its slot's tables hold, by
-// value, and X_0 from F (row stride n).
-struct ServeAdmit {
+// Start of a solve in one launch and its first schedule: what its tables hold, by value, and X_0
+// from F (row stride ld).
+struct SolveStart {
   SnfHeader header;
   Buffers bufs;
-  SlotDesc desc;
-  SlotDesc* slot;      // where desc goes
+  SlotDesc desc;       // (st, bufs, partials, np, n: used in any case)
+  SlotDesc* slot;      // where a served request's desc goes, or null
 };
-int launch_serve_admit(const ServeAdmit& a, const double* F, int lowp_kind, hipStream_t s);
-// D and the final state (out: host-visible) of a finished request.
-void launch_serve_retire(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
+void launch_solve_start(const SolveStart& a, const double* F, int64_t ld, int lowp_kind,
+                        hipStream_t s, int32_t* progress = nullptr);
+// D and the final state (out: host-visible) of a finished solve.
+void launch_solve_finish(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
                          double* D, int64_t ld, SnfState* out, hipStream_t s);
 
 // Tile side of a request's products in FP64 and FP32: 64x64 while its tiles' sums fit the slots
