@@ -536,12 +536,12 @@ __device__ __forceinline__ WorkItem work_item(const ProductGrid& g, int KT) {
 }
 
 // Raw accumulators of a k-slice in tile order: split[piece][r][c], r, c < 128, whatever the
-// thread layout of the kernel that produced them.
-template <bool ROWS_INTERLEAVED, int MT, int QT, typename AccT>
+// thread layout of the kernel that produced them, in the accumulators' type (SliceT).
+template <typename SliceT, bool ROWS_INTERLEAVED, int MT, int QT, typename AccT>
 __device__ __forceinline__ void store_slice(const AccT (&acc)[MT][QT], int wr0, int wc0,
                                             double* split, int piece) {
   const int lane = threadIdx.x & 63;
-  double* base = split + (size_t)piece * kTile * kTile;
+  SliceT* base = (SliceT*)split + (size_t)piece * kTile * kTile;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -550,7 +550,7 @@ __device__ __forceinline__ void store_slice(const AccT (&acc)[MT][QT], int wr0, 
       for (int v = 0; v < 4; ++v) {
         const int r = wr0 + m * 16 + acc_row<ROWS_INTERLEAVED>(lane, v);
         const int c = wc0 + q * 16 + (lane & 15);
-        base[r * kTile + c] = (double)acc[m][q][v];
+        base[r * kTile + c] = acc[m][q][v];
       }
 }
 
@@ -679,7 +679,7 @@ __device__ __forceinline__ void product_body(const SnfState* __restrict__ st,
   }
 
   if (wi.piece >= 0) {
-    store_slice<PREC == kPrecF64>(acc, wr * TR, wc * TC, g.split_buf, wi.piece);
+    store_slice<T, PREC == kPrecF64>(acc, wr * TR, wc * TC, g.split_buf, wi.piece);
     return;
   }
   const EpiArgs ea = epi_args(st, bufs);
@@ -800,7 +800,7 @@ __device__ __forceinline__ void product_bf16_body(const SnfState* __restrict__ s
   }
 
   if (wi.piece >= 0) {
-    store_slice<false>(acc, wr * 64, wc * 64, g.split_buf, wi.piece);
+    store_slice<float, false>(acc, wr * 64, wc * 64, g.split_buf, wi.piece);
     return;
   }
   const EpiArgs ea = epi_args(st, bufs);
@@ -844,10 +844,31 @@ __global__ __launch_bounds__(256, 2) void product_bf16_kernel(const SnfState* __
 }
 
 // Fix-up of the split tail tiles: workgroup (t, b) handles rows 8b .. 8b + 7 of tail tile t
-// (256 threads, 4 consecutive columns each); it adds the k-slices in slice order (the loads
-// of four slices in flight at a time), runs the epilogue of those entries and stores its
-// sums in its own partials slot.
+// (256 threads, 4 consecutive columns each); it adds the k-slices in slice order in FP64 (the
+// loads of four slices in flight at a time), runs the epilogue of those entries and stores its
+// sums in its own partials slot.  Bound by its read of the slices, which the FP32 and BF16
+// products leave in FP32 as they accumulate it (stored in FP64, an FP32-start solve of 19 products
+// took 0.59 ms at n = 300, 0.875 at 700, 1.00 at 1000 and 3.08 at 2000; this 0.525, 0.79, 0.93 and
+// 3.00).  Eight slices in flight, and the linear term's loads ahead of them: no faster.
 constexpr int kMaxSplit = 16;
+template <typename SliceT>
+__device__ __forceinline__ void add_slices(const double* split, size_t at, int count,
+                                           double (&sum)[4]) {
+  typedef SliceT vec __attribute__((ext_vector_type(4)));
+  const vec* base = (const vec*)((const SliceT*)split + at);
+  for (int p0 = 0; p0 < count; p0 += 4) {
+    vec part[4];
+#pragma unroll
+    for (int pp = 0; pp < 4; ++pp)
+      part[pp] = p0 + pp < count ? base[(size_t)(p0 + pp) * (kTile * kTile / 4)] : vec(0);
+#pragma unroll
+    for (int pp = 0; pp < 4; ++pp)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (p0 + pp < count) sum[v] += (double)part[pp][v];
+  }
+}
+
 __global__ __launch_bounds__(256) void split_fixup_kernel(const SnfState* __restrict__ st,
                                                           const Buffers* __restrict__ bufs,
                                                           ProductGrid g) {
@@ -857,21 +878,12 @@ __global__ __launch_bounds__(256) void split_fixup_kernel(const SnfState* __rest
   int bi, bj;
   tile_coords(tile, (int)(g.np / kTile), g.sym, bi, bj);
   const int r = 8 * b + (threadIdx.x >> 5), c0 = (threadIdx.x & 31) * 4;
-  const double* base = g.split_buf + (size_t)t * g.split_s * kTile * kTile + r * kTile + c0;
+  const size_t at = (size_t)t * g.split_s * kTile * kTile + r * kTile + c0;
   double sum[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int p0 = 0; p0 < g.split_s; p0 += 4) {
-    double part[4][4];
-#pragma unroll
-    for (int pp = 0; pp < 4; ++pp)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        part[pp][v] = (p0 + pp < g.split_s) ? base[(size_t)(p0 + pp) * kTile * kTile + v] : 0.0;
-#pragma unroll
-    for (int pp = 0; pp < 4; ++pp)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (p0 + pp < g.split_s) sum[v] += part[pp][v];
-  }
+  if (st->prec == kPrecF64)
+    add_slices<double>(g.split_buf, at, g.split_s, sum);
+  else
+    add_slices<float>(g.split_buf, at, g.split_s, sum);
   const EpiArgs ea = epi_args(st, bufs);
   double e2 = 0.0, t1 = 0.0, t2 = 0.0;
   const int64_t gr = (int64_t)bi * kTile + r;

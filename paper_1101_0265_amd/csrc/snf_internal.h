@@ -130,7 +130,8 @@ struct ProductGrid {
   int split_s;
   int partial_count;   // partial-sum slots written: dp_tiles + 16 * tail_tiles (or tiles)
   double* partials;    // [partial_count][4] FP64 sums per tile / fix-up workgroup
-  double* split_buf;   // [tail_tiles * split_s][64][256] raw accumulators of the slices
+  double* split_buf;   // [tail_tiles * split_s][128][128] raw accumulators (FP64 or FP32) of
+                       // the slices
 };
 
 // Split the last (tiles mod num_cus) tiles into k-slices when that tail would leave most
