@@ -173,15 +173,15 @@ def run_small(args):
     line["ms_per_step"] = out["snf_varmu"]["ms"]
     line["schemes"] = out
     line["speedup_vs_sp2"] = round(out["sp2"]["ms"] / out["snf_varmu"]["ms"], 3)
-    # the product kernel of this order (32x32 tiles, k split inside the workgroup), timed with
-    # HIP events around every product launch of one solve
+    # the step kernel of this order (schedule and product, 32x32 tiles, k split inside the
+    # workgroup), timed with HIP events around every step of one solve
     _, rt = snf.purify_dense(F, "snf_varmu", out=D, want_log=False,
                              flags=snf.FLAG_TIME_PRODUCTS, **kw)
     n = h.n
     achieved = rt["products"] * float(n) * n * (n + 1) / rt["product_ms"] / 1e9
     line["roofline"] = dict(bound="mfma", achieved=round(achieved, 3), peak=78.6,
                             unit="TFLOP/s", frac=round(achieved / 78.6, 5), traffic=None,
-                            kernel="product_f64_small_kernel (32x32 tiles, n=256)",
+                            kernel="direct_step_kernel (32x32 tiles, schedule and product, n=256)",
                             avg_launch_us=round(rt["product_ms"] * 1e3 / rt["products"], 2),
                             note="n^2 (n+1) flops per product over the HIP-event time of its "
                                  "launch; at this order a launch is latency-bound (36 "
@@ -786,7 +786,7 @@ def run_serve(args):
     achieved = (flops64 + flops32) / closed_s / 1e12
     line["roofline"] = dict(bound="mfma", achieved=round(achieved, 2), peak=round(blend, 1),
                             unit="TFLOP/s", frac=round(achieved / blend, 4), traffic=None,
-                            kernel="grouped_product_kernel (f64 and f32, closed loop)",
+                            kernel="grouped product kernels (f64 and f32, closed loop)",
                             note=f"peak = the FP64 (78.6) and FP32 (157.3) MFMA peaks weighted "
                                  f"by this run's work: {flops64 / 1e12:.1f} TFLOP in FP64, "
                                  f"{flops32 / 1e12:.1f} in FP32; achieved over the closed-loop "

@@ -1,6 +1,6 @@
 // Dense kernels of libsnf for gfx950 (MI355X, CDNA4).
 //
-//  * f0_kernel        -- X_0 = f_0(F) (Algorithm 1 or 2 initial map) into a zero-padded
+//  * f_0              -- X_0 = f_0(F) (Algorithm 1 or 2 initial map) into a zero-padded
 //                        n_pad x n_pad buffer, symmetric by construction (upper triangle of F
 //                        read, LDS-transposed for the lower half), plus per-block partial sums
 //                        of tr X_0 and ||X_0||_F^2 and the low-precision operand copy.
@@ -19,6 +19,7 @@
 //                        solve in one workgroup, iterates in LDS.
 //  * schedule_kernel  -- one workgroup: fixed-order reduction of the per-tile partials and the
 //                        scalar state machine (branch, alpha, beta, beta-bar, stopping).
+//  * start / finish   -- a solve's tables with its f_0; D and the final state out.
 //  * copy kernels     -- padded <-> caller layout.
 //  * grouped kernels  -- the serving loop's step over many requests in one launch.
 #include <hip/hip_runtime.h>
