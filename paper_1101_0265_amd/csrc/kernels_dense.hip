@@ -970,15 +970,8 @@ void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid
 // ---------------------------------------------------------------------------------------
 // Schedule: reduce the partials in a fixed order, then advance the scalar state.
 // ---------------------------------------------------------------------------------------
-// alpha of a scaled P_{i,j} step: the smaller of the two sides' roots (tables from the state)
-__device__ __forceinline__ double pij_alpha_state(const SnfScalars* s, const SnfTables* t) {
-  const double lo = sched::pij_alpha_side_tab(s->pij_i, s->pij_j, t->pbin[0], s->xstar, s->beta);
-  const double hi =
-      sched::pij_alpha_side_tab(s->pij_j, s->pij_i, t->pbin[1], 1.0 - s->xstar, s->abar);
-  return lo < hi ? lo : hi;
-}
-
-__device__ __forceinline__ void decide(SnfScalars* s, const SnfConfig* c, const SnfTables* t) {
+__device__ __forceinline__ void decide(SnfScalars* s, const SnfConfig* c, const SnfTables* t,
+                                       double root) {
 #pragma clang fp contract(off)
   // precision phase (only for the mixed-precision modes)
   if (c->mode != SNF_P_FP64) {
@@ -999,9 +992,7 @@ __device__ __forceinline__ void decide(SnfScalars* s, const SnfConfig* c, const 
   int br;
   if (scheme_is_pij(scheme)) {
     br = SNF_BRANCH_PIJ;
-    a = (scheme == SNF_SNF_FIXMU_PIJ)
-            ? pij_alpha_state(s, t)
-            : 1.0;
+    a = (scheme == SNF_SNF_FIXMU_PIJ) ? root : 1.0;
   } else if (scheme == SNF_SP2_TRACE) {
     br = sched::trace_square(s->t1, s->t2, (double)c->n_occ) ? SNF_BRANCH_SQUARE
                                                              : SNF_BRANCH_FOLD;
@@ -1012,9 +1003,7 @@ __device__ __forceinline__ void decide(SnfScalars* s, const SnfConfig* c, const 
       a = sq ? sched::alg2_square_alpha(s->beta) : sched::alg2_fold_alpha(s->betabar);
   } else if (scheme_pmm_m(scheme)) {
     br = s->pmm_m == 3 ? SNF_BRANCH_P33 : SNF_BRANCH_P55;
-    a = (scheme == SNF_SNF_FIXMU3 || scheme == SNF_SNF_FIXMU5)
-            ? sched::pmm_alpha_tab(s->pmm_m, t->pbin[0], s->beta)
-                                                               : 1.0;
+    a = (scheme == SNF_SNF_FIXMU3 || scheme == SNF_SNF_FIXMU5) ? root : 1.0;
   } else {
     br = SNF_BRANCH_P11;
     a = (scheme == SNF_SNF_FIXMU) ? sched::alg1_alpha(s->beta) : 1.0;
@@ -1110,6 +1099,76 @@ __device__ __forceinline__ void advance_beta(SnfScalars* s, const SnfTables* t, 
   }
 }
 
+// The bisection of sched::pmm_alpha_tab and sched::pij_alpha_side_tab by a wave, bit for bit: its
+// halves each solve one side; in a round the 31 lanes of a half evaluate every midpoint that the
+// next five halvings may meet (lane l: node l of a binary heap, its right child the upper half),
+// and the walk down the answers takes the halvings.  Bound by the chain of 53 halvings, which in one
+// thread took 0.5 us each and twice as many for P_{i,j}: scaled P_{3,1}, 28 products, n = 64 0.555
+// ms, this 0.28; 256 0.79, 0.50; 2100 5.00, 4.74; scaled P_{3,3}, 25 products, n = 256 0.51, 0.40.
+template <typename Diff>
+__device__ __forceinline__ double wave_bisect(bool open, double hi, const Diff& diff) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, node = (lane & 31) ? lane & 31 : 1;
+  const int depth = 31 - __clz(node);
+  double lo = 1.0;
+  bool end = !open;
+  for (int round = 0; round < 440 && __ballot(!end) != 0; ++round) {
+    double a = lo, b = hi, mid = 0.5 * (a + b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (k < depth) {
+        if ((node >> (depth - 1 - k)) & 1) a = mid; else b = mid;
+        mid = 0.5 * (a + b);
+      }
+    const unsigned ends = (unsigned)(__ballot(mid <= a || mid >= b) >> (lane & 32));
+    const unsigned ups = (unsigned)(__ballot(diff(mid) < 0.0) >> (lane & 32));
+    int at = 1;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      end = end || ((ends >> at) & 1);
+      if (!end) {
+        const int up = (ups >> at) & 1;
+        const double m = 0.5 * (lo + hi);
+        if (up) lo = m; else hi = m;
+        at = 2 * at + up;
+      }
+    }
+  }
+  return lo;
+}
+
+// Alpha of the iteration that the schedule on header h (in LDS) is about to set up, where it is
+// the root of an Eq. 3 (else 0): the scaled P_{m,m} and P_{i,j} schemes, at the start (init) and
+// behind an iteration's last product.  Every lane of one wave calls it and gets the result.
+__device__ __forceinline__ double schedule_root(const SnfHeader& h, int init) {
+#pragma clang fp contract(off)
+  const int m = h.scheme == SNF_SNF_FIXMU3 || h.scheme == SNF_SNF_FIXMU5 ? h.pmm_m : 0;
+  if (!m && h.scheme != SNF_SNF_FIXMU_PIJ) return 0.0;
+  if (!init && h.kind != kKindFinal) return 0.0;
+  SnfScalars s = h;
+  if (!init) advance_beta(&s, &h, s.branch, s.alpha);
+  if (m) {
+    const double* bin = h.pbin[0];
+    const double beta = s.beta;
+    return wave_bisect(beta > 0.0 && beta < 0.5, 1.0 / (1.0 - 2.0 * beta), [&](double mid) {
+#pragma clang fp contract(off)
+      return sched::pij_eval_tab(m, m, bin, 0.5 * (1.0 - mid)) -
+             sched::pij_eval_tab(m, m, bin, mid * (beta - 0.5) + 0.5);
+    });
+  }
+  const bool hi_side = (threadIdx.x & 32) != 0;
+  const int i = hi_side ? s.pij_j : s.pij_i, j = hi_side ? s.pij_i : s.pij_j;
+  const double* bin = h.pbin[hi_side ? 1 : 0];
+  const double xs = hi_side ? 1.0 - s.xstar : s.xstar, a = hi_side ? s.abar : s.beta;
+  const double root = wave_bisect(a > 0.0 && a < xs, xs / (xs - a), [&](double mid) {
+#pragma clang fp contract(off)
+    return sched::pij_eval_tab(i, j, bin, xs * (1.0 - mid)) -
+           sched::pij_eval_tab(i, j, bin, xs - mid * (xs - a));
+  });
+  const double lo = __shfl(root, 0), hi = __shfl(root, 32);
+  return lo < hi ? lo : hi;
+}
+
 // Set up the next product of a P_{m,m} iteration once the previous one finished:
 // P(1/2 + v) = 1/2 + v r(v^2), v = a (X - I/2), W = v^2.  After W: T = r_m W^2 + r_{m-1} W
 // + r_{m-2} I from W.W; then T <- W.T + r_k I down to k = 0; then X_new = 1/2 I + v T.
@@ -1198,11 +1257,11 @@ __device__ __forceinline__ void schedule_scalars(SnfScalars* __restrict__ s,
                                                  const SnfConfig* __restrict__ c,
                                                  const SnfTables* __restrict__ t,
                                                  snf_log_rec* __restrict__ log, double e2,
-                                                 double t1, double t2, int init) {
+                                                 double t1, double t2, int init, double root) {
   if (init) {
     s->t1 = t1;
     s->t2 = t2;
-    decide(s, c, t);
+    decide(s, c, t, root);
     return;
   }
   s->products += 1;
@@ -1270,7 +1329,7 @@ __device__ __forceinline__ void schedule_scalars(SnfScalars* __restrict__ s,
     s->cur = s->io;
     s->t1 = t1;
     s->t2 = t2;
-    decide(s, c, t);
+    decide(s, c, t, root);
   } else if (s->kind == kKindHorner) {
     s->horner_left -= 1;
     if (s->pij_i) pij_next(s, t); else pmm_next(s, t);
@@ -1280,7 +1339,7 @@ __device__ __forceinline__ void schedule_scalars(SnfScalars* __restrict__ s,
     s->cur = s->io;
     s->t1 = t1;
     s->t2 = t2;
-    decide(s, c, t);
+    decide(s, c, t, root);
   }
 }
 
@@ -1288,10 +1347,10 @@ __device__ __forceinline__ void schedule_scalars(SnfScalars* __restrict__ s,
 // otherwise wait for a chain of single LDS reads.
 __device__ __forceinline__ void schedule_step(SnfHeader* __restrict__ hs,
                                               snf_log_rec* __restrict__ log, double e2, double t1,
-                                              double t2, int init) {
+                                              double t2, int init, double root) {
   SnfScalars sc = *hs;
   const SnfConfig cf = *hs;
-  schedule_scalars(&sc, &cf, hs, log, e2, t1, t2, init);
+  schedule_scalars(&sc, &cf, hs, log, e2, t1, t2, init, root);
   *static_cast<SnfScalars*>(hs) = sc;
 }
 
@@ -1322,7 +1381,10 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
   const bool teller = progress && threadIdx.x == kReduceThreads - 64;
   if (teller) __hip_atomic_store(progress, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   block_sum3(e2, t1, t2, red);             // its barrier also publishes the header copy
-  if (threadIdx.x == 0) schedule_step(&hs, sg->log, e2, t1, t2, init);
+  if (threadIdx.x < 64) {
+    const double root = schedule_root(hs, init);
+    if (threadIdx.x == 0) schedule_step(&hs, sg->log, e2, t1, t2, init, root);
+  }
   __syncthreads();
   for (int i = threadIdx.x; i < words; i += kReduceThreads) {
     gb[i] = hb[i];
@@ -1577,8 +1639,9 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // (FP64 instructions share the matrix cores' units with the other waves' products)
     __builtin_amdgcn_s_setprio(3);
+    const double root = schedule_root(hs, step == 0);
     if (lane == 0) {
-      schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0);
+      schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0, root);
       if (hs.stop) *(volatile int*)&stopped = 1;
     }
     __builtin_amdgcn_s_setprio(0);
@@ -1924,7 +1987,10 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
       xbuf[at(c, r)] = x;
     }
     sum3(e2, t1, t2);
-    if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 1);
+    if (tid < 64) {
+      const double root = schedule_root(hs, 1);
+      if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 1, root);
+    }
     __syncthreads();
   }
   const int nb = np / 16, cnt = nb * (nb + 1) / 2;
@@ -1989,7 +2055,10 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
     else if (mine == 2) product(std::integral_constant<int, 2>());
     else if (mine == 1) product(std::integral_constant<int, 1>());
     sum3(e2, t1, t2);                      // (its barrier: every read of the operands is done)
-    if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 0);
+    if (tid < 64) {
+      const double root = schedule_root(hs, 0);
+      if (tid == 0) schedule_step(&hs, out->log, e2, t1, t2, 0, root);
+    }
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       if (NB != 1 && wid + i * kWgWaves < cnt) {         // (the result is in another buffer)
