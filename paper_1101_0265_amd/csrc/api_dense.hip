@@ -826,15 +826,18 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
     st.slot = nullptr;
     SNF_HIP(hipEventRecord(w->ev[0], s));
     launch_solve_start(st, F_dev, ld, lowp_kind_for(precision), s, progress);
-    const bool lowp = precision != SNF_P_FP64;
+    const int lk = lowp_kind_for(precision);
     const bool pij = scheme_is_pij(scheme);
     int enq = 0;
     rc = lead_steps(max_steps, np <= kLongLeadNp ? kLongLead : kShortLead, progress, s, &enq,
                      [&](int k) -> int {
       if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k], s));
-      launch_product(kPrecF64, w->state, w->bufs_dev, grid, s);
-      if (pij) launch_product_dual(w->state, w->bufs_dev, grid, s);
-      if (lowp) launch_product(lowp_kind_for(precision), w->state, w->bufs_dev, grid, s);
+      if (lk != kPrecF32 ||
+          !launch_product_f64_f32(w->state, w->bufs_dev, grid, w->num_cus, s)) {
+        launch_product(kPrecF64, w->state, w->bufs_dev, grid, s);
+        if (pij) launch_product_dual(w->state, w->bufs_dev, grid, s);
+        if (lk >= 0) launch_product(lk, w->state, w->bufs_dev, grid, s);
+      }
       launch_split_fixup(w->state, w->bufs_dev, grid, s);
       if (time_products) SNF_HIP(hipEventRecord(w->prod_ev[2 * k + 1], s));
       launch_schedule(w->state, w->partials, grid.partial_count, 0, s, nullptr, progress, k + 1);

@@ -837,6 +837,20 @@ __global__ __launch_bounds__(512, 2) void product_f32_kernel(const SnfState* __r
   product_body<float, kPrecF32>(st, bufs, g, work_item(g, (int)(g.np / Mfma<float>::kBK)));
 }
 
+// Both of them, for launches of at most a workgroup per compute unit, where the LDS of both is no
+// loss: a step of an FP32-start solve then has no launch that only finds out that the product is
+// the other kernel's (19 products: n = 130 0.48 ms with the empty launches, 0.44 without; 300 0.54,
+// 0.495; 700 0.78, 0.72; 1000 0.925, 0.875; 1900 2.42, 2.36).
+__global__ __launch_bounds__(512, 2) void product_f64_f32_kernel(const SnfState* __restrict__ st,
+                                                                 const Buffers* __restrict__ bufs,
+                                                                 ProductGrid g) {
+  if (st->stop) return;
+  if (st->prec == kPrecF64)
+    product_body<double, kPrecF64>(st, bufs, g, work_item(g, (int)(g.np / Mfma<double>::kBK)));
+  else
+    product_body<float, kPrecF32>(st, bufs, g, work_item(g, (int)(g.np / Mfma<float>::kBK)));
+}
+
 __global__ __launch_bounds__(256, 2) void product_bf16_kernel(const SnfState* __restrict__ st,
                                                               const Buffers* __restrict__ bufs,
                                                               ProductGrid g) {
@@ -952,6 +966,16 @@ void launch_product(int prec, SnfState* st, const Buffers* bufs_dev, const Produ
   } else {
     hipLaunchKernelGGL(product_bf16_kernel, dim3(grid), dim3(kThreads), 0, s, st, bufs_dev, g);
   }
+}
+
+bool launch_product_f64_f32(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
+                            int num_cus, hipStream_t s) {
+  static_assert(Layout<double, kTile>::NT == 512 && Layout<float, kTile>::NT == 512,
+                "one launch shape");
+  const int grid = g.dp_tiles + g.tail_tiles * g.split_s;
+  if (grid > num_cus) return false;
+  hipLaunchKernelGGL(product_f64_f32_kernel, dim3(grid), dim3(512), 0, s, st, bufs_dev, g);
+  return true;
 }
 
 void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
@@ -1102,9 +1126,9 @@ __device__ __forceinline__ void advance_beta(SnfScalars* s, const SnfTables* t, 
 // The bisection of sched::pmm_alpha_tab and sched::pij_alpha_side_tab by a wave, bit for bit: its
 // halves each solve one side; in a round the 31 lanes of a half evaluate every midpoint that the
 // next five halvings may meet (lane l: node l of a binary heap, its right child the upper half),
-// and the walk down the answers takes the halvings.  Bound by the chain of 53 halvings, which in one
-// thread took 0.5 us each and twice as many for P_{i,j}: scaled P_{3,1}, 28 products, n = 64 0.555
-// ms, this 0.28; 256 0.79, 0.50; 2100 5.00, 4.74; scaled P_{3,3}, 25 products, n = 256 0.51, 0.40.
+// and the walk down the answers takes the halvings.  Bound by the chain of 53 halvings, which in
+// one thread took 0.5 us each and twice as many for P_{i,j}: scaled P_{3,1}, 28 products, n = 64
+// 0.555 ms, this 0.28; 256 0.79, 0.50; 2100 5.00, 4.74; P_{3,3}, 25 products, n = 256 0.51, 0.40.
 template <typename Diff>
 __device__ __forceinline__ double wave_bisect(bool open, double hi, const Diff& diff) {
 #pragma clang fp contract(off)

@@ -191,6 +191,10 @@ int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D,
                     SnfState* out, int max_steps, hipStream_t s);
 // FP64 product with the second epilogue output (P_{i,j} schemes: launched beside
 // launch_product(kPrecF64, ...); exactly one of the two runs, as the state asks).
+// The pending product in FP64 or FP32, whichever the state asks for, in one launch; false (nothing
+// launched) where the launch would have more workgroups than compute units.
+bool launch_product_f64_f32(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
+                            int num_cus, hipStream_t s);
 void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                          hipStream_t s);
 void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,

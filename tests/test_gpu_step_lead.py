@@ -10,8 +10,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,prec", [(130, "fp32_ref64"), (300, "bf16_ref64"), (300, "fp32"),
-                                    (2200, "fp64")])
+@pytest.mark.parametrize("n,prec", [(130, "fp32_ref64"), (2049, "fp32_ref64"),
+                                    (300, "bf16_ref64"), (300, "fp32"), (2200, "fp64")])
 def test_ends(n, prec):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
