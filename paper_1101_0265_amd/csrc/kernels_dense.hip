@@ -2040,9 +2040,9 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
     // the wave's blocks side by side, four k-steps of operands at a time
     auto product = [&](auto countc) {
       constexpr int C = decltype(countc)::value;
-      dbl4 acc[C];
+      dbl4 acc[C][2];                      // (even and odd k-steps: half the rounding of one sum)
 #pragma unroll
-      for (int i = 0; i < C; ++i) acc[i] = dbl4{0.0, 0.0, 0.0, 0.0};
+      for (int i = 0; i < C; ++i) acc[i][0] = acc[i][1] = dbl4{0.0, 0.0, 0.0, 0.0};
       for (int k = 0; k < np; k += 16) {
         double av[C][4], bv[C][4];
 #pragma unroll
@@ -2056,14 +2056,15 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < C; ++i)
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][u], bv[i][u], acc[i], 0, 0, 0);
+            acc[i][u & 1] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][u], bv[i][u], acc[i][u & 1], 0, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < C; ++i)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int r = br[i] * 16 + fk + 4 * v, c = bc[i] * 16 + fr;
-          const double p = acc[i][v], x = L[at(r, c)];
+          const double p = acc[i][0][v] + acc[i][1][v], x = L[at(r, c)];
           const bool on = r == c, in = r < n && c < n;
           y[i][v] = in ? c2 * p + c1 * x + (on ? c0 : 0.0) : 0.0;
           if (NB == 4) y2[i][v] = in ? d2 * p + d1 * x + (on ? d0 : 0.0) : 0.0;
