@@ -658,6 +658,7 @@ static int finish_direct(Workspace* w, snf_result* out, snf_log_rec* log, int32_
   fill_result(st, out, log, log_cap);
   const int status = st->stop ? st->status : SNF_ENOCONV;
   out->status = status;
+  if (status == SNF_EDEVICE) return dev_error(hipErrorUnknown, "a step's operands");
   float ms = 0.f;
   SNF_HIP(hipEventElapsedTime(&ms, w->ev[0], w->ev[1]));
   out->device_ms = ms;

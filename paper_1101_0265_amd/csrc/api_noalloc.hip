@@ -137,6 +137,7 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
   const int status = sh->stop ? sh->status : SNF_ENOCONV;
   fill_result(sh, out, log, log_cap);
   out->status = status;
+  if (status == SNF_EDEVICE) return record_hip_error(hipErrorUnknown, "a step's operands");
   int khz = 0;
   if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0)
     out->device_ms = (double)(ticks[1] - ticks[0]) / (double)khz;

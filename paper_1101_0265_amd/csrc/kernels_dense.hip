@@ -191,11 +191,6 @@ int num_product_tiles(int64_t np, int sym) {
   return (int)(sym ? nt * (nt + 1) / 2 : nt * nt);
 }
 
-__device__ __forceinline__ int num_product_tiles_dev(int64_t np) {
-  const int64_t nt = np / kTile;
-  return (int)(nt * (nt + 1) / 2);
-}
-
 __device__ __forceinline__ int xcd_remap(int w, int total) {
   const int xcd = w & 7, slot = w >> 3;
   const int base = total >> 3, rem = total & 7;
@@ -1666,6 +1661,11 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     const double root = schedule_root(hs, step == 0);
     if (lane == 0) {
       schedule_step(&hs, blockIdx.x == 0 ? g.log : nullptr, e2, t1, t2, step == 0, root);
+      // the product under way reads the buffers that the host named: another choice is an error
+      if (!hs.stop && (hs.ia != pa || hs.ib != pb || hs.ix != px)) {
+        hs.status = SNF_EDEVICE;
+        hs.stop = 1;
+      }
       if (hs.stop) *(volatile int*)&stopped = 1;
     }
     __builtin_amdgcn_s_setprio(0);
@@ -1748,25 +1748,10 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
   }
   __syncthreads();
   if (hs.stop) return;
-  const int ia = __builtin_amdgcn_readfirstlane(hs.ia), ib = __builtin_amdgcn_readfirstlane(hs.ib);
-  if (worker && (ia != pa || ib != pb)) {
-    // not the operands the host expected: again, at leisure
-    const double *Ap = pick_buf(g.bufs, ia), *Bp = pick_buf(g.bufs, ib);
-#pragma unroll
-    for (int m = 0; m < TB; ++m)
-#pragma unroll
-      for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-    for (int ks = kb; ks < ke; ++ks) {
-      load(Ap, Bp, ks, 0);
-      compute(0);
-    }
-  }
 
   // the tile's results
-  const int ix = __builtin_amdgcn_readfirstlane(hs.ix);
-  const double* X = pick_buf(g.bufs, ix);
-  if (!XA || ix != px) load_x(X, 0);
+  const double* X = pick_buf(g.bufs, px);
+  if (!XA) load_x(X, 0);
   DirectOut o;
   o.Y = pick_buf(g.bufs, __builtin_amdgcn_readfirstlane(hs.io));
   o.Y2 = __builtin_amdgcn_readfirstlane(hs.dual)
@@ -1932,10 +1917,12 @@ void StepOperands::next(int (&op)[3]) {
 // registers until the sums are known, so X needs no second buffer and is still whole when the
 // stop test passes.  A step at n = 64 takes 4.9 us: 2.6 the products, 0.4 the sums, 1.4 the
 // schedule, 0.4 the writes.  The 19 products of the solves above at n = 17 / 40 / 64 / 80: 0.10 /
-// 0.12 / 0.14 / 0.17 ms, against 0.38 ms in a cooperative launch of 32x32 tiles.  At order 96 the
-// direct steps take as long (0.23 against 0.22 ms, 31 products 0.30 against 0.32).
+// 0.12 / 0.14 / 0.17 ms, against 0.38 ms in a cooperative launch of 32x32 tiles.  Above order 80 the
+// direct steps take over (at 96, with a third block for some waves, such a solve took 0.23 ms
+// against their 0.22).
 // ---------------------------------------------------------------------------------------
 constexpr int kWgThreads = 512, kWgWaves = kWgThreads / 64;
+constexpr int kWgMaxBlocks = 5;          // 16x16 blocks a side
 
 static int wg_buffers(int scheme) {
   if (scheme_pmm_m(scheme) || scheme_is_pij(scheme)) return 4;
@@ -1943,7 +1930,7 @@ static int wg_buffers(int scheme) {
 }
 
 size_t solve_wg_bytes(int64_t n, int scheme) {
-  if (n > 80) return 0;
+  if (n > 16 * kWgMaxBlocks) return 0;
   const int64_t np = (n + 15) / 16 * 16;
   const size_t bytes = (size_t)wg_buffers(scheme) * np * np * sizeof(double);
   return bytes <= (size_t)144 << 10 ? bytes : 0;
@@ -1956,7 +1943,8 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
                                                               int64_t ldf, double* __restrict__ D,
                                                               int64_t ldd, SnfState* __restrict__ out,
                                                               int max_steps) {
-  constexpr int MB = NB == 4 ? 2 : 3;      // blocks per wave at the largest order
+  constexpr int MB = 2;                    // blocks per wave at the largest order
+  static_assert(kWgMaxBlocks * (kWgMaxBlocks + 1) / 2 <= MB * kWgWaves, "every block has a wave");
   extern __shared__ __attribute__((aligned(16))) double xbuf[];
   __shared__ __attribute__((aligned(16))) SnfHeader hs;
   __shared__ double red[3 * kWgWaves];
@@ -2076,8 +2064,7 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
           }
         }
     };
-    if (MB >= 3 && mine >= 3) product(std::integral_constant<int, MB >= 3 ? 3 : 1>());
-    else if (mine == 2) product(std::integral_constant<int, 2>());
+    if (mine == 2) product(std::integral_constant<int, 2>());
     else if (mine == 1) product(std::integral_constant<int, 1>());
     sum3(e2, t1, t2);                      // (its barrier: every read of the operands is done)
     if (tid < 64) {

@@ -170,8 +170,8 @@ struct DirectArgs {
 void launch_direct_f0(const DirectArgs& a, const SnfHeader& h, const double* F, int64_t ldf,
                       hipStream_t s);
 // Step `step` of the solve: advance the state by the previous step's sums (step 0: f_0's), then,
-// unless that stopped it, the pending product.  op: the operand and linear-term buffers the state
-// will name, as far as the host knows (others are slower, not wrong).
+// unless that stopped it, the pending product.  op: the operand and linear-term buffers that the
+// state will name (StepOperands; if it names others, the solve stops with SNF_EDEVICE).
 void launch_direct_step(int tile, const DirectArgs& a, int step, const int (&op)[3],
                         hipStream_t s);
 // D and the final state (header of slot `slot`, log) out.
@@ -189,12 +189,12 @@ struct StepOperands {
 size_t solve_wg_bytes(int64_t n, int scheme);
 int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D, int64_t ldd,
                     SnfState* out, int max_steps, hipStream_t s);
-// FP64 product with the second epilogue output (P_{i,j} schemes: launched beside
-// launch_product(kPrecF64, ...); exactly one of the two runs, as the state asks).
 // The pending product in FP64 or FP32, whichever the state asks for, in one launch; false (nothing
 // launched) where the launch would have more workgroups than compute units.
 bool launch_product_f64_f32(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                             int num_cus, hipStream_t s);
+// FP64 product with the second epilogue output (P_{i,j} schemes: launched beside
+// launch_product(kPrecF64, ...); exactly one of the two runs, as the state asks).
 void launch_product_dual(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                          hipStream_t s);
 void launch_split_fixup(SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
