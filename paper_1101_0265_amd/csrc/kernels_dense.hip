@@ -1591,6 +1591,14 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     DirectArgs g, int step, int pa, int pb, int px) {
   constexpr int T = 16 * TB, QB = TB / NC, NT = kDirectThreads * NC;
   static_assert(QB * NC == TB, "equal column groups");
+  // The rounding of a sum grows with the terms that go to one running sum.  A quarter's terms go to
+  // S of them in turn, or where the registers do not hold more accumulators to one in PH phases,
+  // each then added to the phases before: at most n / 16 terms a sum (T = 32), n / 16 + 28 (48) and
+  // n / 8 + 28 (64), as few as in the engine's up to 16 k-slices.  With one sum a quarter |D -
+  // D_exact|_F was up to 1.6 times the engine's (scaled P_{1,3}, n = 512: 2.15e-13, engine 1.36e-13,
+  // this 1.26e-13; Algorithm 1, n = 1000: 1.98e-13, 1.53e-13, 1.23e-13), at the same time within
+  // 1%.  From T = 80 on the engine had two or three slices.
+  constexpr int S = TB == 2 ? 4 : 1, PH = TB == 3 ? 4 : TB == 4 ? 2 : 1;
   constexpr int P = TB / 2, LW = T + 2;
   constexpr int SWAVE = SW ? 4 * NC : 0;
   // the product starts ahead of the schedule; the largest tiles wait for it, as their product
@@ -1684,11 +1692,16 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
   // the wave's k-steps (4 values of k each); rows n .. ld - 1 of the buffers are zero
   const int KT = (int)((g.n + 3) / 4);
   const int kb = kq * KT / 4, ke = (kq + 1) * KT / 4;
-  dbl4 acc[TB][QB];
+  dbl4 acc[S][TB][QB];
+  auto clear = [&]() {
 #pragma unroll
-  for (int m = 0; m < TB; ++m)
+    for (int i = 0; i < S; ++i)
 #pragma unroll
-    for (int q = 0; q < QB; ++q) acc[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+      for (int m = 0; m < TB; ++m)
+#pragma unroll
+        for (int q = 0; q < QB; ++q) acc[i][m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  };
+  clear();
   DirectOperand<TB, PD> A;
   DirectOperand<QB, PD> B;
   auto load = [&](const double* Ap, const double* Bp, int ks, int slot) {
@@ -1701,9 +1714,10 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     for (int m = 0; m < TB; ++m)
 #pragma unroll
       for (int q = 0; q < QB; ++q)
-        acc[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.get(slot, m), B.get(slot, q), acc[m][q],
-                                                         0, 0, 0);
+        acc[slot % S][m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+            A.get(slot, m), B.get(slot, q), acc[slot % S][m][q], 0, 0, 0);
   };
+  dbl4 tot[PH > 1 ? TB : 1][PH > 1 ? QB : 1];           // sums of the phases before this one
   // the linear term's values of a band of 32 rows; the first band's ahead of the product where
   // the registers allow it
   constexpr bool XA = TB <= 4;
@@ -1729,17 +1743,36 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
       if (hs.stop) return;
     }
     int ks = kb;
-    for (; ks + PD <= ke; ks += PD) {
-      if (EARLY && *(volatile int*)&stopped) break;
-      // (past the end the last k-step again, never used: the number of loads in flight is the
-      // same on every path, so a wait leaves the newer ones in flight)
+    auto steps = [&](int end) {
+      for (; ks + PD <= end; ks += PD) {
+        if (EARLY && *(volatile int*)&stopped) break;
+        // (past the end the last k-step again, never used: the number of loads in flight is the
+        // same on every path, so a wait leaves the newer ones in flight)
 #pragma unroll
-      for (int u = 0; u < PD; ++u) {
-        compute(u);
-        load(Ap, Bp, ks + u + PD, u);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < PD; ++u) {
+          compute(u);
+          load(Ap, Bp, ks + u + PD, u);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    if constexpr (PH > 1) {
+#pragma unroll
+      for (int m = 0; m < TB; ++m)
+#pragma unroll
+        for (int q = 0; q < QB; ++q) tot[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
+      const int span = ((ke - kb + PH - 1) / PH + PD - 1) / PD * PD;
+#pragma unroll 1
+      for (int end = kb + span; end < ke; end += span) {
+        steps(end);
+#pragma unroll
+        for (int m = 0; m < TB; ++m)
+#pragma unroll
+          for (int q = 0; q < QB; ++q) tot[m][q] += acc[0][m][q];
+        clear();
       }
     }
+    steps(ke);
 #pragma unroll
     for (int u = 0; u < PD; ++u)
       if (ks + u < ke) compute(u);
@@ -1748,6 +1781,17 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
   }
   __syncthreads();
   if (hs.stop) return;
+
+  // the wave's sums of its quarter
+#pragma unroll
+  for (int m = 0; m < TB; ++m)
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      if constexpr (S == 4)
+        acc[0][m][q] = (acc[0][m][q] + acc[1][m][q]) + (acc[2][m][q] + acc[3][m][q]);
+      if constexpr (S == 2) acc[0][m][q] += acc[1][m][q];
+      if constexpr (PH > 1) acc[0][m][q] += tot[m][q];
+    }
 
   // the tile's results
   const double* X = pick_buf(g.bufs, px);
@@ -1767,7 +1811,7 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
   o.d1 = hs.d1;
   o.d0 = hs.d0;
   e2 = t1 = t2 = 0.0;
-  direct_bands<TB, NC, false>(acc, part, xs, [&](int p) { load_x(X, p); }, o, i0, j0, worker, e2,
+  direct_bands<TB, NC, false>(acc[0], part, xs, [&](int p) { load_x(X, p); }, o, i0, j0, worker, e2,
                               t1, t2);
   e2 = wave_sum_rows(e2);
   t1 = wave_sum_rows(t1);
@@ -1864,7 +1908,7 @@ void launch_direct_step(int tile, const DirectArgs& a, int step, const int (&op)
                      op[1], op[2])
   switch (tile) {
     case 32: SNF_DIRECT(2, 1, 8, true); break;
-    case 48: SNF_DIRECT(3, 1, 10, true); break;
+    case 48: SNF_DIRECT(3, 1, 7, true); break;
     case 64: SNF_DIRECT(4, 2, 7, false); break;
     case 80: SNF_DIRECT(5, 1, 6, false); break;
     default: SNF_DIRECT(6, 2, 4, false); break;
