@@ -34,6 +34,7 @@ def _lost(snf, n):
 
 
 @pytest.mark.parametrize("n,chain,adds", [
+    (32, 8, 2), (64, 16, 2), (80, 20, 2),              # one workgroup: four chains
     (256, 256 // 16 + 8, 5), (400, 400 // 16 + 8, 5), (600, 600 // 16 + 8, 5),
     (704, 704 // 16 + 8, 5),                           # four chains a wave, four waves
     (705, 705 // 16 + 28, 7), (896, 896 // 16 + 28, 7), (1000, 1000 // 16 + 28, 7),
