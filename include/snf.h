@@ -241,7 +241,9 @@ int snf_purify_dense(const double* F_dev, int64_t n, int64_t ld, const snf_param
  * torch): all device memory beyond F and D comes from a fixed array of
  * SNF_NOALLOC_SCRATCH_BYTES that the library's code object holds on every device it is loaded
  * on, until the process ends.  Same arguments, results and errors as snf_purify_dense, bit
- * for bit (the same kernels on the same decomposition), restricted to:
+ * for bit (the same kernels on the same decomposition; on a device of fewer than 256 compute
+ * units, where snf_purify_dense may take other tiles than the array holds, to rounding),
+ * restricted to:
  *   - precision SNF_P_FP64 and the schemes other than SNF_SNF_FIXMU_PIJ / SNF_PIJ
  *     (SNF_EINVAL otherwise);
  *   - n rounded up to a multiple of 128 at most SNF_NOALLOC_MAX_N (SNF_ESIZE otherwise).

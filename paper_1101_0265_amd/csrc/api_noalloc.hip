@@ -84,6 +84,10 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
   init_state(sh, n, params, scheme, SNF_P_FP64);
   const int per_it = products_per_iteration(scheme, params->poly_i, params->poly_j);
   const int max_steps = (params->max_iter + 1) * per_it + 1;
+  int cus = 0;
+  NA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const int tile = noalloc_tile(n, cus, kNaMaxLd);
+  if (!tile || direct_stride(n, tile) > kNaMaxLd) return SNF_ESIZE;
   hipLaunchKernelGGL(na_clock_kernel, dim3(1), dim3(64), 0, s, clk);
   if (solve_wg_bytes(n, scheme) > 0) {
     if (launch_solve_wg(*sh, F_dev, ld, D_dev, ld, st, max_steps, s) != 0)
@@ -93,10 +97,6 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
     // stride, and every entry they read is written before (f_0 writes all of X_0 including its
     // zero padding, every step all of its output), so nothing left by an earlier call needs
     // clearing.
-    int cus = 0;
-    NA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const int tile = direct_tile(n, cus);
-    if (!tile || direct_stride(n, tile) > kNaMaxLd) return SNF_EDEVICE;
     DirectArgs a;
     for (int i = 0; i < 4; ++i) {
       a.bufs.x[i] = base + kOffX + (size_t)i * kNaMatrix;

@@ -1433,23 +1433,6 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
 // until the operands are there (the schedule, 2.5 us from its sums on, beside the 3 us of
 // products), 2 the epilogue, 2 to the next launch's first instruction.
 // ---------------------------------------------------------------------------------------
-constexpr int kDirectThreads = 256;
-
-int direct_tile(int64_t n, int num_cus) {
-  if (num_cus > kDirectThreads) num_cus = kDirectThreads;   // (a step sums a slot per thread)
-  for (int t = 32; t <= 96; t += 16) {
-    const int64_t nt = (n + t - 1) / t;
-    if (nt * (nt + 1) / 2 <= num_cus) return t;
-  }
-  return 0;
-}
-
-int64_t direct_stride(int64_t n, int tile) {
-  const int64_t w = (n + tile - 1) / tile * tile;
-  // rows a multiple of 2 KB apart would put the rows of one load on the same channels
-  return w % 256 ? w : w + 16;
-}
-
 __device__ __forceinline__ double* pick_buf(const Buffers& b, int i) {
   double* p = b.x[0];
   if (i == 1) p = b.x[1];

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/snf.h"
+#include "direct_tiles.h"
 #include "schedule_math.h"
 
 namespace snf {
@@ -150,12 +151,6 @@ constexpr int kSplitCap = 512;   // slices held by the split buffer (64*256 doub
 void launch_product(int prec, SnfState* st, const Buffers* bufs_dev, const ProductGrid& g,
                     hipStream_t s);
 // ---- FP64 solves of small and middle order (kernels_dense.hip) --------------------------
-// Work of one workgroup per step: a TxT output tile of the upper triangle, T the smallest of
-// 32, 48, 64, 80, 96 whose tiles number at most one per compute unit; 0: no such T.
-int direct_tile(int64_t n, int num_cus);
-// Row stride of the iterate buffers for that T (a multiple of 16, at least T ceil(n / T)).
-int64_t direct_stride(int64_t n, int tile);
-constexpr int kDirectSlots = 512;     // partial-sum slots per step parity (f_0's blocks, tiles)
 constexpr int kDirectF0Blocks = 256;
 struct DirectArgs {
   Buffers bufs;            // iterate buffers of stride ld (device pointers)
