@@ -738,12 +738,27 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
   // buffers, so its solves only take the tiles of 32, with the padded row stride)
   const bool newton = (params->flags & SNF_FLAG_SUBSPACE_NEWTON) != 0;
   const bool fp64 = precision == SNF_P_FP64;
-  const bool in_wg = fp64 && !newton && solve_wg_bytes(n, scheme) > 0;
+  const bool time_products = (params->flags & SNF_FLAG_TIME_PRODUCTS) != 0;
+  const int per_it = products_per_iteration(scheme, params->poly_i, params->poly_j);
+  const int max_steps = (params->max_iter + 1) * per_it + 1;
+  if (fp64 && !newton && solve_wg_bytes(n, scheme) > 0) {
+    rc = ensure_workspace(w, 0, 0, 0);
+    if (rc != SNF_OK) return rc;
+    init_state(w->state_host, n, params, scheme, precision);
+    SNF_HIP(hipEventRecord(w->ev[0], s));
+    if (launch_solve_wg(*w->state_host, F_dev, ld, D_dev, ld, w->state_host, max_steps, s) == 0) {
+      SNF_HIP(hipEventRecord(w->ev[1], s));
+      SNF_HIP(hipStreamSynchronize(s));
+      return finish_direct(w, out, log, log_cap, time_products, 0);
+    }
+    (void)hipGetLastError();    // the device refused the launch (nothing ran): the direct steps
+  }
   int tile = 0;
-  if (fp64 && !in_wg) tile = direct_tile(newton ? np : n, device_cus(w));
+  if (fp64) tile = direct_tile(newton ? np : n, device_cus(w));
   if (newton && tile != 32) tile = 0;
   const int64_t dld = newton ? np : direct_stride(n, tile ? tile : kTile);
-  rc = ensure_workspace(w, in_wg ? 0 : tile ? std::max(np, dld) : np, lowp_bytes_for(precision), slot_tiles + 16 * kSplitCap,
+  rc = ensure_workspace(w, tile ? std::max(np, dld) : np, lowp_bytes_for(precision),
+                        slot_tiles + 16 * kSplitCap,
                         (scheme_pmm_m(scheme) || scheme_is_pij(scheme)) ? 4 : 3);
   if (rc != SNF_OK) {
     out->status = rc;
@@ -754,23 +769,12 @@ static int purify_dense_body(const double* F_dev, int64_t n, int64_t ld,
   // A workspace of larger order is used with this call's np: the kernels index rows with
   // np, so every buffer just needs np*np elements.
   init_state(w->state_host, n, params, scheme, precision);
-  const bool time_products = (params->flags & SNF_FLAG_TIME_PRODUCTS) != 0;
-  const int per_it = products_per_iteration(scheme, params->poly_i, params->poly_j);
-  const int max_steps = (params->max_iter + 1) * per_it + 1;
   if (time_products && (int)w->prod_ev.size() < 2 * (max_steps + 1)) {
     const size_t old = w->prod_ev.size();
     w->prod_ev.resize(2 * (max_steps + 1));
     for (size_t i = old; i < w->prod_ev.size(); ++i) SNF_HIP(hipEventCreate(&w->prod_ev[i]));
   }
 
-  if (in_wg) {
-    SNF_HIP(hipEventRecord(w->ev[0], s));
-    if (launch_solve_wg(*w->state_host, F_dev, ld, D_dev, ld, w->state_host, max_steps, s) != 0)
-      return dev_error(hipGetLastError(), "the one-workgroup solve");
-    SNF_HIP(hipEventRecord(w->ev[1], s));
-    SNF_HIP(hipStreamSynchronize(s));
-    return finish_direct(w, out, log, log_cap, time_products, 0);
-  }
   int32_t* progress = w->flags_host + 4;
   *(volatile int32_t*)progress = 0;
   int ev_used = 0;

@@ -89,10 +89,12 @@ int na_body(const double* F_dev, int64_t n, int64_t ld, const snf_params* params
   const int tile = noalloc_tile(n, cus, kNaMaxLd);
   if (!tile || direct_stride(n, tile) > kNaMaxLd) return SNF_ESIZE;
   hipLaunchKernelGGL(na_clock_kernel, dim3(1), dim3(64), 0, s, clk);
-  if (solve_wg_bytes(n, scheme) > 0) {
-    if (launch_solve_wg(*sh, F_dev, ld, D_dev, ld, st, max_steps, s) != 0)
-      return record_hip_error(hipGetLastError(), "the one-workgroup solve");
-  } else {
+  bool in_wg = solve_wg_bytes(n, scheme) > 0;
+  if (in_wg && launch_solve_wg(*sh, F_dev, ld, D_dev, ld, st, max_steps, s) != 0) {
+    (void)hipGetLastError();    // the device refused the launch (nothing ran): the direct steps
+    in_wg = false;
+  }
+  if (!in_wg) {
     // The iterate buffers hold kNaMatrix values each; the kernels index rows with this call's
     // stride, and every entry they read is written before (f_0 writes all of X_0 including its
     // zero padding, every step all of its output), so nothing left by an earlier call needs

@@ -2144,16 +2144,18 @@ __global__ __launch_bounds__(kWgThreads) void solve_wg_kernel(SnfHeader h,
   for (int i = tid; i < (int)(sizeof(SnfHeader) / 4); i += kWgThreads) o[i] = ((const unsigned*)&hs)[i];
 }
 
+// (The launch's own status: an error that an earlier call left must not count as a refusal, as the
+// caller would then run the direct steps beside the launched solve.)
 template <int NB>
-static int launch_wg(size_t bytes, const SnfHeader& h, const double* F, int64_t ldf, double* D,
+static int launch_wg(size_t bytes, SnfHeader h, const double* F, int64_t ldf, double* D,
                      int64_t ldd, SnfState* out, int max_steps, hipStream_t s) {
   if (bytes > ((size_t)64 << 10) &&
       hipFuncSetAttribute((const void*)solve_wg_kernel<NB>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
     return -1;
-  hipLaunchKernelGGL(solve_wg_kernel<NB>, dim3(1), dim3(kWgThreads), bytes, s, h, F, ldf, D, ldd,
-                     out, max_steps);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  void* args[] = {&h, &F, &ldf, &D, &ldd, &out, &max_steps};
+  return hipLaunchKernel((const void*)solve_wg_kernel<NB>, dim3(1), dim3(kWgThreads), args, bytes,
+                         s) == hipSuccess ? 0 : -1;
 }
 
 int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D, int64_t ldd,

@@ -180,7 +180,8 @@ struct StepOperands {
 };
 
 // The whole FP64 solve in one workgroup, iterates in LDS: the iterate buffers one scheme needs
-// at order n fit (solve_wg_bytes > 0).
+// at order n fit (solve_wg_bytes > 0).  Not 0: the launch was refused, and the caller takes the
+// direct steps.
 size_t solve_wg_bytes(int64_t n, int scheme);
 int launch_solve_wg(const SnfHeader& h, const double* F, int64_t ldf, double* D, int64_t ldd,
                     SnfState* out, int max_steps, hipStream_t s);
