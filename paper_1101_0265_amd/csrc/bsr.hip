@@ -1024,7 +1024,7 @@ static int build_lookup(BsrBuf& b, int nb, int W, hipStream_t s) {
 struct StepStage {
   size_t cntP, plan, cntN, rpN, tri, flags, total;
   size_t tiles0;                  // first tile of the plan, in words: row_ptr of P comes first
-  StepStage(int nb, int64_t nflags) {
+  StepStage(int nb, int64_t NT) {          // NT super-tiles a side
     size_t o = 0;
     auto take = [&](size_t bytes) {
       const size_t at = o;
@@ -1035,9 +1035,9 @@ struct StepStage {
     cntP = take((size_t)nb * 4);
     cntN = take((size_t)nb * 4);
     rpN = take((size_t)(nb + 1) * 4);
-    flags = take((size_t)nflags);
+    flags = take((size_t)(NT * NT));
     tiles0 = ((size_t)nb + 1 + 15) / 16 * 16;
-    plan = take((tiles0 + (size_t)nflags) * 4);
+    plan = take((tiles0 + (size_t)(NT * (NT + 1) / 2)) * 4);
     total = o;
   }
 };
@@ -1094,9 +1094,9 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
   // 2. symbolic, and 3. the super-tiles it leaves; one wait for what the host needs of both
   const int NT = (nb + kSup - 1) / kSup;
   const int64_t nflags = (int64_t)NT * NT;
-  const StepStage st(nb, nflags);
+  const StepStage st(nb, NT);
   if ((rc = P.bm.reserve((size_t)nb * W)) || (rc = P.pre.reserve((size_t)nb * W)) ||
-      (rc = ensure_pinned(w, st.total)) || (rc = w->plan.reserve(st.tiles0 + nflags)))
+      (rc = ensure_pinned(w, st.total)))
     return rc;
   char* pin = (char*)w->pinned;
   hipLaunchKernelGGL(bsr_symbolic_kernel, dim3(nb), dim3(256), W * sizeof(uint32_t), s,
@@ -1136,7 +1136,9 @@ static int bsr_step(BsrWorkspace* w, BsrBuf& X, BsrBuf& B, BsrBuf& L, BsrBuf& N,
           if (ti != tj && hf[(int64_t)ti * NT + tj]) tl[ntiles++] = (int32_t)((ti << 16) | tj);
   for (int t = 0; t < NT; ++t)
     if (hf[(int64_t)t * NT + t]) tl[ntiles++] = (int32_t)((t << 16) | t);
-  if ((rc = w->partials.reserve((size_t)(ntiles + nb) * 4))) return rc;
+  if ((rc = w->partials.reserve((size_t)(ntiles + nb) * 4)) ||
+      (rc = w->plan.reserve(st.tiles0 + ntiles)))
+    return rc;
   BSR_HIP(hipMemcpyAsync(w->plan.p, plan, (st.tiles0 + ntiles) * sizeof(int32_t),
                          hipMemcpyHostToDevice, s));
   const int32_t* rowP = w->plan.p;
