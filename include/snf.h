@@ -455,7 +455,8 @@ int snf_gap_bounds(const double* F_dev, const double* D_dev, int64_t n, int64_t 
                    const double* start_dev, double* out, void* stream);
 
 /* Bytes of device workspace snf_purify_dense needs for order n (allocated on demand); the
-   P_{m,m} schemes take one more n_pad x n_pad FP64 buffer (n_pad = n rounded up to 128). */
+   P_{m,m} and P_{i,j} schemes take one more FP64 buffer, n_pad x n_pad with n_pad = n rounded
+   up to 128 (up to n = 2112 rows and columns of up to n + 111 values). */
 size_t snf_workspace_bytes(int64_t n, snf_precision precision);
 
 /* Release the calling device's cached workspace (it is re-created on the next call). */

@@ -434,9 +434,13 @@ const char* snf_strerror(int status) {
 size_t snf_workspace_bytes(int64_t n, snf_precision precision) {
   if (n <= 0) return 0;
   const int64_t np = round_up(n, kTile);
-  const size_t elems = (size_t)np * (size_t)np;
+  // (the direct steps' rows can be longer than n_pad)
+  const int64_t rows =
+      precision == SNF_P_FP64 ? std::max(np, direct_max_stride(n)) : np;
+  const size_t elems = (size_t)rows * (size_t)rows;
   return elems * (3 * sizeof(double) + 3 * (size_t)lowp_bytes_for(precision)) +
-         (size_t)(num_product_tiles(np, 1) + kF0Blocks) * 4 * sizeof(double) + sizeof(SnfState);
+         (size_t)(num_product_tiles(np, 1) + kF0Blocks + 2 * kDirectSlots) * 4 * sizeof(double) +
+         sizeof(SnfState) + 2 * sizeof(SnfHeader);
 }
 
 int snf_release_workspace(void) {

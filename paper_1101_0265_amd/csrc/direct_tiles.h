@@ -27,6 +27,16 @@ inline int64_t direct_stride(int64_t n, int tile) {
   return w % 256 ? w : w + 16;
 }
 
+// The longest rows that the direct steps may take for order n on any device, 0 beyond their range.
+inline int64_t direct_max_stride(int64_t n) {
+  int64_t ld = 0;
+  for (int t = 32; t <= 96; t += 16) {
+    const int64_t nt = (n + t - 1) / t;
+    if (nt * (nt + 1) / 2 <= kDirectThreads && direct_stride(n, t) > ld) ld = direct_stride(n, t);
+  }
+  return ld;
+}
+
 // The tile of snf_purify_dense_noalloc, whose buffers hold rows of max_ld values and which has no
 // other path: that of snf_purify_dense, or, where the device has too few compute units for one
 // (a part of a partitioned GPU) or the rows do not fit, what 256 units would take.  A step needs no
