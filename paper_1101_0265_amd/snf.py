@@ -163,6 +163,18 @@ def _check_dense(t, name):
         raise ValueError(f"{name} must be a square row-major matrix")
 
 
+def _dense_out(like, out, name="out"):
+    """``out``, or a new tensor, with the shape and row stride of ``like``: the library writes the
+    result with the operand's row stride (a slice's ``empty_like`` has a shorter one)."""
+    import torch
+    if out is None:
+        return torch.empty_strided(like.shape, like.stride(), dtype=like.dtype, device=like.device)
+    _check_dense(out, name)
+    if out.shape != like.shape or (like.shape[0] > 1 and out.stride(0) != like.stride(0)):
+        raise ValueError(f"{name} must have the operand's shape and row stride")
+    return out
+
+
 def make_params(*, lambda_min, lambda_max, mu=float("nan"), xi=float("nan"),
                 homo=float("nan"), lumo=float("nan"), n_occ=-1, tol=1e-10, max_iter=200,
                 flags=0, gap_switch=0.0, lowp_floor=0.0, poly_ij=None,
@@ -205,11 +217,9 @@ def purify_dense(F, scheme: str = "snf_varmu", precision: str = "fp64", *, out=N
     (varying-mu), n_occ, tol, max_iter, flags, gap_switch, lowp_floor, poly_ij = (i, j) for
     the P_{i,j} schemes (see snf_params).
     """
-    import torch
     _check_dense(F, "F")
     n = F.shape[0]
-    D = out if out is not None else torch.empty_like(F)
-    _check_dense(D, "out")
+    D = _dense_out(F, out)
     p = make_params(**params)
     res = Result()
     logs = (LogRec * LOG_MAX)() if want_log else None
@@ -226,12 +236,11 @@ def step_dense(A, B, c2: float, c1: float, c0: float, precision: str = "fp64", *
                stream=None) -> tuple:
     """Y = c2 A.B + c1 A + c0 I with FP64 sums (||A.B - A||_F^2, tr Y, ||Y||_F^2).
     Returns (Y, sums tuple, product-kernel milliseconds)."""
-    import torch
     _check_dense(A, "A")
     _check_dense(B, "B")
     if A.shape != B.shape or A.stride(0) != B.stride(0):
         raise ValueError("A and B must have the same shape and row stride")
-    Y = out if out is not None else torch.empty_like(A)
+    Y = _dense_out(A, out)
     sums = (ctypes.c_double * 3)()
     ms = ctypes.c_double(0.0)
     rc = lib().snf_step_dense(A.data_ptr(), B.data_ptr(), A.shape[0], A.stride(0), c2, c1,
@@ -396,12 +405,11 @@ class Server:
                       out=None, **params) -> int:
         """Submit a float64 CUDA tensor F (kept alive until completion); D is written to
         ``out`` (allocated if None), returned by poll/wait."""
-        import torch
         _check_dense(F, "F")
         if not F.is_contiguous():
             raise ValueError("F must be contiguous")
         n = F.shape[0]
-        D = out if out is not None else torch.empty_like(F)
+        D = _dense_out(F, out)
         p = make_params(**params)
         t = ctypes.c_uint64(0)
         rc = lib().snf_serve_submit_device(self._h, F.data_ptr(), n, ctypes.byref(p),
