@@ -2189,19 +2189,27 @@ void launch_schedule(SnfState* st, const double* partials, int count, int init, 
 // ---------------------------------------------------------------------------------------
 static unsigned copy_blocks(int64_t rows) { return (unsigned)(rows < 2048 ? rows : 2048); }
 
+// Two values at any 8-byte address of global memory, as one 16-byte access (which the target allows
+// at 4-byte steps there).  Rows that are not 16-byte aligned took 8-byte accesses 32 bytes apart
+// from lane to lane: a two-operand FP64 step of n = 8191 spent 890 us beside its product, one of
+// 3001 169, this 702 and 139 (the copies before that, element by element, 767 and 150).
+typedef double dbl2a8 __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ dbl2a8 gload2(const double* p) {
+  return *(const __attribute__((address_space(1))) dbl2a8*)(p);
+}
+
 // dst[r][c] = src[r][c] for r, c < n: a row per workgroup and turn (no index division), four
-// columns per thread, as two 16-byte accesses where both rows allow them.
+// columns per thread, as two 16-byte accesses.
 __device__ __forceinline__ void copy_rows(const double* __restrict__ src, int64_t lds_,
                                           double* __restrict__ dst, int64_t ldd, int64_t n) {
-  const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0 && !((lds_ | ldd) & 1);
   for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
     const double* p = src + r * lds_;
     double* q = dst + r * ldd;
     for (int64_t c = 4 * (int64_t)threadIdx.x; c < n; c += 4 * (int64_t)blockDim.x) {
-      if (vec && c + 4 <= n) {
-        const u32x4 v0 = gload16(p + c), v1 = gload16(p + c + 2);
-        *(u32x4*)(q + c) = v0;
-        *(u32x4*)(q + c + 2) = v1;
+      if (c + 4 <= n) {
+        const dbl2a8 v0 = gload2(p + c), v1 = gload2(p + c + 2);
+        *(dbl2a8*)(q + c) = v0;
+        *(dbl2a8*)(q + c + 2) = v1;
       } else {
         for (int64_t e = c; e < n && e < c + 4; ++e) q[e] = p[e];
       }
@@ -2215,15 +2223,13 @@ __global__ __launch_bounds__(256) void pad_copy_kernel(const double* __restrict_
                                                        int64_t ld, double* __restrict__ dst,
                                                        int64_t np, void* __restrict__ lp,
                                                        int lowp_kind) {
-  const bool vec = ((uintptr_t)src & 15) == 0 && !(ld & 1);
   for (int64_t r = blockIdx.x; r < np; r += gridDim.x) {
     const double* p = src + r * ld;
     for (int64_t c = 4 * (int64_t)threadIdx.x; c < np; c += 4 * (int64_t)blockDim.x) {
       double v[4] = {0.0, 0.0, 0.0, 0.0};
       if (r < n) {
-        if (vec && c + 4 <= n) {
-          const double2 v0 = __builtin_bit_cast(double2, gload16(p + c));
-          const double2 v1 = __builtin_bit_cast(double2, gload16(p + c + 2));
+        if (c + 4 <= n) {
+          const dbl2a8 v0 = gload2(p + c), v1 = gload2(p + c + 2);
           v[0] = v0.x;
           v[1] = v0.y;
           v[2] = v1.x;
