@@ -169,6 +169,10 @@ def _dense_out(like, out, name="out"):
     import torch
     if out is None:
         return torch.empty_strided(like.shape, like.stride(), dtype=like.dtype, device=like.device)
+    if isinstance(out, torch.Tensor) and out.shape == like.shape and \
+            out.stride() == like.stride() and out.dtype == like.dtype and \
+            out.device == like.device:
+        return out                                  # (the operand passed _check_dense)
     _check_dense(out, name)
     if out.shape != like.shape or (like.shape[0] > 1 and out.stride(0) != like.stride(0)):
         raise ValueError(f"{name} must have the operand's shape and row stride")
