@@ -456,14 +456,19 @@ static int ensure(BoundsWorkspace* w, int64_t np, int kmax, int nv) {
   return SNF_OK;
 }
 
-// Tiles per strip: as many as leave each compute unit two strips (n = 4096: 544 strips of 4).
-// 40-step gap_bounds at n = 1000 / 2000 / 4096 / 6000: 1.59 / 2.28 / 4.02 / 6.36 ms with one
-// tile a strip, 1.74 / 1.98 / 4.00 / 5.34 with two, 1.58 / 1.98 / 3.80 / 5.48 by this rule (one,
-// two, four, four), 2.88 / 2.95 / 3.53 / 5.24 with eight at every order.
+// Tiles per strip, by the tiles a side alone: the more, the longer a workgroup's reads run on
+// while its partial row sums are few, until too few strips are left for the chip.  40-step
+// gap_bounds (spectral_bounds follows the same order within 5%), ms with 1, 2, 3, 4, 5, 8 tiles a
+// strip: n = 1000 1.50 1.69 1.88 2.07 2.25 2.83; 2048 2.15 1.94 2.10 2.17 2.34 2.90; 3072 2.95 2.36
+// 2.59 2.79 2.70 3.20; 4096 3.93 3.29 2.88 3.06 3.30 3.41; 6000 6.44 5.29 5.50 5.15 5.59 5.12; 9000
+// 13.3 11.2 10.9 10.9 11.0 11.3; 16384 42.1 34.3 31.0 31.8 31.0 31.0.
+// The grid is an odd number of strips wide: workgroups go to the 8 XCDs in turn, and where the
+// width divided by 8 a row's strip k ran on the same XCD in every row, of which the later ones have
+// no strip k (four tiles a strip: n = 8000 11.9 ms, 8.99 with an odd width; 4096 3.80, 3.06).
 static void launch_symv(SymvArgs& g, hipStream_t s, bool abs_mode = false) {
   const int nt = (int)(g.np / kT);
-  g.strip = nt >= 48 ? 4 : nt >= 32 ? 2 : 1;
-  const dim3 grid((nt + g.strip - 1) / g.strip, nt);
+  g.strip = nt < 32 ? 1 : nt < 52 ? 2 : nt < 72 ? 3 : nt < 200 ? 4 : 5;
+  const dim3 grid(((nt + g.strip - 1) / g.strip) | 1, nt);
   if (abs_mode) hipLaunchKernelGGL((symv_tile_kernel<1, true>), grid, dim3(256), 0, s, g, nt);
   else if (g.nv == 1) hipLaunchKernelGGL((symv_tile_kernel<1, false>), grid, dim3(256), 0, s, g, nt);
   else hipLaunchKernelGGL((symv_tile_kernel<2, false>), grid, dim3(256), 0, s, g, nt);
