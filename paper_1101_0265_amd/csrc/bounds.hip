@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/snf.h"
+#include "wave_sum.h"
 
 namespace snf {
 namespace {
@@ -59,17 +60,11 @@ struct SymvArgs {
   int j;
 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // The norm from its nt partial sums, by every wave for itself (fixed order).
 __device__ __forceinline__ double norm_of(const double* __restrict__ nrm2, int nt) {
   double s = 0.0;
   for (int i = threadIdx.x & 63; i < nt; i += 64) s += nrm2[i];
-  return sqrt(wave_sum(s));
+  return sqrt(wave_sum_rows(s));
 }
 
 // One workgroup per strip of up to g.strip upper tiles (I, J), (I, J + 1), ... of block row I:
@@ -204,7 +199,7 @@ __global__ __launch_bounds__(1024) void symv_reduce_kernel(SymvArgs g, int nt) {
   __syncthreads();
   const double y = acc[0][r];
   for (int k = grp; k <= g.j; k += 16) {
-    const double d = wave_sum(g.V[v][(size_t)k * g.np + i] * y);
+    const double d = wave_sum_rows(g.V[v][(size_t)k * g.np + i] * y);
     if (r == 0) g.hp[v][(size_t)k * nt + B] = d;
   }
 }
@@ -234,6 +229,8 @@ struct Chains {
 // partials of what the next kernel needs: the second pass's dot products (PASS 0) or ||w||^2
 // (PASS 1).  Every block sums all partials of h itself, which costs less than a launch; h_j goes
 // into alpha_j (set on pass 0, added on 1).
+// Long runs on small matrices, where one workgroup has every sum to itself, are bound by the wave
+// sums (500 steps at n = 10: 25.2 ms with shuffles, 15.7 by DPP).
 template <int PASS>
 __global__ __launch_bounds__(1024) void lz_update_kernel(Chains c, int j) {
   __shared__ double h[kMaxSteps];
@@ -246,7 +243,7 @@ __global__ __launch_bounds__(1024) void lz_update_kernel(Chains c, int j) {
   for (int k = grp; k <= j; k += 16) {
     double s = 0.0;
     for (int b = r; b < nt; b += 64) s += hp[(size_t)k * nt + b];
-    s = wave_sum(s);
+    s = wave_sum_rows(s);
     if (r == 0) h[k] = s;
   }
   __syncthreads();
@@ -265,7 +262,7 @@ __global__ __launch_bounds__(1024) void lz_update_kernel(Chains c, int j) {
     c.w[(size_t)ch * c.np + i] = w;
     acc[0][r] = w;
     if (PASS == 1) {
-      const double q = wave_sum(w * w);
+      const double q = wave_sum_rows(w * w);
       if (r == 0) c.nrm2[(size_t)ch * nt + B] = q;
     }
   }
@@ -274,7 +271,7 @@ __global__ __launch_bounds__(1024) void lz_update_kernel(Chains c, int j) {
   const double w = acc[0][r];
   double* hn = c.hp + ((size_t)ch * 2 + 1) * (c.kmax + 1) * nt;
   for (int k = grp; k <= j; k += 16) {
-    const double d = wave_sum(V[(size_t)k * c.np + i] * w);
+    const double d = wave_sum_rows(V[(size_t)k * c.np + i] * w);
     if (r == 0) hn[(size_t)k * nt + B] = d;
   }
 }
@@ -309,7 +306,7 @@ __global__ __launch_bounds__(kT) void lz_start_kernel(Chains c, const double* st
   double v = 0.0;
   if (i < n) v = start ? start[i] : splitmix_uniform((uint64_t)i);
   c.w[(size_t)ch * c.np + i] = v;
-  const double q = wave_sum(v * v);
+  const double q = wave_sum_rows(v * v);
   if (threadIdx.x == 0) c.nrm2[(size_t)ch * c.nt + blockIdx.x] = q;
 }
 

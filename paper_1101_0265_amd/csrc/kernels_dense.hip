@@ -29,6 +29,7 @@
 
 #include "schedule_math.h"
 #include "snf_internal.h"
+#include "wave_sum.h"
 
 namespace snf {
 
@@ -60,28 +61,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
-}
-
-// The same sum in another order, without the shuffles' trips through LDS: within rows of 16
-// lanes by DPP, then the four rows' sums from scalar registers (0.1 us against 0.4).
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-  return v + __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
-__device__ __forceinline__ double wave_sum_rows(double v) {
-  v = dpp_add<0xB1>(v);       // lanes 1, 0, 3, 2 of each quad
-  v = dpp_add<0x4E>(v);       // lanes 2, 3, 0, 1
-  v = dpp_add<0x141>(v);      // the other quad of each eight (row_half_mirror)
-  v = dpp_add<0x140>(v);      // the other eight of each row (row_mirror)
-  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // Sum three values over the block (up to 8 waves), in wave order; result valid in thread 0.
