@@ -262,13 +262,20 @@ void launch_solve_start(const SolveStart& a, const double* F, int64_t ld, int lo
 void launch_solve_finish(const SnfState* st, const Buffers* bufs_dev, int64_t n, int64_t np,
                          double* D, int64_t ld, SnfState* out, hipStream_t s);
 
-// Tile side of a request's products in FP64 and FP32: 64x64 while its tiles' sums fit the slots
-// that its layout holds anyway (kF0Blocks, up to order 2816; beyond, one request has tiles
-// enough), else 128x128, as the BF16 products always.
+// Tile side of a request's products in FP64 and FP32: 64x64 up to a padded order of 2048, else
+// 128x128, as the BF16 products always.  The rule takes the order alone, so that a request's
+// results do not depend on the requests beside it, and is drawn where large bursts of one order
+// take as long with either.  16 at once, 128x128 / 64x64 tiles, FP64: n = 1500 19.6 / 19.2 ms, 2048
+// 42.7 / 42.7, 2400 66.0 / 69.1, 2800 100 / 105; FP32 start: 14.9 / 13.7, 30.0 / 28.9, 45.5 / 46.3,
+// 67.6 / 70.1.  (40 FP64 of 1792 to 2048: 2% slower; counts whose 128x128 tiles just fill the chip
+// lose up to 7%, six of 1536 or four of 1920, the others gain up to 2.7 times.  Alone 64x64 would
+// gain up to 2600: n = 2400 FP64 6.70 / 4.97 ms.)
 constexpr int kFineTile = 64;
+constexpr int64_t kFineMaxNp = 2048;
+static_assert((kFineMaxNp / kFineTile) * (kFineMaxNp / kFineTile + 1) / 2 <= kF0Blocks,
+              "the tiles' sums fit the slots that a request's layout holds");
 inline int request_tile(int64_t np, int prec) {
-  const int64_t nt = np / kFineTile;
-  return prec != kPrecBF16 && nt * (nt + 1) / 2 <= kF0Blocks ? kFineTile : kTile;
+  return prec != kPrecBF16 && np <= kFineMaxNp ? kFineTile : kTile;
 }
 
 // One step of every active request.  Each product kernel runs on its own list of requests, those
