@@ -1407,8 +1407,8 @@ __device__ __forceinline__ void schedule_body(SnfState* __restrict__ sg,
 // 6 us of launch boundary, cold operand loads and epilogue.
 // A scale-and-fold solve of 19 products (wall time), this against the engine's three kernels (n
 // > 896), 32x32 tiles and a schedule kernel (256 < n <= 896), those in one cooperative launch
-// with grid barriers (n <= 256): n = 256 0.27 / 0.44 ms, 400 0.33 / 0.58, 704 0.47 / 0.89, 1056
-// 0.79 / 1.31, 1408 1.32 / 1.97, 1760 2.1 / 3.1, 2112 3.2 / 4.5.  A step at n = 256 takes 8 us: 1.7
+// with grid barriers (n <= 256): n = 256 0.27 / 0.43 ms, 400 0.32 / 0.58, 704 0.45 / 0.88, 1056
+// 0.77 / 1.26, 1408 1.25 / 1.92, 1760 2.03 / 3.07, 2112 3.19 / 4.46.  A step at n = 256 takes 8 us: 1.7
 // until the operands are there (the schedule, 2.5 us from its sums on, beside the 3 us of
 // products), 2 the epilogue, 2 to the next launch's first instruction.
 // ---------------------------------------------------------------------------------------
@@ -1680,6 +1680,10 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
             A.get(slot, m), B.get(slot, q), acc[slot % S][m][q], 0, 0, 0);
   };
   dbl4 tot[PH > 1 ? TB : 1][PH > 1 ? QB : 1];           // sums of the phases before this one
+#pragma unroll
+  for (int m = 0; m < (PH > 1 ? TB : 1); ++m)
+#pragma unroll
+    for (int q = 0; q < (PH > 1 ? QB : 1); ++q) tot[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
   // the linear term's values of a band of 32 rows; the first band's ahead of the product where
   // the registers allow it
   constexpr bool XA = TB <= 4;
@@ -1719,10 +1723,6 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
       }
     };
     if constexpr (PH > 1) {
-#pragma unroll
-      for (int m = 0; m < TB; ++m)
-#pragma unroll
-        for (int q = 0; q < QB; ++q) tot[m][q] = dbl4{0.0, 0.0, 0.0, 0.0};
       const int span = ((ke - kb + PH - 1) / PH + PD - 1) / PD * PD;
 #pragma unroll 1
       for (int end = kb + span; end < ke; end += span) {
@@ -1921,9 +1921,9 @@ void StepOperands::next(int (&op)[3]) {
 // latency, so nothing leaves the compute unit between steps: no launch, no grid barrier, no
 // memory.  Eight waves share the 16x16 blocks of the upper triangle; a step's results stay in
 // registers until the sums are known, so X needs no second buffer and is still whole when the
-// stop test passes.  A step at n = 64 takes 4.9 us: 2.6 the products, 0.4 the sums, 1.4 the
+// stop test passes.  A step at n = 64 takes 4.5 us: 2.3 the products, 0.4 the sums, 1.4 the
 // schedule, 0.4 the writes.  The 19 products of the solves above at n = 17 / 40 / 64 / 80: 0.10 /
-// 0.12 / 0.14 / 0.17 ms, against 0.38 ms in a cooperative launch of 32x32 tiles.  Above order 80 the
+// 0.11 / 0.13 / 0.16 ms, against 0.37 ms in a cooperative launch of 32x32 tiles.  Above order 80 the
 // direct steps take over (at 96, with a third block for some waves, such a solve took 0.23 ms
 // against their 0.22).
 // ---------------------------------------------------------------------------------------
