@@ -195,9 +195,12 @@ typedef struct {
   double trace_err;       /* tr D - n_occ (0 if n_occ unknown)                          */
   double alpha_last, beta_last, betabar_last;
   double device_ms;       /* f_0 through the copy-out of D, HIP events on `stream`      */
-  double product_ms;      /* summed product-kernel time (SNF_FLAG_TIME_PRODUCTS); at
-                             padded order <= 256 in FP64 the whole step loop is one
-                             launch, and this is its duration                          */
+  double product_ms;      /* summed time of the product launches (SNF_FLAG_TIME_PRODUCTS).
+                             FP64 solves up to order 2112 run a step as one launch, which
+                             includes the schedule of the step before; where the iterates
+                             fit one compute unit's LDS (order <= 80, for the P_{m,m} and
+                             P_{i,j} schemes 64; not with the subspace correction) the
+                             whole solve is one launch, and this is its duration       */
   uint8_t branch[SNF_LOG_MAX]; /* SNF_BRANCH_* of iteration i                            */
   double flops;           /* algorithmic flops of all products: n^2 (n+1) each (only the
                              upper triangle of a symmetric product is needed); block-sparse:

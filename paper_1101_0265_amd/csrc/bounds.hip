@@ -71,10 +71,10 @@ __device__ __forceinline__ double norm_of(const double* __restrict__ nrm2, int n
 // the row part sum_J M_IJ x_J (for block I) and each tile's column part M_IJ^T x_I (for block J).
 // Every thread keeps 16 values of the tile in registers (4 rows x 4 columns, 16 apart) and uses
 // each for both parts, the next tile's 16 loads in flight meanwhile; sums run over the 16 lanes
-// of a row once per strip and over the 16 threads of a column once per tile.  19 us with one
-// vector and 24 us with two at n = 4096 (67 MB: 3.5 and 2.8 TB/s).  x through LDS instead, or
+// of a row once per strip and over the 16 threads of a column once per tile.  16 us with one
+// vector and 17 us with two at n = 4096 (68 MB: 4.3 and 4.0 TB/s).  x through LDS instead, or
 // x_J loaded a tile ahead, cost the two-vector kernel registers (3 -> 2 waves per SIMD) or time
-// (24 -> 26 us).
+// (24 -> 26 us, with strips of four tiles).
 template <int NV, bool ABS>
 __global__ __launch_bounds__(256) void symv_tile_kernel(SymvArgs g, int nt) {
   const int I = blockIdx.y, J0 = I + (int)blockIdx.x * g.strip;
