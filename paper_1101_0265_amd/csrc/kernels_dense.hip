@@ -1561,6 +1561,7 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
   // this 1.26e-13; Algorithm 1, n = 1000: 1.98e-13, 1.53e-13, 1.23e-13), at the same time within
   // 1%.  From T = 80 on the engine had two or three slices.
   constexpr int S = TB == 2 ? 4 : 1, PH = TB == 3 ? 4 : TB == 4 ? 2 : 1;
+  static_assert(S == 1 || S == 4, "added by pairs");
   constexpr int P = TB / 2, LW = T + 2;
   constexpr int SWAVE = SW ? 4 * NC : 0;
   // the product starts ahead of the schedule; the largest tiles wait for it, as their product
@@ -1751,7 +1752,6 @@ __global__ __launch_bounds__(kDirectThreads* NC + (SW ? 64 : 0)) void direct_ste
     for (int q = 0; q < QB; ++q) {
       if constexpr (S == 4)
         acc[0][m][q] = (acc[0][m][q] + acc[1][m][q]) + (acc[2][m][q] + acc[3][m][q]);
-      if constexpr (S == 2) acc[0][m][q] += acc[1][m][q];
       if constexpr (PH > 1) acc[0][m][q] += tot[m][q];
     }
 
