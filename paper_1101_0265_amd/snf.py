@@ -168,6 +168,8 @@ def _dense_out(like, out, name="out"):
     result with the operand's row stride (a slice's ``empty_like`` has a shorter one)."""
     import torch
     if out is None:
+        if like.is_contiguous():
+            return torch.empty_like(like)
         return torch.empty_strided(like.shape, like.stride(), dtype=like.dtype, device=like.device)
     if isinstance(out, torch.Tensor) and out.shape == like.shape and \
             out.stride() == like.stride() and out.dtype == like.dtype and \
